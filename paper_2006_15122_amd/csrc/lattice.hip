@@ -102,9 +102,10 @@ static void layout(const lattice_params* p, size_t* off_part, size_t* off_part2,
   *off_part = o;
   o = align_up(o + part_doubles * sizeof(double), 256);
   // every other pass of a chain writes its records here: at most mb blocks
-  // (tiles of at least 1024 sites) of 4 scalar or 11 U(1) sums
+  // (tiles of at least 1024 sites) of 4 scalar or 11 U(1) sums; SU(2) x U(1)
+  // blocks take 256 sites or more and write 7
   *off_part2 = o;
-  o = align_up(o + (size_t)mb * 16 * sizeof(double), 256);
+  o = align_up(o + (is_su2(*p) ? (size_t)(V / 256) * 16 : (size_t)mb * 16) * sizeof(double), 256);
   *off_spec = o;
   o = align_up(o + (size_t)(spec_blocks((int)N) + 2) * spec_bins((int)N) * 24, 256);
   *off_buf0 = o;

@@ -46,13 +46,10 @@ __device__ __forceinline__ void sincos_m1(double x, double* s, double* cm1) {
   sincos(x, s, &c);
   *cm1 = cos_m1(c, *s);
 }
-__device__ __forceinline__ void sincos_m1(float x, float* s, float* cm1) {
-  if (!(fabsf(x) <= 64.f)) {
-    float c;
-    sincosf(x, s, &c);
-    *cm1 = cos_m1(c, *s);
-    return;
-  }
+// The same for |x| <= 64 without the check: the phases of wrapped links and
+// sums of four of them.
+__device__ __forceinline__ void sincos_m1_near(double x, double* s, double* cm1) { sincos_m1(x, s, cm1); }
+__device__ __forceinline__ void sincos_m1_near(float x, float* s, float* cm1) {
   const float k = rintf(x * 0.636619772f);
   float r = fmaf(-k, 1.57079637f, x);
   r = fmaf(-k, -4.37113883e-08f, r);
@@ -70,6 +67,15 @@ __device__ __forceinline__ void sincos_m1(float x, float* s, float* cm1) {
   *s = (q & 2) ? -sb : sb;
   const float cx = ((q + 1) & 2) ? -cb : cb;
   *cm1 = q == 0 ? cr : cx - 1.f;
+}
+__device__ __forceinline__ void sincos_m1(float x, float* s, float* cm1) {
+  if (!(fabsf(x) <= 64.f)) {
+    float c;
+    sincosf(x, s, &c);
+    *cm1 = cos_m1(c, *s);
+    return;
+  }
+  sincos_m1_near(x, s, cm1);
 }
 
 }  // namespace cl

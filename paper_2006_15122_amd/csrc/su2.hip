@@ -1,9 +1,8 @@
 // Doublet with SU(2) x U(1) gauge links on gfx950 (Sec. 6: staggered
 // leapfrog, velocity Verlet and its Yoshida compositions; initial state
-// Sec. 7.2).  Every pass of the shared schedule is three kernels: a
-// pointwise drift of the fields and links into the other state buffer, a
-// kick of every momentum from the drifted fields with per-block FP64 partial
-// sums, and the FP64 finish that advances a and b.
+// Sec. 7.2).  Every pass of the shared schedule is one kernel, drift and kick
+// in one sweep from one state buffer into the other with per-block FP64
+// partial sums, whose finish (a and b) the next pass of a chain applies.
 //
 // Components (storage precision, N^3 each):
 //   0..3   Phi = (Phi_0, Phi_1) as Re Phi_0, Im Phi_0, Re Phi_1, Im Phi_1
@@ -23,6 +22,7 @@
 //             + a^{alpha-1} 2/(g dx^3) sum_{j!=i}(c_a[U_ij(n)] - c_a[U_j(n-j)^dag U_ij(n-j) U_j(n-j)])
 // with c_a the vector part of an SU(2) element.  SU(2) elements are carried
 // as quaternions (w, x, y, z) = w + i(x sigma_1 + y sigma_2 + z sigma_3).
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -39,8 +39,9 @@ constexpr int kPH = 0, kPI = 4, kTH = 8, kPA = 11, kUL = 14, kPB = 26;
 constexpr int kSu2Acc = 16;  // the workspace reserves 16 FP64 partials per 256-site block
 constexpr int kSu2GaussAcc = 6;
 
+// (aligned so that a quaternion moves as one 16-byte LDS access in FP32)
 template <typename T>
-struct Q4 {
+struct alignas(16) Q4 {
   T w, x, y, z;
 };
 template <typename T>
@@ -84,7 +85,7 @@ __device__ __forceinline__ void qapply(const Q4<T>& q, T wm, const Cx2<T> (&v)[2
 template <typename T>
 __device__ __forceinline__ T qw_m1(const Q4<T>& q) {
   const T v2 = q.x * q.x + q.y * q.y + q.z * q.z;
-  return q.w > T(0) ? -v2 / (T(1) + q.w) : q.w - T(1);
+  return q.w > T(0) ? -quot_t(v2, T(1) + q.w) : q.w - T(1);
 }
 // Im(conj(a) b), Re(conj(a) b)
 template <typename T>
@@ -108,7 +109,6 @@ struct Su2Args {
   int N;
   double dx, alpha, fmp2, lam, m2, e, g, wf2, h;
   int expand;
-  int fields_in_dst;  // the kick reads the drifted fields from dst (else src)
   PassDesc pd;
   double* partials;
   DevState* st;
@@ -134,366 +134,650 @@ __device__ void su2_block_partials(double (&acc)[NACC], double* partials) {
   if (tid < NACC) partials[(size_t)blockIdx.x * NACC + tid] = ((red[0][tid] + red[1][tid]) + red[2][tid]) + red[3][tid];
 }
 
-// Drift of the fields and links into dst (Sec. 6.2.1 and 6.2.2):
-//   Phi += wd h pi / a_mid^{3-alpha};
-//   V   <- (1 - i u)/(1 + i u) V,  u = e wd h dx pi_A / (2 a_mid^{1-alpha}), as th -= 2 atan u;
-//   U   <- (1 - i X)(1 + i X)^{-1} U = ((1 - |w|^2) - 2 i w.sigma)/(1 + |w|^2) U,
-//          w = g wd h dx pi_B / (4 a_mid^{1-alpha});
-// U is renormalised to unit length after the product (rounding only).
+// ---------------------------------------------------------------------------
+// The pass kernel: drift and kick of one pass in one sweep.
+//
+// A block owns a TY x TZ tile of the (y, z) plane and marches along x over XC
+// planes.  Each plane enters LDS drifted (Phi, the U(1) phases and the SU(2)
+// links of the tile and a one-site ring with corners); planes x and x+1 are
+// held.
+//
+// Every site computes each of its three plaquettes once, P_ij(n) = U_i(n)
+// U_j(n+i) U_i(n+j)^dag U_j(n)^dag, and hands the forces of the neighbours on:
+// the backward plaquettes a link force needs are the same P seen from one site
+// further, U_j(m)^dag P_ij(m) U_j(m) at n = m + j for link i and
+// U_i(m)^dag P_ij(m) U_i(m) at n = m + i for link j, i.e. rotations of P's
+// vector part.  The parallel-transported doublet W_d(m)^dag Phi(m) goes the same
+// way, so each link's sine and cosine are formed once.  What goes to x+1 stays
+// in registers, what goes to y+1 and z+1 passes through LDS; the
+// row y0-1 and the column z0-1 are computed by the waves without ring sites.
+//
+// Bound by its instruction stream: about 1600 VALU instructions a wave and
+// plane (45% of the issue slots at two waves per SIMD, which 252 VGPRs and
+// 79 KB of LDS per block allow).  At 128^3 in FP32 a pass takes 219 us, 64^3
+// 38 us and 192^3 700 us; a pointwise drift and a kick that read every
+// neighbour's links from memory took 484, 67 and 1560 us.  Ring threads in
+// waves of their own (six waves a block at 168 VGPRs) left one block on a CU
+// and spilled: 395 us.  FP64 takes half the tile so that a block's planes fit
+// (64^3: 129 us against 137, 96^3: 370 against 550).
+// ---------------------------------------------------------------------------
 template <typename T>
-__global__ __launch_bounds__(256) void su2_drift_kernel(Su2Args<T> A) {
-  const size_t V = (size_t)A.N * A.N * A.N;
-  const size_t s = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (s >= V) return;
-  const double a_in = A.st->a, b_in = A.st->b;
+struct Su2PassArgs {
+  const T* src;  // component c at src + c N^3
+  T* dst;
+  int N, XC, swizzle;
+  double dx, alpha, fmp2, lam, m2, e, g, wf2, h;
+  int expand;
+  PassDesc pd;
+  double* partials;
+  DevState* st;
+  PrevPass prev;  // finish of the previous pass of a chain (partials == nullptr: none)
+};
+
+// Sums of a stepping pass: pi_Phi^2, |W Phi_+ - Phi|^2, V, pi_A^2, 1 - cos Phi_ij,
+// pi_B^2, 1 - Tr U_ij/2 (LF: in and out of the kick added).  Observation passes
+// keep the kSu2Acc sums of the table above.
+constexpr int kSu2StepAcc = 7;
+
+// U^dag (i v.sigma) U as a vector: (w^2 - |q|^2) v + 2 (v.q) q - 2 w (v x q)
+template <typename T>
+struct V3 {
+  T x, y, z;
+};
+template <typename T>
+__device__ __forceinline__ V3<T> qrotate(const Q4<T>& u, const Q4<T>& p) {
+  const T s = u.w * u.w - (u.x * u.x + u.y * u.y + u.z * u.z);
+  const T d = T(2) * (p.x * u.x + p.y * u.y + p.z * u.z), w2 = T(2) * u.w;
+  return V3<T>{s * p.x + d * u.x - w2 * (p.y * u.z - p.z * u.y), s * p.y + d * u.y - w2 * (p.z * u.x - p.x * u.z),
+               s * p.z + d * u.z - w2 * (p.x * u.y - p.y * u.x)};
+}
+
+template <typename T, bool OBS>
+__device__ void su2_finish_state(const Su2PassArgs<T>& A, const PassDesc& pd, const DevState* in, const double* S,
+                                 DevState* out, double& a_next, double& b_next);
+template <int NACC, int NT>
+__device__ bool su2_reduce_records(const double* rec, int nb, double (&S)[NACC]);
+
+// one site's raw components
+template <typename T>
+struct Su2Raw {
+  T ph[4], pi[4], th[3], pa[3], pb[9];
+  Q4<T> u[3];
+};
+
+template <int TZ, int TY>
+struct Su2Tile {
+  static constexpr int NT = TZ * TY, LY = TY + 2, LZ = TZ + 2;
+  static constexpr int NR = 2 * LZ + 2 * TY;  // ring sites
+};
+
+template <typename T, int TZ, int TY, int WPE, bool OBS>
+__global__ __launch_bounds__(TZ* TY, WPE) void su2_pass_kernel(Su2PassArgs<T> A) {
+  using Tile = Su2Tile<TZ, TY>;
+  constexpr int LY = Tile::LY, LZ = Tile::LZ, NR = Tile::NR, NT = Tile::NT;
+  constexpr int NACC = OBS ? kSu2Acc : kSu2StepAcc;
+  static_assert(NR <= NT, "one ring site per thread");
+  // first thread of the row y0-1 and of the column z0-1: waves that own no
+  // ring site (where the block has four)
+  constexpr int ROW0 = NT >= 256 ? 128 : 0, COL0 = NT >= 256 ? 192 : 64;
+  static_assert(ROW0 + TZ <= COL0 && COL0 + TY <= NT, "row and column in different threads");
+  __shared__ Q4<T> LU[2][3][LY][LZ];  // drifted SU(2) links
+  __shared__ Q4<T> LP[2][LY][LZ];     // drifted Phi (re0, im0, re1, im1)
+  __shared__ T Lt[2][3][LY][LZ];      // drifted U(1) phases
+  // handed on to y+1 (0) and z+1 (1), at the receiver's place: (W^dag - 1) Phi,
+  // two rotated plaquettes, two plaquette sines
+  __shared__ Q4<T> Bh[2][TY][TZ];
+  __shared__ T Bv[2][8][TY][TZ];
+  __shared__ double red[NT / 64][NACC];
+
+  const int N = A.N;
+  const unsigned NN = (unsigned)N * N;
+  const size_t V = (size_t)NN * N;
+  const int tid = threadIdx.x;
+  int bid = blockIdx.x;
+  if (A.swizzle) bid = (bid & 7) * (gridDim.x >> 3) + (bid >> 3);
+  const int nzt = N / TZ, nyt = N / TY;
+  const int z0 = (bid % nzt) * TZ, y0 = ((bid / nzt) % nyt) * TY, x0 = (bid / (nzt * nyt)) * A.XC;
+
+  // places in the LDS tile of this thread's site and of its ring site
+  const int tz = tid % TZ, ty = tid / TZ, ly = 1 + ty, lz = 1 + tz;
+  const bool has_ring = tid < NR;
+  int rly, rlz;
+  if (tid < LZ) { rly = 0; rlz = tid; }
+  else if (tid < 2 * LZ) { rly = TY + 1; rlz = tid - LZ; }
+  else if (tid < 2 * LZ + TY) { rly = 1 + tid - 2 * LZ; rlz = TZ + 1; }
+  else { rly = 1 + tid - 2 * LZ - TY; rlz = 0; }
+  const unsigned plane = NN * (unsigned)sizeof(T);
+  auto column = [&](int y, int z) -> unsigned {
+    return ((unsigned)((y0 - 1 + y + N) % N) * N + (unsigned)((z0 - 1 + z + N) % N)) * (unsigned)sizeof(T);
+  };
+  const unsigned col = column(ly, lz), rcol = has_ring ? column(rly, rlz) : 0u;
+  const bool low_row = tid >= ROW0 && tid < ROW0 + TZ, low_col = tid >= COL0 && tid < COL0 + TY;
+
+  // Component c of the state through a scalar base address that steps from one
+  // component to the next and is opaque to the compiler: 70 bases kept across
+  // the loop overflow the scalar registers, and formed from the component
+  // number they become 64-bit vector arithmetic, three instructions a load.
+  struct Walk {
+    const char* p;
+    size_t st;
+    __device__ __forceinline__ Walk(const T* base, size_t V) : p(reinterpret_cast<const char*>(base)), st(V * sizeof(T)) {
+      asm volatile("" : "+s"(p));
+    }
+    __device__ __forceinline__ T* next(unsigned o) {
+      const char* q = p;
+      p += st;
+      asm volatile("" : "+s"(p));
+      return reinterpret_cast<T*>(const_cast<char*>(q) + o);
+    }
+  };
+  Su2Raw<T> raw, rraw;
+  auto load_site = [&](Su2Raw<T>& w, unsigned o) {
+    Walk c(A.src, V);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) w.ph[k] = *c.next(o);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) w.pi[k] = *c.next(o);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) w.th[i] = *c.next(o);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) w.pa[i] = *c.next(o);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      w.u[i].w = *c.next(o);
+      w.u[i].x = *c.next(o);
+      w.u[i].y = *c.next(o);
+      w.u[i].z = *c.next(o);
+    }
+#pragma unroll
+    for (int k = 0; k < 9; ++k) w.pb[k] = *c.next(o);
+  };
+  auto load_own = [&](int x) { load_site(raw, (unsigned)x * plane + col); };
+  auto load_ring = [&](int x) {
+    if (has_ring) load_site(rraw, (unsigned)x * plane + rcol);
+  };
+  // the first plane's loads need no coefficients: their latency overlaps the
+  // previous pass's finish
+  load_own((x0 - 1 + N) % N);
+
+  double a_in, b_in;
+  if (A.prev.partials) {
+    __shared__ double ab[2];
+    double S[kSu2StepAcc];
+    if (su2_reduce_records<kSu2StepAcc, NT>(A.prev.partials, A.prev.nblocks, S)) {
+      double an, bn;
+      su2_finish_state<T, false>(A, A.prev.pd, A.st, S, blockIdx.x == 0 ? A.prev.out : nullptr, an, bn);
+      ab[0] = an;
+      ab[1] = bn;
+    }
+    __syncthreads();
+    a_in = ab[0];
+    b_in = ab[1];
+  } else {
+    a_in = A.st->a;
+    b_in = A.st->b;
+  }
   const double hw = A.pd.wd * A.h;
   const double anew = A.expand ? a_in + hw * b_in : a_in;
   const double amid = 0.5 * (a_in + anew);
-  // coefficients as hi + lo pairs (no coherent rounding of them)
+  const bool dr = A.pd.wd != 0.0;
+  // per-pass coefficients as hi + lo pairs (no coherent rounding of them)
+  const double p1 = apow(amid, 1.0 - A.alpha), pl = apow(anew, 1.0 + A.alpha), pb = apow(anew, A.alpha - 1.0);
+  const double dx3 = A.dx * A.dx * A.dx;
   const Coef<T> cd = ucoef<T>(hw * apow(amid, -(3.0 - A.alpha)));
-  const Coef<T> cu = ucoef<T>(A.e * hw * A.dx / (2.0 * apow(amid, 1.0 - A.alpha)));
-  const Coef<T> cw = ucoef<T>(A.g * hw * A.dx / (4.0 * apow(amid, 1.0 - A.alpha)));
-#pragma unroll
-  for (int k = 0; k < 4; ++k) A.dst[kPH + k][s] = fma_c(cd, A.src[kPI + k][s], A.src[kPH + k][s]);
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-    A.dst[kTH + i][s] = wrap_turns(A.src[kTH + i][s] - T(2) * atan_t(mul_c(cu, A.src[kPA + i][s])));
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    const Q4<T> u{A.src[kUL + 4 * i][s], A.src[kUL + 4 * i + 1][s], A.src[kUL + 4 * i + 2][s],
-                  A.src[kUL + 4 * i + 3][s]};
-    const T w0 = mul_c(cw, A.src[kPB + 3 * i][s]), w1 = mul_c(cw, A.src[kPB + 3 * i + 1][s]),
-            w2 = mul_c(cw, A.src[kPB + 3 * i + 2][s]);
-    const T ww = w0 * w0 + w1 * w1 + w2 * w2;
-    const T d = T(1) / (T(1) + ww);
-    const Q4<T> c{(T(1) - ww) * d, T(-2) * w0 * d, T(-2) * w1 * d, T(-2) * w2 * d};
-    Q4<T> n = qmul(c, u);
-    const T r = rsqrt_s(n.w * n.w + n.x * n.x + n.y * n.y + n.z * n.z);
-    A.dst[kUL + 4 * i][s] = n.w * r;
-    A.dst[kUL + 4 * i + 1][s] = n.x * r;
-    A.dst[kUL + 4 * i + 2][s] = n.y * r;
-    A.dst[kUL + 4 * i + 3][s] = n.z * r;
-  }
-}
+  const Coef<T> cu = ucoef<T>(A.e * hw * A.dx / (2.0 * p1));
+  const Coef<T> cw = ucoef<T>(A.g * hw * A.dx / (4.0 * p1));
+  const Coef<T> cl = ucoef<T>(pl / (A.dx * A.dx));
+  const Coef<T> cp = ucoef<T>(apow(anew, 3.0 + A.alpha));
+  const Coef<T> cjA = ucoef<T>(pl * 2.0 * A.e / A.dx / A.wf2);
+  const Coef<T> cjB = ucoef<T>(pl * A.g / A.dx / A.wf2);
+  const Coef<T> cbA = ucoef<T>(pb / (A.e * dx3));
+  const Coef<T> cbB = ucoef<T>(pb * 2.0 / (A.g * dx3));
+  const Coef<T> ck = ucoef<T>((A.pd.wk1 + A.pd.wk2) * A.h);
+  const Coef<T> cE = ucoef<T>((A.pd.mode == MODE_LF ? A.pd.wk1 + A.pd.wk2 : A.pd.wk1) * A.h);
+  const T lam = (T)A.lam, m2 = (T)A.m2;
+  const Coef<T> lam2c = ucoef<T>(2.0 * A.lam), m2c = ucoef<T>(A.m2);
+  const bool lf = A.pd.mode == MODE_LF;
 
-// Kick of every momentum at a' = a + wd h b from the (drifted) fields, and
-// the lattice sums of the energies:
-//   pi += (wk1 + wk2) h K; E_K from pi_in and pi + wk1 h K (VV) or the mean of
-//   <pi_in^2> and <pi_out^2> (LF), for each of pi_Phi, pi_A, pi_B.
-// Sums: 0,1 pi_Phi (in, e), 2 sum_i |W_i Phi_{+i} - Phi|^2, 3 lambda|Phi|^4,
-// 4 m2|Phi|^2, 5,6 pi_A, 7 sum_{i<j}(1 - cos Phi_ij), 8,9 pi_B,
-// 10 sum_{i<j}(1 - Re/Tr-half U_ij), 11..14 the four components of Phi, 15 |Phi|^2.
-template <typename T>
-__global__ __launch_bounds__(256, 2) void su2_kick_kernel(Su2Args<T> A) {
-  const int N = A.N;
-  const size_t NN = (size_t)N * N, V = NN * N;
-  const size_t s = (size_t)blockIdx.x * 256 + threadIdx.x;
-  double acc[kSu2Acc];
+  // Drift of the raw site into LDS buffer b (Sec. 6.2.1 and 6.2.2):
+  //   Phi += wd h pi / a_mid^{3-alpha};
+  //   V   <- (1 - i u)/(1 + i u) V,  u = e wd h dx pi_A / (2 a_mid^{1-alpha}), as th -= 2 atan u;
+  //   U   <- ((1 - |w|^2) - 2 i w.sigma)/(1 + |w|^2) U,  w = g wd h dx pi_B / (4 a_mid^{1-alpha}),
+  // U renormalised to unit length after the product (rounding only).  A pass
+  // without drift leaves the links as they are.
+  auto drift_site = [&](const Su2Raw<T>& w, int b, int y, int z) {
+    if (!dr) {
+      LP[b][y][z] = Q4<T>{w.ph[0], w.ph[1], w.ph[2], w.ph[3]};
 #pragma unroll
-  for (int k = 0; k < kSu2Acc; ++k) acc[k] = 0.0;
-  if (s < V) {
-    const T* const* F = A.fields_in_dst ? const_cast<const T* const*>(A.dst) : A.src;
-    // periodic neighbour offsets, once per thread: sp[d] = n + e_d, sm[d] = n - e_d,
-    // and dg[a][b] = n - e_b + e_a (a != b)
-    // (sites fit in 32 bits: N^3 <= 2^30)
-    const unsigned su = (unsigned)s, n = (unsigned)N, nn = (unsigned)NN;
-    const unsigned c[3] = {su / nn, (su / n) % n, su % n};
-    const unsigned str[3] = {nn, n, 1u};
-    int op[3], om[3];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      op[d] = c[d] == n - 1 ? -(int)((n - 1) * str[d]) : (int)str[d];
-      om[d] = c[d] == 0 ? (int)((n - 1) * str[d]) : -(int)str[d];
+      for (int i = 0; i < 3; ++i) { Lt[b][i][y][z] = wrap_turns(w.th[i]); LU[b][i][y][z] = w.u[i]; }
+      return;
     }
-    unsigned sp[3], sm[3], dg[3][3];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      sp[d] = su + op[d];
-      sm[d] = su + om[d];
-    }
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-      for (int b = 0; b < 3; ++b) dg[a][b] = su + om[b] + op[a];
-    auto LP = [&](unsigned t, Cx2<T> (&p)[2]) {
-      p[0] = Cx2<T>{F[kPH][t], F[kPH + 1][t]};
-      p[1] = Cx2<T>{F[kPH + 2][t], F[kPH + 3][t]};
-    };
-    auto LQ = [&](int i, unsigned t) -> Q4<T> {
-      return Q4<T>{F[kUL + 4 * i][t], F[kUL + 4 * i + 1][t], F[kUL + 4 * i + 2][t], F[kUL + 4 * i + 3][t]};
-    };
-    auto LT = [&](int i, unsigned t) -> T { return F[kTH + i][t]; };
-
-    const double a_in = A.st->a, b_in = A.st->b;
-    const double anew = A.expand ? a_in + A.pd.wd * A.h * b_in : a_in;
-    const Coef<T> cl = ucoef<T>(apow(anew, 1.0 + A.alpha) / (A.dx * A.dx));
-    const Coef<T> cp = ucoef<T>(apow(anew, 3.0 + A.alpha));
-    const Coef<T> cjA = ucoef<T>(apow(anew, 1.0 + A.alpha) * 2.0 * A.e / A.dx / A.wf2);
-    const Coef<T> cjB = ucoef<T>(apow(anew, 1.0 + A.alpha) * A.g / A.dx / A.wf2);
-    const Coef<T> cbA = ucoef<T>(apow(anew, A.alpha - 1.0) / (A.e * A.dx * A.dx * A.dx));
-    const Coef<T> cbB = ucoef<T>(apow(anew, A.alpha - 1.0) * 2.0 / (A.g * A.dx * A.dx * A.dx));
-    const Coef<T> ck = ucoef<T>((A.pd.wk1 + A.pd.wk2) * A.h);
-    const Coef<T> cE = ucoef<T>((A.pd.mode == MODE_LF ? A.pd.wk1 + A.pd.wk2 : A.pd.wk1) * A.h);
-    const T lam = (T)A.lam, m2 = (T)A.m2;
-    const Coef<T> lam2c = ucoef<T>(2.0 * A.lam), m2c = ucoef<T>(A.m2);
-
-    Cx2<T> p[2];
-    LP(su, p);
-    // ---- matter: covariant differences in the cancellation-free form
-    //   W Phi_+ - Phi = (V - 1) y + (U - 1) Phi_+ + (Phi_+ - Phi),  y = U Phi_+
-    //   W(n-i)^dag Phi_- - Phi = (U^dag - 1) y' + (conj V - 1) Phi_- + (Phi_- - Phi),  y' = conj(V) Phi_-
-    Cx2<T> lap[2] = {{T(0), T(0)}, {T(0), T(0)}};
-    T eg = T(0), curA[3], curB[3][3];
+    LP[b][y][z] = Q4<T>{fma_c(cd, w.pi[0], w.ph[0]), fma_c(cd, w.pi[1], w.ph[1]), fma_c(cd, w.pi[2], w.ph[2]),
+                        fma_c(cd, w.pi[3], w.ph[3])};
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
-      Cx2<T> fp[2], fm[2];
-      LP(sp[i], fp);
-      LP(sm[i], fm);
-      // forward
-      const Q4<T> u = LQ(i, su);
-      Cx2<T> um1f[2];
-      qapply(u, qw_m1(u), fp, um1f);  // (U - 1) Phi_+
-      T sn, cm;
-      sincos_m1(LT(i, su), &sn, &cm);
-      const Cx2<T> vm1{cm, sn};
-      Cx2<T> g[2];
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const Cx2<T> y = cadd2(fp[k], um1f[k]);
-        g[k] = cadd2(cadd2(cmul2(vm1, y), um1f[k]), csub2(fp[k], p[k]));
-      }
-      // backward
-      const Q4<T> ub = qdag(LQ(i, sm[i]));
-      T snb, cmb;
-      sincos_m1(LT(i, sm[i]), &snb, &cmb);
-      const Cx2<T> vbm1{cmb, -snb};  // conj(V) - 1
-      Cx2<T> vf[2], yb[2], ubm1[2];
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        vf[k] = cmul2(vbm1, fm[k]);
-        yb[k] = cadd2(fm[k], vf[k]);
-      }
-      qapply(ub, qw_m1(ub), yb, ubm1);
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const Cx2<T> gb = cadd2(cadd2(ubm1[k], vf[k]), csub2(fm[k], p[k]));
-        lap[k] = cadd2(lap[k], cadd2(g[k], gb));
-      }
-      eg += g[0].re * g[0].re + g[0].im * g[0].im + g[1].re * g[1].re + g[1].im * g[1].im;
-      // currents Im[Phi^dag g], Im[Phi^dag sigma_a g] (Im[Phi^dag sigma Phi] = 0)
-      curA[i] = cross_im(p[0], g[0]) + cross_im(p[1], g[1]);
-      curB[i][0] = cross_im(p[0], g[1]) + cross_im(p[1], g[0]);
-      curB[i][1] = -dot_re(p[0], g[1]) + dot_re(p[1], g[0]);
-      curB[i][2] = cross_im(p[0], g[0]) - cross_im(p[1], g[1]);
+      Lt[b][i][y][z] = wrap_turns(w.th[i] - T(2) * atan_t(mul_c(cu, w.pa[i])));
+      const T w0 = mul_c(cw, w.pb[3 * i]), w1 = mul_c(cw, w.pb[3 * i + 1]), w2 = mul_c(cw, w.pb[3 * i + 2]);
+      const T ww = w0 * w0 + w1 * w1 + w2 * w2;
+      // (1 + |w|^2) C U; the factor goes with the normalisation
+      const Q4<T> n = qmul(Q4<T>{T(1) - ww, T(-2) * w0, T(-2) * w1, T(-2) * w2}, w.u[i]);
+      const T r = rsqrt_s(n.w * n.w + n.x * n.x + n.y * n.y + n.z * n.z);
+      LU[b][i][y][z] = Q4<T>{n.w * r, n.x * r, n.y * r, n.z * r};
     }
-    const T r2 = p[0].re * p[0].re + p[0].im * p[0].im + p[1].re * p[1].re + p[1].im * p[1].im;
-
-    // ---- U(1) plaquettes: sin Phi_ab(m), Phi_ab(m) = th_a(m) + th_b(m+a) - th_a(m+b) - th_b(m),
-    // at m = n and at m = n - e_q (m + e_a = n when a = q)
-    auto pos = [&](int q, int a) -> unsigned { return a == q ? su : dg[a][q]; };
-    auto plA = [&](int a, int b, int q, T* om1) -> T {
-      const unsigned m = q < 0 ? su : sm[q];
-      const unsigned ma = q < 0 ? sp[a] : pos(q, a), mb = q < 0 ? sp[b] : pos(q, b);
-      const T ph = (LT(a, m) + LT(b, ma)) - (LT(a, mb) + LT(b, m));
-      T sn, cm;
-      sincos_m1(ph, &sn, &cm);
-      if (om1) *om1 = -cm;  // 1 - cos Phi
-      return sn;
-    };
-    T omA[3];
-    const T S01 = plA(0, 1, -1, &omA[0]), S02 = plA(0, 2, -1, &omA[1]), S12 = plA(1, 2, -1, &omA[2]);
-    const T curlA[3] = {(S01 - plA(0, 1, 1, nullptr)) + (S02 - plA(0, 2, 2, nullptr)),
-                        (-S01 + plA(0, 1, 0, nullptr)) + (S12 - plA(1, 2, 2, nullptr)),
-                        (-S02 + plA(0, 2, 0, nullptr)) + (-S12 + plA(1, 2, 1, nullptr))};
-
-    // ---- SU(2) plaquettes U_ab(n) = U_a(n) U_b(n+a) U_a(n+b)^dag U_b(n)^dag and the
-    // backward ones transported to n (products of three links)
-    auto plB = [&](int a, int b) -> Q4<T> {
-      return qmul(qmul(LQ(a, su), LQ(b, sp[a])), qdag(qmul(LQ(b, su), LQ(a, sp[b]))));
-    };
-    const Q4<T> P01 = plB(0, 1), P02 = plB(0, 2), P12 = plB(1, 2);
-    T omB = T(0);
-    {
-      const Q4<T>* P[3] = {&P01, &P02, &P12};
-#pragma unroll
-      for (int k = 0; k < 3; ++k) omB += -qw_m1(*P[k]);  // 1 - w = (2 - Tr)/2
-    }
-    // i = a, plane (a, b), base m = n - b: U_b(m)^dag U_a(m) U_b(m+a) U_a(n)^dag
-    auto tA = [&](int a, int b) -> Q4<T> {
-      return qmul(qmul(qdag(LQ(b, sm[b])), LQ(a, sm[b])), qmul(LQ(b, dg[a][b]), qdag(LQ(a, su))));
-    };
-    // i = b, plane (a, b), base m = n - a: U_b(n) U_a(m+b)^dag U_b(m)^dag U_a(m)
-    auto tB = [&](int a, int b) -> Q4<T> {
-      return qmul(qmul(LQ(b, su), qdag(LQ(a, dg[b][a]))), qmul(qdag(LQ(b, sm[a])), LQ(a, sm[a])));
-    };
-    T magB[3][3];
-    {
-      const Q4<T> t01 = tA(0, 1), t02 = tA(0, 2), t12 = tA(1, 2);
-      const Q4<T> r01 = tB(0, 1), r02 = tB(0, 2), r12 = tB(1, 2);
-      // i = 0: [c(P01) - c(t01)] + [c(P02) - c(t02)]
-      magB[0][0] = (P01.x - t01.x) + (P02.x - t02.x);
-      magB[0][1] = (P01.y - t01.y) + (P02.y - t02.y);
-      magB[0][2] = (P01.z - t01.z) + (P02.z - t02.z);
-      // i = 1: [-c(P01) + c(r01)] + [c(P12) - c(t12)]
-      magB[1][0] = (r01.x - P01.x) + (P12.x - t12.x);
-      magB[1][1] = (r01.y - P01.y) + (P12.y - t12.y);
-      magB[1][2] = (r01.z - P01.z) + (P12.z - t12.z);
-      // i = 2: [-c(P02) + c(r02)] + [-c(P12) + c(r12)]
-      magB[2][0] = (r02.x - P02.x) + (r12.x - P12.x);
-      magB[2][1] = (r02.y - P02.y) + (r12.y - P12.y);
-      magB[2][2] = (r02.z - P02.z) + (r12.z - P12.z);
-    }
-
-    // ---- kicks and sums
-    const bool wr = A.pd.write != 0;
-    T ts[kSu2Acc];
-#pragma unroll
-    for (int k = 0; k < kSu2Acc; ++k) ts[k] = T(0);
+  };
+  auto drift_into = [&](int b) {
+    drift_site(raw, b, ly, lz);
+    if (has_ring) drift_site(rraw, b, rly, rlz);
+  };
+  auto phi_at = [&](int b, int y, int z, Cx2<T> (&p)[2]) {
+    const Q4<T> v = LP[b][y][z];
+    p[0] = Cx2<T>{v.w, v.x};
+    p[1] = Cx2<T>{v.y, v.z};
+  };
+  // (W^dag - 1) Phi = (U^dag - 1) y' + (conj V - 1) Phi, y' = conj(V) Phi, from (sin, cos - 1) of V's phase
+  auto back = [&](const Q4<T>& u, T sn, T cm, const Cx2<T> (&p)[2]) -> Q4<T> {
+    Cx2<T> vf[2], y[2], o[2];
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-      // V'(Phi) = (2 lambda |Phi|^2 + m2) Phi
-      const T dre = fma_c(lam2c, r2 * p[k].re, mul_c(m2c, p[k].re));
-      const T dim = fma_c(lam2c, r2 * p[k].im, mul_c(m2c, p[k].im));
-      const Cx2<T> K{mul_c(cl, lap[k].re) - mul_c(cp, dre), mul_c(cl, lap[k].im) - mul_c(cp, dim)};
-      const Cx2<T> pin{A.src[kPI + 2 * k][s], A.src[kPI + 2 * k + 1][s]};
-      const Cx2<T> pe{fma_c(cE, K.re, pin.re), fma_c(cE, K.im, pin.im)};
-      ts[0] += pin.re * pin.re + pin.im * pin.im;
-      ts[1] += pe.re * pe.re + pe.im * pe.im;
-      if (wr) {
-        A.dst[kPI + 2 * k][s] = fma_c(ck, K.re, pin.re);
-        A.dst[kPI + 2 * k + 1][s] = fma_c(ck, K.im, pin.im);
+      vf[k] = cmul2(Cx2<T>{cm, -sn}, p[k]);
+      y[k] = cadd2(p[k], vf[k]);
+    }
+    const Q4<T> ud = qdag(u);
+    qapply(ud, qw_m1(ud), y, o);
+    const Cx2<T> a = cadd2(o[0], vf[0]), b = cadd2(o[1], vf[1]);
+    return Q4<T>{a.re, a.im, b.re, b.im};
+  };
+  // plaquettes of place (y, z) of plane buffer c (plane x+1 in buffer n)
+  auto plB = [&](const Q4<T>& ua, const Q4<T>& ubf, const Q4<T>& ub, const Q4<T>& uaf) -> Q4<T> {
+    return qmul(qmul(ua, ubf), qdag(qmul(ub, uaf)));
+  };
+  auto plA = [&](T ta, T tbf, T taf, T tb, T& om) -> T {
+    T sn, cm;
+    sincos_m1_near((ta + tbf) - (taf + tb), &sn, &cm);
+    om = -cm;  // 1 - cos Phi
+    return sn;
+  };
+
+  double acc[NACC];
+#pragma unroll
+  for (int k = 0; k < NACC; ++k) acc[k] = 0.0;
+  // handed on from plane x-1 of the own column
+  Q4<T> hx{T(0), T(0), T(0), T(0)}, pxm = hx;
+  V3<T> rx01{T(0), T(0), T(0)}, rx02 = rx01;
+  T sx01 = T(0), sx02 = T(0);
+  T qc[16], qn[16];
+  auto momenta = [&](T (&q)[16]) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) q[k] = raw.pi[k];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) q[4 + k] = raw.pa[k];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) q[7 + k] = raw.pb[k];
+  };
+
+  // prologue: plane x0-1 -> buffer 1, plane x0 -> buffer 0, what x0-1 hands on, plane x0+1 -> buffer 1
+  load_ring((x0 - 1 + N) % N);
+  drift_into(1);
+  load_own(x0);
+  load_ring(x0);
+  drift_into(0);
+  momenta(qc);
+  __syncthreads();
+  load_own((x0 + 1) % N);
+  {
+    T om;
+    const Q4<T> u0 = LU[1][0][ly][lz];
+    rx01 = qrotate(u0, plB(u0, LU[0][1][ly][lz], LU[1][1][ly][lz], LU[1][0][ly + 1][lz]));
+    rx02 = qrotate(u0, plB(u0, LU[0][2][ly][lz], LU[1][2][ly][lz], LU[1][0][ly][lz + 1]));
+    sx01 = plA(Lt[1][0][ly][lz], Lt[0][1][ly][lz], Lt[1][0][ly + 1][lz], Lt[1][1][ly][lz], om);
+    sx02 = plA(Lt[1][0][ly][lz], Lt[0][2][ly][lz], Lt[1][0][ly][lz + 1], Lt[1][2][ly][lz], om);
+    T sn, cm;
+    sincos_m1_near(Lt[1][0][ly][lz], &sn, &cm);
+    Cx2<T> p[2];
+    phi_at(1, ly, lz, p);
+    hx = back(u0, sn, cm, p);
+    pxm = LP[1][ly][lz];
+  }
+  load_ring((x0 + 1) % N);
+  __syncthreads();
+  drift_into(1);
+  momenta(qn);
+  __syncthreads();
+
+  for (int i = 0; i < A.XC; ++i) {
+    const int x = x0 + i, c = i & 1, n = c ^ 1;
+    // ---- what every site of plane x computes once
+    Cx2<T> lap[2];
+    T eg = T(0), curA[3], curB[3][3], magA[3], magB[3][3], omA = T(0), omB = T(0);
+    {
+      Cx2<T> p[2];
+      phi_at(c, ly, lz, p);
+      const Q4<T> u0 = LU[c][0][ly][lz], u1 = LU[c][1][ly][lz], u2 = LU[c][2][ly][lz];
+      const T t0 = Lt[c][0][ly][lz], t1 = Lt[c][1][ly][lz], t2 = Lt[c][2][ly][lz];
+      // backward neighbour along x: W^dag Phi_- - Phi
+      lap[0] = Cx2<T>{hx.w + (pxm.w - p[0].re), hx.x + (pxm.x - p[0].im)};
+      lap[1] = Cx2<T>{hx.y + (pxm.y - p[1].re), hx.z + (pxm.z - p[1].im)};
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        const Q4<T>& u = d == 0 ? u0 : d == 1 ? u1 : u2;
+        T sn, cm;
+        sincos_m1_near(d == 0 ? t0 : d == 1 ? t1 : t2, &sn, &cm);
+        Cx2<T> fp[2], um1f[2], g[2];
+        phi_at(d == 0 ? n : c, ly + (d == 1), lz + (d == 2), fp);
+        // W Phi_+ - Phi = (V - 1) y + (U - 1) Phi_+ + (Phi_+ - Phi),  y = U Phi_+
+        qapply(u, qw_m1(u), fp, um1f);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const Cx2<T> y = cadd2(fp[k], um1f[k]);
+          g[k] = cadd2(cadd2(cmul2(Cx2<T>{cm, sn}, y), um1f[k]), csub2(fp[k], p[k]));
+          lap[k] = cadd2(lap[k], g[k]);
+        }
+        eg += g[0].re * g[0].re + g[0].im * g[0].im + g[1].re * g[1].re + g[1].im * g[1].im;
+        // currents Im[Phi^dag g], Im[Phi^dag sigma_a g] (Im[Phi^dag sigma Phi] = 0)
+        curA[d] = cross_im(p[0], g[0]) + cross_im(p[1], g[1]);
+        curB[d][0] = cross_im(p[0], g[1]) + cross_im(p[1], g[0]);
+        curB[d][1] = -dot_re(p[0], g[1]) + dot_re(p[1], g[0]);
+        curB[d][2] = cross_im(p[0], g[0]) - cross_im(p[1], g[1]);
+        const Q4<T> hb = back(u, sn, cm, p);
+        if (d == 0) hx = hb;
+        if (d == 1 && ty + 1 < TY) Bh[0][ty + 1][tz] = hb;
+        if (d == 2 && tz + 1 < TZ) Bh[1][ty][tz + 1] = hb;
+      }
+      pxm = LP[c][ly][lz];
+      auto to_y = [&](int k, T v) { if (ty + 1 < TY) Bv[0][k][ty + 1][tz] = v; };
+      auto to_z = [&](int k, T v) { if (tz + 1 < TZ) Bv[1][k][ty][tz + 1] = v; };
+      {
+        T o01, o02, o12;
+        const T S01 = plA(t0, Lt[n][1][ly][lz], Lt[c][0][ly + 1][lz], t1, o01);
+        const T S02 = plA(t0, Lt[n][2][ly][lz], Lt[c][0][ly][lz + 1], t2, o02);
+        const T S12 = plA(t1, Lt[c][2][ly + 1][lz], Lt[c][1][ly][lz + 1], t2, o12);
+        omA = o01 + o02 + o12;
+        magA[0] = S01 + S02;
+        magA[1] = (sx01 - S01) + S12;
+        magA[2] = (sx02 - S02) - S12;
+        sx01 = S01;
+        sx02 = S02;
+        to_y(6, S01);
+        to_y(7, S12);
+        to_z(6, S02);
+        to_z(7, S12);
+      }
+      {
+        const Q4<T> P = plB(u0, LU[n][1][ly][lz], u1, LU[c][0][ly + 1][lz]);
+        omB += -qw_m1(P);  // 1 - w = (2 - Tr)/2
+        magB[0][0] = P.x; magB[0][1] = P.y; magB[0][2] = P.z;
+        magB[1][0] = rx01.x - P.x; magB[1][1] = rx01.y - P.y; magB[1][2] = rx01.z - P.z;
+        rx01 = qrotate(u0, P);
+        const V3<T> t = qrotate(u1, P);
+        to_y(0, t.x); to_y(1, t.y); to_y(2, t.z);
+      }
+      {
+        const Q4<T> P = plB(u0, LU[n][2][ly][lz], u2, LU[c][0][ly][lz + 1]);
+        omB += -qw_m1(P);
+        magB[0][0] += P.x; magB[0][1] += P.y; magB[0][2] += P.z;
+        magB[2][0] = rx02.x - P.x; magB[2][1] = rx02.y - P.y; magB[2][2] = rx02.z - P.z;
+        rx02 = qrotate(u0, P);
+        const V3<T> t = qrotate(u2, P);
+        to_z(0, t.x); to_z(1, t.y); to_z(2, t.z);
+      }
+      {
+        const Q4<T> P = plB(u1, LU[c][2][ly + 1][lz], u2, LU[c][1][ly][lz + 1]);
+        omB += -qw_m1(P);
+        magB[1][0] += P.x; magB[1][1] += P.y; magB[1][2] += P.z;
+        magB[2][0] -= P.x; magB[2][1] -= P.y; magB[2][2] -= P.z;
+        const V3<T> t = qrotate(u2, P), r = qrotate(u1, P);
+        to_z(3, t.x); to_z(4, t.y); to_z(5, t.z);
+        to_y(3, r.x); to_y(4, r.y); to_y(5, r.z);
       }
     }
+    if (low_row) {
+      // row y0-1, place (0, 1 + rid)
+      const int rid = tid - ROW0, z = 1 + rid;
+      const Q4<T> u0 = LU[c][0][0][z], u1 = LU[c][1][0][z], u2 = LU[c][2][0][z];
+      const Q4<T> P01 = plB(u0, LU[n][1][0][z], u1, LU[c][0][1][z]);
+      const Q4<T> P12 = plB(u1, LU[c][2][1][z], u2, LU[c][1][0][z + 1]);
+      const V3<T> t = qrotate(u1, P01), r = qrotate(u1, P12);
+      Bv[0][0][0][rid] = t.x; Bv[0][1][0][rid] = t.y; Bv[0][2][0][rid] = t.z;
+      Bv[0][3][0][rid] = r.x; Bv[0][4][0][rid] = r.y; Bv[0][5][0][rid] = r.z;
+      T om;
+      Bv[0][6][0][rid] = plA(Lt[c][0][0][z], Lt[n][1][0][z], Lt[c][0][1][z], Lt[c][1][0][z], om);
+      Bv[0][7][0][rid] = plA(Lt[c][1][0][z], Lt[c][2][1][z], Lt[c][1][0][z + 1], Lt[c][2][0][z], om);
+      T sn, cm;
+      sincos_m1_near(Lt[c][1][0][z], &sn, &cm);
+      Cx2<T> p[2];
+      phi_at(c, 0, z, p);
+      Bh[0][0][rid] = back(u1, sn, cm, p);
+    }
+    if (low_col) {
+      // column z0-1, place (1 + q, 0)
+      const int q = tid - COL0, y = 1 + q;
+      const Q4<T> u0 = LU[c][0][y][0], u1 = LU[c][1][y][0], u2 = LU[c][2][y][0];
+      const Q4<T> P02 = plB(u0, LU[n][2][y][0], u2, LU[c][0][y][1]);
+      const Q4<T> P12 = plB(u1, LU[c][2][y + 1][0], u2, LU[c][1][y][1]);
+      const V3<T> t = qrotate(u2, P02), r = qrotate(u2, P12);
+      Bv[1][0][q][0] = t.x; Bv[1][1][q][0] = t.y; Bv[1][2][q][0] = t.z;
+      Bv[1][3][q][0] = r.x; Bv[1][4][q][0] = r.y; Bv[1][5][q][0] = r.z;
+      T om;
+      Bv[1][6][q][0] = plA(Lt[c][0][y][0], Lt[n][2][y][0], Lt[c][0][y][1], Lt[c][2][y][0], om);
+      Bv[1][7][q][0] = plA(Lt[c][1][y][0], Lt[c][2][y + 1][0], Lt[c][1][y][1], Lt[c][2][y][0], om);
+      T sn, cm;
+      sincos_m1_near(Lt[c][2][y][0], &sn, &cm);
+      Cx2<T> p[2];
+      phi_at(c, y, 0, p);
+      Bh[1][q][0] = back(u2, sn, cm, p);
+    }
+    // what the kick takes over is complete here: without these the compiler
+    // sinks its computation past the barrier and keeps the inputs instead
+    auto pin = [](T& v) { asm volatile("" : "+v"(v)); };
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      const T K = fma_c(cbA, curlA[i], mul_c(cjA, curA[i]));
-      const T ain = A.src[kPA + i][s], ae = fma_c(cE, K, ain);
-      ts[5] += ain * ain;
-      ts[6] += ae * ae;
-      if (wr) A.dst[kPA + i][s] = fma_c(ck, K, ain);
+    for (int k = 0; k < 2; ++k) { pin(lap[k].re); pin(lap[k].im); }
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      pin(curA[d]);
+      pin(magA[d]);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) { pin(curB[d][a]); pin(magB[d][a]); }
+    }
+    pin(eg);
+    pin(omA);
+    pin(omB);
+    __syncthreads();
+    // plane x+2 is in flight during the kick (its ring after the kick's
+    // registers are free); the last iteration re-reads plane x+1 (unused) so
+    // that the loads are unconditional
+    const int xn = i + 1 < A.XC ? (x + 2) % N : (x + 1) % N;
+    load_ring(xn);
+    load_own(xn);
+    __builtin_amdgcn_sched_barrier(0);
+    // ---- kick of the own sites of plane x
+    {
+      const unsigned o = (unsigned)x * plane + col;
+      const Q4<T> pq = LP[c][ly][lz], py = LP[c][ly - 1][lz], pz = LP[c][ly][lz - 1];
+      const Q4<T> hy = Bh[0][ty][tz], hz = Bh[1][ty][tz];
+      const T ph[4] = {pq.w, pq.x, pq.y, pq.z};
+      const T lp[4] = {lap[0].re + ((hy.w + (py.w - pq.w)) + (hz.w + (pz.w - pq.w))),
+                       lap[0].im + ((hy.x + (py.x - pq.x)) + (hz.x + (pz.x - pq.x))),
+                       lap[1].re + ((hy.y + (py.y - pq.y)) + (hz.y + (pz.y - pq.y))),
+                       lap[1].im + ((hy.z + (py.z - pq.z)) + (hz.z + (pz.z - pq.z)))};
+      const T r2 = ph[0] * ph[0] + ph[1] * ph[1] + ph[2] * ph[2] + ph[3] * ph[3];
+      T kin = T(0), kin0 = T(0), ka = T(0), ka0 = T(0), kb = T(0), kb0 = T(0);
+      Walk w(A.dst, V);
+      auto put = [&](T v) {
+        if constexpr (!OBS) __builtin_nontemporal_store(v, w.next(o));
+      };
+#pragma unroll
+      for (int k = 0; k < 4; ++k) put(ph[k]);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        // V'(Phi) = (2 lambda |Phi|^2 + m2) Phi
+        const T K = mul_c(cl, lp[k]) - mul_c(cp, fma_c(lam2c, r2 * ph[k], mul_c(m2c, ph[k])));
+        const T pe = fma_c(cE, K, qc[k]);
+        kin0 += qc[k] * qc[k];
+        kin += pe * pe;
+        put(fma_c(ck, K, qc[k]));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int d = 0; d < 3; ++d) put(Lt[c][d][ly][lz]);
+      // magnetic forces: the neighbours' shares
+      magA[0] -= Bv[0][6][ty][tz] + Bv[1][6][ty][tz];
+      magA[1] -= Bv[1][7][ty][tz];
+      magA[2] += Bv[0][7][ty][tz];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        const T K = fma_c(cbA, magA[d], mul_c(cjA, curA[d]));
+        const T ain = qc[4 + d], ae = fma_c(cE, K, ain);
+        ka0 += ain * ain;
+        ka += ae * ae;
+        put(fma_c(ck, K, ain));
+      }
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        const Q4<T> u = LU[c][d][ly][lz];
+        put(u.w);
+        put(u.x);
+        put(u.y);
+        put(u.z);
+        __builtin_amdgcn_sched_barrier(0);
+      }
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
-        const T KB = fma_c(cbB, magB[i][a], mul_c(cjB, curB[i][a]));
-        const T bin = A.src[kPB + 3 * i + a][s], be = fma_c(cE, KB, bin);
-        ts[8] += bin * bin;
-        ts[9] += be * be;
-        if (wr) A.dst[kPB + 3 * i + a][s] = fma_c(ck, KB, bin);
+        magB[0][a] -= Bv[0][a][ty][tz] + Bv[1][a][ty][tz];
+        magB[1][a] -= Bv[1][3 + a][ty][tz];
+        magB[2][a] += Bv[0][3 + a][ty][tz];
+      }
+#pragma unroll
+      for (int d = 0; d < 3; ++d)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          const T KB = fma_c(cbB, magB[d][a], mul_c(cjB, curB[d][a]));
+          const T bin = qc[7 + 3 * d + a], be = fma_c(cE, KB, bin);
+          kb0 += bin * bin;
+          kb += be * be;
+          put(fma_c(ck, KB, bin));
+        }
+      if constexpr (OBS) {
+        const T ts[kSu2Acc] = {kin0, kin, eg, lam * r2 * r2, m2 * r2, ka0, ka, omA, kb0, kb, omB,
+                               ph[0], ph[1], ph[2], ph[3], r2};
+#pragma unroll
+        for (int k = 0; k < kSu2Acc; ++k) acc[k] += (double)ts[k];
+      } else {
+        if (lf) { kin += kin0; ka += ka0; kb += kb0; }
+        const T ts[kSu2StepAcc] = {kin, eg, lam * r2 * r2 + m2 * r2, ka, omA, kb, omB};
+#pragma unroll
+        for (int k = 0; k < kSu2StepAcc; ++k) acc[k] += (double)ts[k];
       }
     }
-    if (wr && !A.fields_in_dst) {
-      // a kick-only pass: the fields move to the other buffer unchanged
 #pragma unroll
-      for (int k = 0; k < 4; ++k) A.dst[kPH + k][s] = A.src[kPH + k][s];
-#pragma unroll
-      for (int i = 0; i < 3; ++i) A.dst[kTH + i][s] = A.src[kTH + i][s];
-#pragma unroll
-      for (int k = 0; k < 12; ++k) A.dst[kUL + k][s] = A.src[kUL + k][s];
+    for (int k = 0; k < 16; ++k) qc[k] = qn[k];
+    __syncthreads();
+    if (i + 1 < A.XC) {
+      drift_into(c);  // plane x+2 replaces plane x
+      momenta(qn);
+      __syncthreads();
     }
-    ts[2] = eg;
-    ts[3] = lam * r2 * r2;
-    ts[4] = m2 * r2;
-    ts[7] = omA[0] + omA[1] + omA[2];
-    ts[10] = omB;
-    ts[11] = p[0].re;
-    ts[12] = p[0].im;
-    ts[13] = p[1].re;
-    ts[14] = p[1].im;
-    ts[15] = r2;
-#pragma unroll
-    for (int k = 0; k < kSu2Acc; ++k) acc[k] = (double)ts[k];
   }
-  su2_block_partials<kSu2Acc>(acc, A.partials);
-}
-
-// Energies (Sec. 5.4.1, Sec. 6.3.1) at a' and the scale-factor kernel with
-// both gauge sectors, K_a = (1/3)(f/m_p)^2 a'^{1+2 alpha}[(alpha-2)E_K + alpha E_G
-// + (alpha+1)E_V + (alpha-1)(E_K^A + E_G^A + E_K^B + E_G^B)]; b_out = b + (wk1 + wk2) h K_a.
-// First stage of a pass's reduction: block g of R sums the contiguous range
-// g of the nb records (lanes in order, then the waves in order) into record g
-// of `out`, so that the one-block finish reads R records, not nb.  With one
-// block reading the 8192 records of a 128^3 pass the finish took 36 us.
-constexpr int kSu2FoldBlocks = 64;
-
-template <int NACC>
-__global__ __launch_bounds__(256) void su2_fold_records(const double* in, int nb, double* out) {
-  __shared__ double red[4][NACC];
-  const int R = gridDim.x, g = blockIdx.x;
-  const int chunk = (nb + R - 1) / R;
-  const int b0 = g * chunk, b1 = b0 + chunk < nb ? b0 + chunk : nb;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  double t[NACC];
-#pragma unroll
-  for (int k = 0; k < NACC; ++k) t[k] = 0.0;
-  for (int b = b0 + tid; b < b1; b += 256)
-#pragma unroll
-    for (int k = 0; k < NACC; ++k) t[k] += in[(size_t)b * NACC + k];
+  // the tile's sums: waves in order
 #pragma unroll
   for (int k = 0; k < NACC; ++k) {
-    const double v = wsum64(t[k]);
-    if (lane == 0) red[wv][k] = v;
+    const double s = wsum64(acc[k]);
+    if ((tid & 63) == 0) red[tid >> 6][k] = s;
   }
   __syncthreads();
-  if (tid < NACC) out[(size_t)g * NACC + tid] = ((red[0][tid] + red[1][tid]) + red[2][tid]) + red[3][tid];
+  if (tid < NACC) {
+    double s = red[0][tid];
+#pragma unroll
+    for (int w = 1; w < NT / 64; ++w) s += red[w][tid];
+    A.partials[(size_t)blockIdx.x * NACC + tid] = s;
+  }
 }
 
-// One block of kSu2FinishThreads threads: four waves leave each thread the
-// registers for its FP64 sums (1024 threads, held to 128 VGPRs, spilled them).
-constexpr int kSu2FinishThreads = 256;
-
-template <typename T>
-__global__ __launch_bounds__(kSu2FinishThreads) void su2_finish_kernel(Su2Args<T> A, int nblocks) {
-  constexpr int NW = kSu2FinishThreads / 64;
-  __shared__ double red[NW][kSu2Acc];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  double tot[kSu2Acc];
-#pragma unroll
-  for (int k = 0; k < kSu2Acc; ++k) tot[k] = 0.0;
-  for (int b = tid; b < nblocks; b += kSu2FinishThreads)
-#pragma unroll
-    for (int k = 0; k < kSu2Acc; ++k) tot[k] += A.partials[(size_t)b * kSu2Acc + k];
-#pragma unroll
-  for (int k = 0; k < kSu2Acc; ++k) {
-    const double v = wsum64(tot[k]);
-    if (lane == 0) red[wv][k] = v;
+// Sums of nb records in a fixed order by one block of NT threads: thread t
+// takes doubles t, t + NL, ... (NL a multiple of the record length, so the
+// loads are coalesced and a thread's values belong to one accumulator), then
+// the threads of each accumulator in order.  The first thread returns the
+// sums in S.
+template <int NACC, int NT>
+__device__ bool su2_reduce_records(const double* rec, int nb, double (&S)[NACC]) {
+  constexpr int NL = (NT / NACC) * NACC;
+  static_assert(NT >= 64 && NACC <= 64, "the first wave finishes the sums");
+  __shared__ double part[NL];
+  const int tid = threadIdx.x;
+  const int64_t nv = (int64_t)nb * NACC;
+  if (tid < NL) {
+    double s = 0.0;
+#pragma unroll 8
+    for (int64_t e = tid; e < nv; e += NL) s += rec[e];
+    part[tid] = s;
   }
   __syncthreads();
-  if (tid != 0) return;
-  double S[kSu2Acc];
-  for (int k = 0; k < kSu2Acc; ++k) {
-    double v = 0.0;
-    for (int w = 0; w < NW; ++w) v += red[w][k];
-    S[k] = v;
-  }
-  const PassDesc& pd = A.pd;
-  DevState* st = A.st;
+  if (tid >= 64) return false;
+  double v = 0.0;
+  if (tid < NACC)
+    for (int j = tid; j < NL; j += NACC) v += part[j];
+#pragma unroll
+  for (int k = 0; k < NACC; ++k) S[k] = __shfl(v, k, 64);
+  return tid == 0;
+}
+
+// Energies (Sec. 5.4.1, Sec. 6.3.1) at a' from the lattice sums S of pass `pd`,
+// which started from state `in`, and the scale-factor kernel with both gauge
+// sectors, K_a = (1/3)(f/m_p)^2 a'^{1+2 alpha}[(alpha-2)E_K + alpha E_G + (alpha+1)E_V
+// + (alpha-1)(E_K^A + E_G^A + E_K^B + E_G^B)]; b_out = b + (wk1 + wk2) h K_a.
+// The state goes to `out` (may be `in`; nullptr: not stored); a and b after
+// the pass are returned in a_next, b_next.
+template <typename T, bool OBS>
+__device__ void su2_finish_state(const Su2PassArgs<T>& A, const PassDesc& pd, const DevState* in, const double* S,
+                                 DevState* out, double& a_next, double& b_next) {
   const double V = (double)A.N * A.N * A.N;
-  const double a_in = st->a, b_in = st->b, al = A.alpha;
+  const double a_in = in->a, b_in = in->b, al = A.alpha;
   const double a = A.expand ? a_in + pd.wd * A.h * b_in : a_in;
   const bool lf = pd.mode == MODE_LF;
   const double a2 = a * a, a4 = a2 * a2, a6 = a4 * a2, dx2 = A.dx * A.dx, dx4 = dx2 * dx2;
-  lattice_obs o = st->obs;
-  o.EK = (lf ? 0.5 * (S[0] + S[1]) : S[1]) / V / a6;
-  o.EG = S[2] / V / (a2 * dx2);
-  o.EV_term[0] = S[4] / V;
-  o.EV_term[1] = S[3] / V;
-  o.EV_term[2] = 0.0;
-  o.EV = o.EV_term[0] + o.EV_term[1];
-  o.EK_A = A.wf2 * (lf ? 0.5 * (S[5] + S[6]) : S[6]) / V / (2.0 * a4);
-  o.EG_A = A.wf2 * S[7] / V / (a4 * dx4 * A.e * A.e);
-  o.EK_B = A.wf2 * (lf ? 0.5 * (S[8] + S[9]) : S[9]) / V / (2.0 * a4);
-  o.EG_B = 2.0 * A.wf2 * (2.0 * S[10]) / V / (a4 * dx4 * A.g * A.g);
+  // kinetic, gradient, potential, then electric and magnetic sums of U(1) and SU(2)
+  double kin, grad, kA, mA, kB, mB;
+  lattice_obs o = in->obs;
+  bool bad = false;
+  if constexpr (OBS) {
+    kin = lf ? 0.5 * (S[0] + S[1]) : S[1];
+    grad = S[2];
+    o.EV_term[0] = S[4] / V;
+    o.EV_term[1] = S[3] / V;
+    o.EV_term[2] = 0.0;
+    o.EV = o.EV_term[0] + o.EV_term[1];
+    kA = lf ? 0.5 * (S[5] + S[6]) : S[6];
+    mA = S[7];
+    kB = lf ? 0.5 * (S[8] + S[9]) : S[9];
+    mB = S[10];
+    o.mean_f[0] = S[11] / V;
+    o.mean_f[1] = S[12] / V;
+    o.mean_lo[0] = S[13] / V;
+    o.mean_lo[1] = S[14] / V;
+    o.meansq_f[0] = S[15] / V;
+    o.meansq_f[1] = 0.0;
+  } else {
+    const double f = lf ? 0.5 : 1.0;
+    kin = f * S[0];
+    grad = S[1];
+    o.EV = S[2] / V;
+    kA = f * S[3];
+    mA = S[4];
+    kB = f * S[5];
+    mB = S[6];
+    o.EV_term[0] = o.EV_term[1] = o.EV_term[2] = NAN;
+    o.mean_f[0] = o.mean_f[1] = o.mean_lo[0] = o.mean_lo[1] = o.meansq_f[0] = o.meansq_f[1] = NAN;
+  }
+  for (int k = 0; k < (OBS ? kSu2Acc : kSu2StepAcc); ++k) bad = bad || !isfinite(S[k]);
+  o.EK = kin / V / a6;
+  o.EG = grad / V / (a2 * dx2);
+  o.EK_A = A.wf2 * kA / V / (2.0 * a4);
+  o.EG_A = A.wf2 * mA / V / (a4 * dx4 * A.e * A.e);
+  o.EK_B = A.wf2 * kB / V / (2.0 * a4);
+  o.EG_B = 2.0 * A.wf2 * (2.0 * mB) / V / (a4 * dx4 * A.g * A.g);
   o.EK_f[0] = o.EK;
   o.EK_f[1] = 0.0;
   o.EG_f[0] = o.EG;
   o.EG_f[1] = 0.0;
-  o.mean_f[0] = S[11] / V;
-  o.mean_f[1] = S[12] / V;
-  o.mean_lo[0] = S[13] / V;
-  o.mean_lo[1] = S[14] / V;
-  o.meansq_f[0] = S[15] / V;
-  o.meansq_f[1] = 0.0;
-  bool bad = false;
-  for (int k = 0; k < kSu2Acc; ++k) bad = bad || !isfinite(S[k]);
   const double gauge = o.EK_A + o.EG_A + o.EK_B + o.EG_B;
   const double rho = o.EK + o.EG + o.EV + gauge;
   double b_out = b_in, b_sync = b_in, hc = 0.0;
@@ -505,7 +789,7 @@ __global__ __launch_bounds__(kSu2FinishThreads) void su2_finish_kernel(Su2Args<T
     const double rhs = A.fmp2 / 3.0 * apow(a, 2.0 * (al + 1.0)) * rho;
     hc = fabs(b_sync * b_sync - rhs) / (b_sync * b_sync);
   }
-  const double eta_new = st->eta + pd.wd * A.h;
+  const double eta_new = in->eta + pd.wd * A.h;
   o.eta = eta_new;
   o.a = a;
   o.b = b_sync;
@@ -517,13 +801,31 @@ __global__ __launch_bounds__(kSu2FinishThreads) void su2_finish_kernel(Su2Args<T
   o.step = 0;
   o.staggered = lf ? 1 : 0;
   o.reserved = 0;
-  st->obs = o;
-  if (bad) st->nonfinite = 1;
+  a_next = pd.update ? a : a_in;
+  b_next = pd.update ? b_out : b_in;
+  if (!out) return;
+  if (out != in) *out = *in;
+  out->obs = o;
+  if (bad) out->nonfinite = 1;
   if (pd.update) {
-    st->a = a;
-    st->b = b_out;
-    st->eta = eta_new;
+    out->a = a;
+    out->b = b_out;
+    out->eta = eta_new;
   }
+}
+
+// The finish of the pass described by A, into `out`: one block of
+// kSu2FinishThreads threads (four waves leave each thread the registers for
+// its FP64 sums).
+constexpr int kSu2FinishThreads = 256;
+
+template <typename T, bool OBS>
+__global__ __launch_bounds__(kSu2FinishThreads) void su2_finish_kernel(Su2PassArgs<T> A, int nblocks, DevState* out) {
+  constexpr int NACC = OBS ? kSu2Acc : kSu2StepAcc;
+  double S[NACC];
+  if (!su2_reduce_records<NACC, kSu2FinishThreads>(A.partials, nblocks, S)) return;
+  double an, bn;
+  su2_finish_state<T, OBS>(A, A.pd, A.st, S, out, an, bn);
 }
 
 // Gauss residuals (Sec. 5.2 and Sec. 6.2, with the electric field at n - i
@@ -610,45 +912,111 @@ static void su2_fill(lattice* h, Su2Args<T>& A, const PassDesc& pd) {
   A.wf2 = h->p.omega_over_f * h->p.omega_over_f;
   A.h = h->p.dt;
   A.expand = h->p.expansion;
-  A.fields_in_dst = 0;
   A.pd = pd;
   A.partials = h->partials;
   A.st = h->st;
 }
 
-// One pass of the shared schedule: drift (when wd != 0) into the other
-// buffer, kick, finish; the buffers swap when the pass writes.
 template <typename T>
-static int su2_pass_t(lattice* h, const PassDesc& pd) {
-  Su2Args<T> A;
-  su2_fill(h, A, pd);
-  const int64_t V = (int64_t)h->p.N * h->p.N * h->p.N;
-  const int nb = (int)((V + 255) / 256);
-  if (pd.wd != 0.0) {
-    if (!pd.write) { set_error("SU(2) pass: a drift must write"); return LAT_EINVAL; }
-    hipLaunchKernelGGL(su2_drift_kernel<T>, dim3(nb), dim3(256), 0, h->stream, A);
+static void su2_pass_args(lattice* h, Su2PassArgs<T>& A, const PassDesc& pd) {
+  A = {};
+  A.src = static_cast<const T*>(h->buf[h->cur][0]);
+  A.dst = static_cast<T*>(h->buf[1 - h->cur][0]);
+  A.N = h->p.N;
+  A.dx = h->dx;
+  A.alpha = h->p.alpha;
+  A.fmp2 = h->p.fstar_over_mp * h->p.fstar_over_mp;
+  A.lam = h->p.lambda;
+  A.m2 = h->p.m2[0];
+  A.e = h->p.e;
+  A.g = h->p.g;
+  A.wf2 = h->p.omega_over_f * h->p.omega_over_f;
+  A.h = h->p.dt;
+  A.expand = h->p.expansion;
+  A.pd = pd;
+  A.partials = h->partials;
+  A.st = h->st;
+}
+
+// Planes per block: every block pays about three planes' work before its
+// first (planes x0-1, x0, x0+1 and what x0-1 hands on), and the chip holds
+// `slots` blocks at once.  At least 256 sites per block, the record regions'
+// size.
+static int su2_xc(int N, int tiles, int slots, int least) {
+  int best = N;
+  double cost = 1e30;
+  for (int xc = least; xc <= N; ++xc) {
+    if (N % xc) continue;
+    const int nb = tiles * (N / xc);
+    const double c = (double)((nb + slots - 1) / slots) * (xc + 3.0);
+    if (c < cost) { cost = c; best = xc; }
+  }
+  return best;
+}
+
+// One pass of the shared schedule in one kernel; the buffers swap when it
+// writes.  Within a chain the finish is the next pass's, else a kernel of its
+// own follows.
+template <typename T, int TZ, int TY, int WPE>
+static int su2_pass_t(lattice* h, const PassDesc& pd, PassChain* chain) {
+  Su2PassArgs<T> A;
+  su2_pass_args(h, A, pd);
+  const int N = h->p.N;
+  constexpr int NT = Su2Tile<TZ, TY>::NT;
+  const int tiles = (N / TZ) * (N / TY);
+  A.XC = su2_xc(N, tiles, 256 * (4 * WPE / (NT / 64)), (256 + NT - 1) / NT);
+  const int nb = tiles * (N / A.XC);
+  if ((int64_t)nb * 256 > (int64_t)N * N * N) { set_error("SU(2) pass: records exceed their region"); return LAT_EINVAL; }
+  A.swizzle = nb % 8 == 0 ? 1 : 0;
+  DevState* slot[2] = {h->st, h->st2};
+  if (chain) {
+    A.st = slot[chain->rd];
+    A.partials = (chain->k & 1) ? h->partials2 : h->partials;
+    A.prev = chain->prev;
+    if (A.prev.partials) A.prev.out = slot[1 - chain->rd];
+  }
+  if (!pd.write) {
+    if (pd.wd != 0.0 || chain) { set_error("SU(2) pass: an observation neither drifts nor chains"); return LAT_EINVAL; }
+    hipLaunchKernelGGL((su2_pass_kernel<T, TZ, TY, WPE, true>), dim3(nb), dim3(NT), 0, h->stream, A);
     CL_HIP(hipGetLastError());
-    A.fields_in_dst = 1;
+    hipLaunchKernelGGL((su2_finish_kernel<T, true>), dim3(1), dim3(kSu2FinishThreads), 0, h->stream, A, nb, h->st);
+    CL_HIP(hipGetLastError());
+    return LAT_OK;
   }
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
-  if (pd.write && 2 * h->timer_used + 1 < h->timer.size()) {
+  if (2 * h->timer_used + 1 < h->timer.size()) {
     ev0 = h->timer[2 * h->timer_used];
     ev1 = h->timer[2 * h->timer_used + 1];
     ++h->timer_used;
   }
-  if (ev0) CL_HIP(hipEventRecord(ev0, h->stream));
-  hipLaunchKernelGGL(su2_kick_kernel<T>, dim3(nb), dim3(256), 0, h->stream, A);
+  if (ev0)
+    hipExtLaunchKernelGGL((su2_pass_kernel<T, TZ, TY, WPE, false>), dim3(nb), dim3(NT), 0, h->stream, ev0, ev1, 0, A);
+  else
+    hipLaunchKernelGGL((su2_pass_kernel<T, TZ, TY, WPE, false>), dim3(nb), dim3(NT), 0, h->stream, A);
   CL_HIP(hipGetLastError());
-  if (ev1) CL_HIP(hipEventRecord(ev1, h->stream));
-  // the kick's nb records folded into R records in the second partials
-  // buffer (it holds max_blocks >= R records of 16 sums), then the finish
-  const int R = (int)std::min<int64_t>(kSu2FoldBlocks, h->max_blocks);
-  hipLaunchKernelGGL(su2_fold_records<kSu2Acc>, dim3(R), dim3(256), 0, h->stream, A.partials, nb, h->partials2);
+  if (chain) {
+    if (A.prev.partials) chain->rd ^= 1;
+    chain->prev = PrevPass{A.partials, nb, pd, nullptr};
+    ++chain->k;
+  } else {
+    hipLaunchKernelGGL((su2_finish_kernel<T, false>), dim3(1), dim3(kSu2FinishThreads), 0, h->stream, A, nb, h->st);
+    CL_HIP(hipGetLastError());
+  }
+  h->cur ^= 1;
+  return LAT_OK;
+}
+
+// Trailing finish of a chain: the last pass's records, from the slot that
+// pass started from, into h->st.
+template <typename T>
+static int su2_chain_finish(lattice* h, const PassChain& c) {
+  Su2PassArgs<T> A;
+  su2_pass_args(h, A, c.prev.pd);
+  A.partials = const_cast<double*>(c.prev.partials);
+  A.st = c.rd ? h->st2 : h->st;
+  hipLaunchKernelGGL((su2_finish_kernel<T, false>), dim3(1), dim3(kSu2FinishThreads), 0, h->stream, A,
+                     c.prev.nblocks, h->st);
   CL_HIP(hipGetLastError());
-  A.partials = h->partials2;
-  hipLaunchKernelGGL(su2_finish_kernel<T>, dim3(1), dim3(kSu2FinishThreads), 0, h->stream, A, R);
-  CL_HIP(hipGetLastError());
-  if (pd.write) h->cur ^= 1;
   return LAT_OK;
 }
 
@@ -665,14 +1033,20 @@ static int su2_gauss_t(lattice* h) {
   return LAT_OK;
 }
 
-static int su2_pass(lattice* h, const PassDesc& pd) {
-  return h->p.precision == LAT_FP32 ? su2_pass_t<float>(h, pd) : su2_pass_t<double>(h, pd);
+static int su2_pass(lattice* h, const PassDesc& pd, PassChain* chain = nullptr) {
+  return h->p.precision == LAT_FP32 ? su2_pass_t<float, 32, 8, 2>(h, pd, chain)
+                                    : su2_pass_t<double, 32, 4, 1>(h, pd, chain);
 }
 
 int su2_step(lattice* h, int64_t n) {
   const std::vector<PassDesc> sched = pass_schedule(h->p.integrator, h->weights, &h->staggered, n);
+  PassChain chain;
   for (const PassDesc& pd : sched) {
-    const int rc = su2_pass(h, pd);
+    const int rc = su2_pass(h, pd, &chain);
+    if (rc) return rc;
+  }
+  if (chain.k) {
+    const int rc = h->p.precision == LAT_FP32 ? su2_chain_finish<float>(h, chain) : su2_chain_finish<double>(h, chain);
     if (rc) return rc;
   }
   h->step += n;

@@ -194,3 +194,44 @@ def test_su2_energy_constraint_ladder_and_orders():
     for lo, hi in zip(order, order[1:]):
         assert hc[0.0025, hi] <= max(hc[0.0025, lo] / 10.0, 1e-12), (lo, hi)
     assert 0.5 < hc[0.0025, "lf2"] / hc[0.0025, "vv2"] < 4.0
+
+
+@pytest.mark.parametrize("precision,N,integ,nsteps,tol", [
+    ("fp64", 32, "lf2", 3, 1e-11), ("fp64", 64, "vv4", 1, 1e-11), ("fp32", 32, "vv2", 3, 2e-5),
+    ("fp32", 96, "lf2", 2, 2e-5), ("fp32", 64, "vv4", 1, 2e-5)])
+def test_su2_pass_sites_on_a_rough_state(precision, N, integ, nsteps, tol):
+    """Site by site against the oracle on a state that is rough at the scale of
+    a site (phases over the whole circle, links all over SU(2)), at the sizes
+    where a block marches one plane and several; every component, tile edges
+    and periodic seams included.  FP32: single sites, a few hundred roundings
+    of 6e-8 each; FP64 the same with 1e-16."""
+    rng = np.random.default_rng(17)
+    cfg = _cfg(N, precision, integrator=integ, e=0.5, g=0.5)
+    st = oracle.su2_vacuum_ic(cfg)
+    th = rng.uniform(-math.pi, math.pi, (3, N, N, N)).astype(np.float32).astype(np.float64)
+    u = rng.normal(size=(3, 4, N, N, N))
+    u = (u / np.sqrt((u ** 2).sum(1, keepdims=True))).astype(np.float32).astype(np.float64)
+    u /= np.sqrt((u ** 2).sum(1, keepdims=True))
+    st["links"] = np.stack([np.cos(th), np.sin(th)], axis=1)
+    st["su2"] = u
+    for key, amp in (("phi", 0.5), ("pi", 0.5), ("piA", 5.0), ("piB", 5.0)):
+        st[key] = amp * rng.normal(size=st[key].shape).astype(np.float32).astype(np.float64)
+    m = oracle.su2_model(cfg)
+    lat = _lattice(cfg)
+    _set(lat, st)
+    h = cfg["dt"]
+    before = lat.spectrum(0)
+    lat.step(nsteps)
+    if integ == "lf2":
+        oracle.su2_lf_startup(m, st, h)
+        oracle.su2_lf_steps(m, st, h, nsteps, omp=True)
+    else:
+        oracle.su2_vv_steps(m, st, h, integ, nsteps, omp=True)
+    s = lat.get_state()
+    for key in STATE:
+        scale = np.sqrt(np.mean(st[key] ** 2))
+        assert np.max(np.abs(s[key] - st[key])) < tol * max(scale, np.max(np.abs(st[key])) / 10), key
+    assert abs(s["a"] - st["a"]) < tol * st["a"] and abs(s["b"] - st["b"]) < tol * abs(st["b"])
+    # the chain's records stay in their regions: the shell geometry behind them is untouched
+    after = lat.spectrum(0)
+    assert np.array_equal(before["k"], after["k"]) and np.array_equal(before["count"], after["count"])
