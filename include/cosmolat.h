@@ -244,15 +244,14 @@ const char* lattice_last_error(void);
 
 /* Tile shape of the fused pass: threads along z, rows of threads along y,
    rows per thread, x-planes per block.  Scalar lattices compile (64,4,2)
-   (64,8,2) (32,8,2) (128,8,2) (256,4,2) (128,4,2) for FP32 two fields, plus
-   the full-row tiles (128,16,1) (256,8,1) (512,4,1), valid only where the first
-   number equals N: a block holds whole z-rows, four sites per thread, and
-   each site's update is bit for bit the general tiles'.  FP64 two fields
-   compile (64,4,2) (32,8,2) (32,4,4) and the full-row tiles (128,8,1)
-   (256,4,1) (512,2,1) (two sites per thread); other scalar storage and field
-   counts (64,4,2) (32,8,2) (32,4,4); U(1) lattices (64,4,2) and
-   (32,8,1) in FP32, (32,8,1) in FP64.  lattice_init picks one (the built-in
-   autotuner times them for N >= 128, once per model, size, precision,
+   (64,8,2) (32,8,2) (128,8,2) (256,4,2) (128,4,2) for FP32 two fields and
+   (64,4,2) (32,8,2) (32,4,4) for other storage and field counts, and for all
+   of them the full-row tiles (N,by,1): a block holds by whole z-rows, four
+   sites per thread in FP32 (by = 4, 8 or 16) and two in FP64 (by = 2, 4 or
+   8), in whole waves of at most 768 threads; each site's update is bit for
+   bit the general tiles'.  U(1) lattices compile (64,4,2) and (32,8,1) in
+   FP32, (32,8,1) in FP64.  lattice_init picks one (by a rule below 128^3, else
+   the built-in autotuner times them, once per model, size, precision,
    integrator and expansion in a process, so that later lattices of the same
    configuration share the tile and with it the order of their FP64 sums);
    this call reports it.  SU(2) x U(1) passes are untiled (0, 0, 0, 0).  */
@@ -313,8 +312,11 @@ int lattice_batch_energies(lattice_batch_t* b, lattice_obs* out);
    Errors: LAT_EINVAL. */
 int lattice_batch_run(lattice_batch_t* b, int run, lattice_t** out);
 
-/* Tile shape shared by the batched pass (see lattice_set_tiling), and graph
-   capture on/off (default on).  Errors: LAT_EINVAL. */
+/* Tile shape shared by the batched pass (see lattice_set_tiling; (32,8,2)
+   (32,4,4) (32,8,4) (64,4,2) (64,4,4), or (4,256,1) in FP32 and (2,256,1) in
+   FP64: blocks of 256 threads with as many whole z-rows of their run as fit,
+   for batches of lattices up to 128^3), and graph capture on/off (default
+   on).  Errors: LAT_EINVAL. */
 int lattice_batch_get_tiling(lattice_batch_t* b, int32_t* tz, int32_t* by, int32_t* ry, int32_t* xc);
 int lattice_batch_set_tiling(lattice_batch_t* b, int32_t tz, int32_t by, int32_t ry, int32_t xc);
 int lattice_batch_use_graph(lattice_batch_t* b, int on);

@@ -25,6 +25,7 @@
 
 #include "common.hpp"
 #include "internal.hpp"
+#include "scalar_rows.hpp"
 #include "scalar_tile.hpp"
 
 namespace cl {
@@ -76,6 +77,58 @@ __global__ __launch_bounds__(TZ* BY, RY <= 4 ? 4 : 1) void batch_pass_kernel(
   });
 }
 
+// Full-row blocks for batches whose lattices are at most 128 sites wide: a
+// block takes as many whole z-rows of its run as fit kBatchRowLanes lanes of W
+// sites.  Against the 32-wide general tile, which the smallest run imposes on
+// all, rows have no z halo and move 16 bytes a lane.
+constexpr int kBatchRowLanes = 256;
+constexpr int kBatchRowN = 128;
+
+template <typename T>
+__host__ __device__ constexpr int batch_row_width() { return sizeof(T) == 4 ? 4 : 2; }
+// y-rows of a block at size N: the most that fit, a divisor of N
+__host__ __device__ inline int batch_rows(int N, int W) {
+  int by = 1;
+  while (2 * by * (N / W) <= kBatchRowLanes && N % (2 * by) == 0) by *= 2;
+  return by;
+}
+
+template <typename T, int NF>
+__global__ __launch_bounds__(kBatchRowLanes) void batch_rows_kernel(
+    const ScalarArgs<T>* runs, const int* tile_run, const int* tile_local, const int* tile_offset,
+    DevState* const* slots, int rd, BatchPrev prev, double* partials, PassDesc pd) {
+  constexpr int W = batch_row_width<T>();
+  int b = blockIdx.x;
+  if ((gridDim.x & 7) == 0) b = (b & 7) * (gridDim.x >> 3) + (b >> 3);
+  const int r = tile_run[b], local = tile_local[b];
+  ScalarArgs<T> A = runs[r];
+  A.pd = pd;
+  A.partials = partials;
+  A.st = slots[2 * r + rd];
+  const int first = tile_offset[r], nrec = tile_offset[r + 1] - first;
+  DevState* const out = slots[2 * r + (rd ^ 1)];
+  // (at most two halo sites per lane up to N = 128)
+  scalar_rows<T, W, NF, NF, true>(A, batch_rows(A.N, W), local, b, [&](double& a_in, double& b_in) {
+    if (prev.partials) {
+      constexpr int NP = Acc<NF, false>::N;
+      __shared__ double ab[2];
+      double S[NP];
+      if (rows_reduce_partials<NP>(prev.partials, first, nrec, S)) {
+        double an, bn;
+        finish_state<T, NF, false>(A, prev.pd, A.st, S, local == 0 ? out : nullptr, an, bn);
+        ab[0] = an;
+        ab[1] = bn;
+      }
+      __syncthreads();
+      a_in = ab[0];
+      b_in = ab[1];
+    } else {
+      a_in = A.st->a;
+      b_in = A.st->b;
+    }
+  });
+}
+
 // Closing finish of a chain, one block per run: slot rd plus the last pass's
 // records give the run's canonical state (slot 0).
 template <typename T, int NF>
@@ -110,7 +163,8 @@ struct BatchChain {
 template <typename T, int NF>
 static hipError_t launch_batch_t(const Tiling& t, int ntiles, const void* runs, const int* tile_run,
                                  const int* tile_local, const int* tile_offset, DevState* const* slots,
-                                 double* partials, const PassDesc& pd, const BatchChain& c, hipStream_t s) {
+                                 double* partials, const PassDesc& pd, const BatchChain& c, size_t row_lds,
+                                 hipStream_t s) {
   const ScalarArgs<T>* R = static_cast<const ScalarArgs<T>*>(runs);
   bool ok = false;
 #define X(a, b, cc)                                                                                            \
@@ -121,6 +175,11 @@ static hipError_t launch_batch_t(const Tiling& t, int ntiles, const void* runs, 
   }
   CL_BATCH_SHAPES(X)
 #undef X
+  if (!ok && t.tz == batch_row_width<T>() && t.by == kBatchRowLanes && t.ry == 1) {
+    hipLaunchKernelGGL((batch_rows_kernel<T, NF>), dim3(ntiles), dim3(kBatchRowLanes), row_lds, s, R, tile_run,
+                       tile_local, tile_offset, slots, c.rd, c.prev, partials, pd);
+    ok = true;
+  }
   if (!ok) return hipErrorInvalidValue;
   return hipGetLastError();
 }
@@ -151,6 +210,7 @@ struct lattice_batch {
   size_t args_bytes;
   int64_t max_tiles;
   int ntiles;
+  size_t row_lds;       // dynamic LDS of a full-row block (the largest over the runs)
   int parity;           // common ping-pong index of all runs
   int use_graph;
   std::map<std::pair<int64_t, int>, std::pair<hipGraph_t, hipGraphExec_t>> graphs;
@@ -196,7 +256,27 @@ static void batch_header(const lattice_params* ps, int nruns, size_t* args_bytes
   *header = o;
 }
 
+// Full-row tile of this batch: W sites per lane, kBatchRowLanes lanes.
+static bool batch_is_rows(const lattice_batch* B, const Tiling& t) {
+  return t.tz == (B->fp32 ? 4 : 2) && t.by == kBatchRowLanes && t.ry == 1;
+}
+// x-chunks of a run's z-y tiles, y-rows of a block
+static int batch_tile_rows(const lattice_batch* B, const Tiling& t, int N) {
+  return batch_is_rows(B, t) ? batch_rows(N, t.tz) : t.by * t.ry;
+}
+static int batch_tiles(const lattice_batch* B, const Tiling& t, int N) {
+  const int nz = batch_is_rows(B, t) ? 1 : N / t.tz;
+  return nz * (N / batch_tile_rows(B, t, N)) * (N / t.xc);
+}
+
 static bool batch_tiling_ok(const lattice_batch* B, const Tiling& t) {
+  if (batch_is_rows(B, t)) {
+    for (lattice* h : B->runs)
+      if (h->p.N > kBatchRowN || t.xc < 1 || h->p.N % t.xc) return false;
+    int64_t nt = 0;
+    for (lattice* h : B->runs) nt += batch_tiles(B, t, h->p.N);
+    return nt <= B->max_tiles;
+  }
   bool compiled = false;
   for (const auto& s : kBatchShapes)
     if (s[0] == t.tz && s[1] == t.by && s[2] == t.ry) compiled = true;
@@ -214,10 +294,12 @@ static bool batch_tiling_ok(const lattice_batch* B, const Tiling& t) {
 template <typename T>
 static int batch_upload_tables(lattice_batch* B) {
   std::vector<int> trun, tloc, toff(1, 0);
-  const int ty = B->tile.by * B->tile.ry;
+  B->row_lds = 0;
   for (int r = 0; r < B->nruns; ++r) {
     const int N = B->runs[r]->p.N;
-    const int nt = (N / B->tile.tz) * (N / ty) * (N / B->tile.xc);
+    const int nt = batch_tiles(B, B->tile, N);
+    if (batch_is_rows(B, B->tile))
+      B->row_lds = std::max(B->row_lds, rows_lds_bytes<T>(B->nf, N, batch_tile_rows(B, B->tile, N)));
     for (int t = 0; t < nt; ++t) {
       trun.push_back(r);
       tloc.push_back(t);
@@ -277,7 +359,7 @@ static hipError_t batch_launch(lattice_batch* B, const PassDesc& pd, int parity,
   auto go = [&](auto* tag, auto nf) {
     using T = std::remove_pointer_t<decltype(tag)>;
     return launch_batch_t<T, decltype(nf)::value>(B->tile, B->ntiles, args, B->tile_run, B->tile_local,
-                                                  B->tile_offset, B->slots, part, pd, c, B->stream);
+                                                  B->tile_offset, B->slots, part, pd, c, B->row_lds, B->stream);
   };
   if (B->fp32)
     e = B->nf == 1 ? go((float*)nullptr, std::integral_constant<int, 1>{})
@@ -322,10 +404,10 @@ static int sync_parity(lattice_batch* B) {
   return LAT_OK;
 }
 
-// Time every shape and x-chunk in two sweeps (six chained passes each, after
-// a warm-up pass) and keep the one with the smallest time of the two: one
-// short timing picked x-chunks 8 and 16 in turn between runs of the same
-// ensemble, a spread of 6% in the pass time.
+// Time every shape and x-chunk (six chained passes each, after a warm-up pass),
+// those within a tenth of the quickest once more, and keep the one with the
+// smallest time: one short timing picked x-chunks 8 and 16 in turn between
+// runs of the same ensemble, a spread of 6% in the pass time.
 static int batch_autotune(lattice_batch* B) {
   hipEvent_t e0, e1;
   CL_HIP(hipEventCreate(&e0));
@@ -337,13 +419,19 @@ static int batch_autotune(lattice_batch* B) {
       Tiling t{s[0], s[1], s[2], xc};
       if (batch_tiling_ok(B, t)) cands.push_back(t);
     }
+  for (int xc : xcs) {
+    Tiling t{B->fp32 ? 4 : 2, kBatchRowLanes, 1, xc};
+    if (batch_tiling_ok(B, t)) cands.push_back(t);
+  }
   std::vector<float> tmin(cands.size(), 1e30f);
   // chained passes into the other buffers that leave a and b as they are
   // (update 0), as lattice_batch_step chains them; the closing finish
   // stores only observables
   const PassDesc pd = pass(1.0, 0.5, 0.5, MODE_VV, 1, 0);
+  float least = 1e30f;
   for (int sweep = 0; sweep < 2; ++sweep)
     for (size_t i = 0; i < cands.size(); ++i) {
+      if (sweep && tmin[i] > 1.1f * least) continue;
       B->tile = cands[i];
       int rc = batch_upload(B);
       if (rc) return rc;
@@ -359,6 +447,7 @@ static int batch_autotune(lattice_batch* B) {
       float ms = 0.f;
       CL_HIP(hipEventElapsedTime(&ms, e0, e1));
       tmin[i] = std::min(tmin[i], ms);
+      least = std::min(least, ms);
     }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);

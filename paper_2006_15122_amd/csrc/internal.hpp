@@ -108,7 +108,7 @@ int scalar_chain_end(lattice* h, const PassChain& chain);
 // blocks of a scalar observation pass (its fixed tile) at size N
 int64_t scalar_obs_blocks(int N);
 int num_shapes(int fp32, int nf);
-void get_shape(int fp32, int nf, int i, int* tz, int* by, int* ry);
+bool get_shape(int fp32, int nf, int N, int i, int* tz, int* by, int* ry);
 hipError_t launch_scalar_pass(int fp32, int nf, const void* const* src, void* const* dst, int N, int tz, int by,
                               int ry, int xc, int swizzle, const double* phys, int expand, const PassDesc& pd,
                               double* partials, DevState* st, hipStream_t s, int* nblocks_out, int full,

@@ -690,7 +690,7 @@ bool tiling_ok(const lattice* h, const Tiling& t) {
   for (int i = 0; i < ns; ++i) {
     int tz, by, ry;
     if (u1) u1_get_shape(fp32, i, &tz, &by, &ry);
-    else get_shape(fp32, h->p.nf, i, &tz, &by, &ry);
+    else if (!get_shape(fp32, h->p.nf, h->p.N, i, &tz, &by, &ry)) continue;
     if (tz == t.tz && by == t.by && ry == t.ry) compiled = true;
   }
   if (!compiled) return false;
@@ -719,18 +719,32 @@ void default_tiling(lattice* h) {
     h->tile = t;
     return;
   }
-  Tiling cands[] = {{64, 4, 4, 16}, {64, 4, 2, 16}, {32, 8, 2, 8}, {32, 4, 4, 4}};
-  for (const Tiling& t : cands)
-    if (tiling_ok(h, t)) { h->tile = t; return; }
-  h->tile = Tiling{32, 4, 4, 4};
+  // Below 128^3 (where no tuner runs) a pass is latency: as many blocks as the
+  // record regions take, 1024 sites each, marching as few planes as that
+  // gives.  FP64 two-field lattices take full rows (32^3, 64^3, 96^3: 9.8, 9.8
+  // and 18.9 us a pass against 12.2, 13.1 and 27.4 for the best general tile),
+  // the others the two-row tile (FP32 64^3: 9.1 us with two planes a block, 21.5
+  // with sixteen), from 512 blocks on with more planes rather than more blocks
+  // (FP32 96^3: 12.8 us with four, 14.6 with two).
+  const bool rows = h->p.precision == LAT_FP64 && h->p.nf == 2;
+  Tiling t = rows ? Tiling{N, N % 64 ? 4 : 8, 1, 1} : N % 64 == 0 ? Tiling{64, 4, 2, 1} : Tiling{32, 8, 2, 1};
+  if (rows && N == 32) t.by = 8;
+  const int64_t plane = (int64_t)t.tz * t.by * t.ry, tiles = (int64_t)N * N / plane;
+  for (int c = 1; c <= N; ++c) {
+    if (N % c) continue;
+    t.xc = c;
+    if (plane * c >= 1024 && (rows || tiles * (N / c) <= 512) && tiling_ok(h, t)) break;
+  }
+  h->tile = tiling_ok(h, t) ? t : Tiling{32, 8, 2, 8};
 }
 
 // Time every compiled tile shape and x-chunk on zeroed state buffers with
 // chains of full passes (a, b left untouched) that ping-pong between the two
-// buffers as lattice_step does; keep the fastest.  Each candidate is timed in
-// two sweeps over all of them and keeps its quicker time, so that one slow
-// sample (a clock ramp, a neighbour's traffic) cannot hand the choice to a
-// tile 5-10% slower.  The caller builds the initial state afterwards.
+// buffers as lattice_step does; keep the fastest.  One sweep over every
+// candidate, then two over those within a tenth of the quickest, each
+// keeping its quicker time, so that one slow sample (a clock ramp, a
+// neighbour's traffic) cannot hand the choice to a tile 5-10% slower.  The
+// caller builds the initial state afterwards.
 int autotune(lattice* h) {
   // zero state (finite arithmetic), a = 1, b = 0; the caller builds the real
   // state after tuning
@@ -744,7 +758,10 @@ int autotune(lattice* h) {
   CL_HIP(hipEventCreate(&e0));
   CL_HIP(hipEventCreate(&e1));
   const bool u1 = is_u1(h->p);
-  const std::vector<int> xcs = u1 ? std::vector<int>{4, 8, 16, 32, 64} : std::vector<int>{8, 16, 32, 64};
+  // planes per block: few enough to fill the chip, many enough for the two
+  // planes every block reads beyond its own
+  std::vector<int> xcs = {8, 12, 16, 24, 32, 48, 64};
+  if (u1 || h->p.N < 256) xcs.insert(xcs.begin(), {4, 6});
   Tiling bt = h->tile;
   const int fp32 = h->p.precision == LAT_FP32;
   const PassDesc pd = pass(1.0, 0.5, 0.5, MODE_VV, 1, 0);
@@ -761,20 +778,22 @@ int autotune(lattice* h) {
   for (int i = 0; i < ns; ++i) {
     int tz, by, ry;
     if (u1) u1_get_shape(fp32, i, &tz, &by, &ry);
-    else get_shape(fp32, h->p.nf, i, &tz, &by, &ry);
+    else if (!get_shape(fp32, h->p.nf, h->p.N, i, &tz, &by, &ry)) continue;
     for (int xc : xcs) {
       const Tiling t{tz, by, ry, xc};
       if (tiling_ok(h, t)) cand.push_back(t);
     }
   }
   std::vector<float> tbest(cand.size(), 1e30f);
-  for (int sweep = 0; sweep < 2 && !rc; ++sweep) {
+  float least = 1e30f;
+  for (int sweep = 0; sweep < 3 && !rc; ++sweep) {
     for (size_t i = 0; i < cand.size() && !rc; ++i) {
+      if (sweep && tbest[i] > 1.1f * least) continue;
       h->tile = cand[i];
       rc = run(2);  // warm-up, ping-pong
       if (rc) break;
       hipError_t e = hipEventRecord(e0, h->stream);
-      if (e == hipSuccess) rc = run(6);
+      if (e == hipSuccess) rc = run(h->p.N < 256 ? 12 : 6);
       if (!rc && e == hipSuccess) e = hipEventRecord(e1, h->stream);
       if (!rc && e == hipSuccess) e = hipEventSynchronize(e1);
       float ms = 0.f;
@@ -785,6 +804,7 @@ int autotune(lattice* h) {
         break;
       }
       tbest[i] = std::min(tbest[i], ms);
+      least = std::min(least, ms);
     }
   }
   float best = 1e30f;

@@ -55,13 +55,15 @@ hipError_t launch_shape(const ScalarArgs<T>& A, int nblocks, hipStream_t s, hipE
 }
 
 // Full-row tiles (stepping passes): tz = N, ry = 1, by y-rows per block.
-template <typename T, int W, int NF, int NL, int BY>
+template <typename T, int W, int NF, int BY>
 hipError_t launch_rows(const ScalarArgs<T>& A, int nblocks, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1,
                        DevState* fin) {
+  const dim3 blk(A.N / W * BY);
+  const size_t shm = rows_lds_bytes<T>(NF, A.N, BY);
   if (ev0)
-    hipExtLaunchKernelGGL((scalar_rows_kernel<T, W, NF, NL, BY>), dim3(nblocks), dim3(NL * BY), 0, s, ev0, ev1, 0, A);
+    hipExtLaunchKernelGGL((scalar_rows_kernel<T, W, NF, BY>), dim3(nblocks), blk, shm, s, ev0, ev1, 0, A);
   else
-    hipLaunchKernelGGL((scalar_rows_kernel<T, W, NF, NL, BY>), dim3(nblocks), dim3(NL * BY), 0, s, A);
+    hipLaunchKernelGGL((scalar_rows_kernel<T, W, NF, BY>), dim3(nblocks), blk, shm, s, A);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !fin) return e;
   hipLaunchKernelGGL((scalar_finish_kernel<T, NF, false>), dim3(1), dim3(kFinishThreads), 0, s, A, nblocks, fin);
@@ -84,23 +86,24 @@ hipError_t launch_rows(const ScalarArgs<T>& A, int nblocks, hipStream_t s, hipEv
   X(T, NF, 32, 8, 2)              \
   X(T, NF, 32, 4, 4)
 
-// full-row shapes (tz = N sites, by rows, ry = 1), 512 lanes, for N = 128,
-// 256 and 512 (1024-lane blocks of these spill): four sites per lane in
-// FP32 storage, two in FP64 (two FP32 sites per lane fit two blocks per CU
-// but are slower: 113.9 against 109.7 us per pass at 256^3)
-#define CL_ROWS_MAIN(X, NF) \
-  X(float, NF, 128, 16, 4)  \
-  X(float, NF, 256, 8, 4)   \
-  X(float, NF, 512, 4, 4)
-#define CL_ROWS_F64(X, NF)  \
-  X(double, NF, 128, 8, 2)  \
-  X(double, NF, 256, 4, 2)  \
-  X(double, NF, 512, 2, 2)
+// full-row shapes (tz = N sites, by rows, ry = 1) in blocks of at most
+// kRowsMaxThreads lanes and 96 KB of LDS: four sites per lane in FP32 storage,
+// two in FP64 (two FP32 sites per lane fit two blocks per CU but are slower:
+// 113.9 against 109.7 us per pass at 256^3)
+#define CL_ROWS_F32(X, T, NF) \
+  X(T, NF, 4, 4)              \
+  X(T, NF, 4, 8)              \
+  X(T, NF, 4, 16)
+#define CL_ROWS_F64(X, T, NF) \
+  X(T, NF, 2, 2)              \
+  X(T, NF, 2, 4)              \
+  X(T, NF, 2, 8)
 
-static const Shape kShapesMain[] = {{64, 4, 2}, {64, 8, 2},  {32, 8, 2},  {128, 8, 2}, {256, 4, 2},
-                                    {128, 4, 2}, {128, 16, 1}, {256, 8, 1}, {512, 4, 1}};
-static const Shape kShapesSmall[] = {{64, 4, 2}, {32, 8, 2}, {32, 4, 4}};
-static const Shape kShapesF64[] = {{64, 4, 2}, {32, 8, 2}, {32, 4, 4}, {128, 8, 1}, {256, 4, 1}, {512, 2, 1}};
+// general shapes, then full-row ones (tz = 0 stands for N)
+static const Shape kShapesMain[] = {{64, 4, 2},  {64, 8, 2}, {32, 8, 2}, {128, 8, 2}, {256, 4, 2},
+                                    {128, 4, 2}, {0, 4, 1},  {0, 8, 1},  {0, 16, 1}};
+static const Shape kShapesSmall[] = {{64, 4, 2}, {32, 8, 2}, {32, 4, 4}, {0, 4, 1}, {0, 8, 1}, {0, 16, 1}};
+static const Shape kShapesF64[] = {{64, 4, 2}, {32, 8, 2}, {32, 4, 4}, {0, 2, 1}, {0, 4, 1}, {0, 8, 1}};
 
 // Observation passes always use the 32 x 16 tile with 8 planes, which
 // divides every supported N.
@@ -117,31 +120,38 @@ hipError_t launch_scalar_pass_t(const ScalarArgs<T>& A, const Shape& sh, int nbl
 #define X(TT, NFF, a, b, c) \
   if (sh.tz == a && sh.by == b && sh.ry == c)  \
     return launch_shape<TT, NFF, false, a, b, c>(A, nblocks, s, ev0, ev1, fin);
+#define XR(TT, NFF, w, b) \
+  if (sh.ry == 1 && sh.by == b) return launch_rows<TT, w, NFF, b>(A, nblocks, s, ev0, ev1, fin);
   if constexpr (std::is_same<T, float>::value && NF == 2) {
     CL_SHAPES_MAIN(X, T, NF)
-#define XR(TT, NFF, n, b, w) \
-  if (sh.tz == n && sh.by == b && sh.ry == 1) return launch_rows<TT, w, NFF, n / w, b>(A, nblocks, s, ev0, ev1, fin);
-    CL_ROWS_MAIN(XR, NF)
   } else {
     CL_SHAPES_SMALL(X, T, NF)
-    if constexpr (std::is_same<T, double>::value && NF == 2) {
-      CL_ROWS_F64(XR, NF)
-    }
-#undef XR
   }
+  if constexpr (std::is_same<T, float>::value) {
+    CL_ROWS_F32(XR, T, NF)
+  } else {
+    CL_ROWS_F64(XR, T, NF)
+  }
+#undef XR
 #undef X
   return hipErrorInvalidValue;
 }
 
 int num_shapes(int fp32, int nf) {
-  if (nf == 2) return fp32 ? (int)(sizeof(kShapesMain) / sizeof(Shape)) : (int)(sizeof(kShapesF64) / sizeof(Shape));
-  return (int)(sizeof(kShapesSmall) / sizeof(Shape));
+  if (fp32) return nf == 2 ? (int)(sizeof(kShapesMain) / sizeof(Shape)) : (int)(sizeof(kShapesSmall) / sizeof(Shape));
+  return (int)(sizeof(kShapesF64) / sizeof(Shape));
 }
-void get_shape(int fp32, int nf, int i, int* tz, int* by, int* ry) {
-  const Shape& sh = nf == 2 ? (fp32 ? kShapesMain[i] : kShapesF64[i]) : kShapesSmall[i];
-  *tz = sh.tz;
+// Shape i at size N; false where a full-row block would hold a part of a
+// wave, too many lanes or too much LDS.
+bool get_shape(int fp32, int nf, int N, int i, int* tz, int* by, int* ry) {
+  const Shape& sh = fp32 ? (nf == 2 ? kShapesMain[i] : kShapesSmall[i]) : kShapesF64[i];
+  *tz = sh.tz ? sh.tz : N;
   *by = sh.by;
   *ry = sh.ry;
+  if (sh.ry > 1) return true;
+  const int nt = N / (fp32 ? 4 : 2) * sh.by;
+  const size_t lds = fp32 ? rows_lds_bytes<float>(nf, N, sh.by) : rows_lds_bytes<double>(nf, N, sh.by);
+  return nt % 64 == 0 && nt <= kRowsMaxThreads && lds <= 98304;
 }
 
 

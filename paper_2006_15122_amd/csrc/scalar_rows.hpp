@@ -13,6 +13,11 @@
 // z halo loads at all), every global access is a whole 16-byte lane segment
 // of a row, and one address serves W sites.  The only halo left is the two
 // y-rows above and below the block, spread over all lanes.
+//
+// N is a run-time number (any multiple of 32), so the block size is too: with
+// BY a multiple of 64 / W every block is whole waves.  Each row's place in LDS
+// is an address formed once per lane, which costs nothing measurable against
+// rows of a compiled length.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -41,24 +46,86 @@ __device__ __forceinline__ T lane_sum(const T (&v)[W]) {
   return v[0];
 }
 
-template <typename T, int W, int NF, int NL, int BY, typename GetAB>
-__device__ __forceinline__ void scalar_rows(const ScalarArgs<T>& A, int tile, int pidx, GetAB get_ab) {
+// Per-lane accumulators of a block of whole waves into partials[pidx] (wave
+// shuffles, then the waves in order).
+constexpr int kRowsMaxThreads = 768;
+
+template <int NACC>
+__device__ __forceinline__ void rows_partials(double* partials, double (&acc)[NACC], int pidx) {
+  __shared__ double red[kRowsMaxThreads / 64][NACC];
+  const int tid = threadIdx.x, nw = blockDim.x >> 6;
+#pragma unroll
+  for (int k = 0; k < NACC; ++k) {
+    const double s = wave_sum(acc[k]);
+    if ((tid & 63) == 0) red[tid >> 6][k] = s;
+  }
+  __syncthreads();
+  if (tid < NACC) {
+    double s = 0.0;
+    for (int w = 0; w < nw; ++w) s += red[w][tid];
+    partials[(size_t)pidx * NACC + tid] = s;
+  }
+}
+
+// As reduce_partials, for a block of any number of whole waves.
+template <int NACC>
+__device__ bool rows_reduce_partials(const double* partials, int first, int nb, double (&S)[NACC]) {
+  __shared__ double red[kRowsMaxThreads / 64][NACC];
+  const int tid = threadIdx.x, nw = blockDim.x >> 6;
+  double tot[NACC];
+#pragma unroll
+  for (int k = 0; k < NACC; ++k) tot[k] = 0.0;
+  for (int b = tid; b < nb; b += blockDim.x) {
+#pragma unroll
+    for (int k = 0; k < NACC; ++k) tot[k] += partials[(size_t)(first + b) * NACC + k];
+  }
+#pragma unroll
+  for (int k = 0; k < NACC; ++k) {
+    const double s = wave_sum(tot[k]);
+    if ((tid & 63) == 0) red[tid >> 6][k] = s;
+  }
+  __syncthreads();
+  if (tid != 0) return false;
+  for (int k = 0; k < NACC; ++k) {
+    double s = 0.0;
+    for (int w = 0; w < nw; ++w) s += red[w][k];
+    S[k] = s;
+  }
+  return true;
+}
+
+// LDS bytes of a block: two planes of NF fields, BY + 2 rows each
+template <typename T>
+__host__ __device__ constexpr size_t rows_lds_bytes(int nf, int N, int by) {
+  return (size_t)2 * nf * (by + 2) * N * sizeof(T);
+}
+
+// KH: halo sites per lane, at least 2 NF W / BY.  IDLE: the block may have more
+// lanes than the NL BY its rows take (batches of several N); the lanes beyond
+// only join the barriers and sums.
+template <typename T, int W, int NF, int KH, bool IDLE, typename GetAB>
+__device__ __forceinline__ void scalar_rows(const ScalarArgs<T>& A, const int BY, int tile, int pidx, GetAB get_ab) {
   using VW = typename RowVec<T, W>::type;  // W consecutive sites
-  constexpr int N = W * NL;
-  constexpr int NT = NL * BY;
   constexpr int NACC = Acc<NF, false>::N;
-  static_assert(NT % 64 == 0 && NT <= 1024, "block of whole waves");
   // drifted planes in two buffers: plane x0 + i in buffer i & 1 (x0 - 1 in
   // buffer 1), rows y0-1 .. y0+BY, each a whole z-row; the x-1 neighbours of
   // the stencil are read from the other buffer
-  __shared__ VW lds[2][NF][BY + 2][NL];
+  extern __shared__ __align__(16) unsigned char rows_smem[];
+  VW* const lds = reinterpret_cast<VW*>(rows_smem);
 
+  const int N = A.N, NL = N / W, NT = NL * BY;
   const int tid = threadIdx.x;
-  const int tz = tid % NL, ty = tid / NL;
-  constexpr int nyt = N / BY;
+  const int ty = tid / NL, tz = tid - ty * NL;
+  const bool active = !IDLE || tid < NT;
+  const int fst = (BY + 2) * NL, bst = NF * fst;  // field and buffer strides
+  const int nyt = N / BY;
   const int yt = tile % nyt, xcI = tile / nyt;
   const int y0 = yt * BY, x0 = xcI * A.XC;
   const size_t NN = (size_t)N * N;
+  const int own = (1 + ty) * NL + tz;  // this lane's place in a row buffer
+  // its z-neighbours' places, in sites (periodic in the row)
+  const int zl = ((1 + ty) * NL + (tz == 0 ? NL - 1 : tz - 1)) * W + W - 1;
+  const int zh = ((1 + ty) * NL + (tz == NL - 1 ? 0 : tz + 1)) * W;
 
   const Coef<T> ckick = ucoef<T>((A.pd.wk1 + A.pd.wk2) * A.h);
   const Coef<T> cE = ucoef<T>((A.pd.mode == MODE_LF ? (A.pd.wk1 + A.pd.wk2) : A.pd.wk1) * A.h);
@@ -72,19 +139,38 @@ __device__ __forceinline__ void scalar_rows(const ScalarArgs<T>& A, int tile, in
   for (int k = 0; k < NACC; ++k) acc[k] = 0.0;
 
   const int y = y0 + ty;
-  const int ly = 1 + ty;
   // register planes (four sites each): pc = drifted x, qc = momentum at x,
   // (pn, qn) = raw x+1, (pf, qf) = raw x+2 in flight
   VW pc[NF], qc[NF], pn[NF], qn[NF], pf[NF], qf[NF];
 
   // halo rows y0-1 and y0+BY of plane x+1, loaded one plane ahead of their
   // use: 2 NF N single sites spread over all lanes, KH per lane
-  constexpr int NHI = 2 * NF * N;
-  constexpr int KH = (NHI + NT - 1) / NT;
+  const int NHI = 2 * NF * N;
   T hp[KH], hq[KH];
+  // halo item k of this lane: row r (0: y0-1, 1: y0+BY), field f, site z; its
+  // place in the fields and in a row buffer
+  const T *hsrc[KH], *hsrq[KH];
+  int hl[KH];
+#pragma unroll
+  for (int k = 0; k < KH; ++k) {
+    const int it = tid + k * NT;
+    const int rf = it / N, z = it - rf * N, r = rf / NF, f = rf - r * NF;
+    const int yy = r == 0 ? (y0 - 1 + N) % N : (y0 + BY) % N;
+    hsrc[k] = (f == 0 ? A.src[0] : A.src[NF - 1]) + (size_t)yy * N + z;
+    hsrq[k] = (f == 0 ? A.src[2] : A.src[2 + NF - 1]) + (size_t)yy * N + z;
+    hl[k] = active && it < NHI ? f * fst * W + (r == 0 ? 0 : BY + 1) * N + z : -1;
+  }
 
-  auto at = [&](const T* base, size_t o) { return *reinterpret_cast<const VW*>(base + o); };
+  auto at = [&](const T* base, size_t o) {
+    return *reinterpret_cast<const __attribute__((address_space(1))) VW*>(
+        (const __attribute__((address_space(1))) T*)base + o);
+  };
+  auto store = [&](const VW& v, T* base, size_t o) {
+    __builtin_nontemporal_store(v, reinterpret_cast<__attribute__((address_space(1))) VW*>(
+                                       (__attribute__((address_space(1))) T*)base + o));
+  };
   auto load_own = [&](int x, VW (&p)[NF], VW (&pq)[NF]) {
+    if (!active) return;
     const size_t o = (size_t)x * NN + (size_t)y * N + W * tz;
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
@@ -92,23 +178,12 @@ __device__ __forceinline__ void scalar_rows(const ScalarArgs<T>& A, int tile, in
       pq[f] = at(A.src[2 + f], o);
     }
   };
-  // halo item k of this lane: row r (0: y0-1, 1: y0+BY), field f, site z
-  auto halo_item = [&](int k, int& r, int& f, int& z) {
-    const int it = tid + k * NT;
-    r = it / (NF * N);
-    f = (it / N) % NF;
-    z = it % N;
-    return it < NHI;
-  };
   auto load_halo = [&](int x) {
 #pragma unroll
     for (int k = 0; k < KH; ++k) {
-      int r, f, z;
-      if (halo_item(k, r, f, z)) {
-        const int yy = r == 0 ? (y0 - 1 + N) % N : (y0 + BY) % N;
-        const size_t o = (size_t)x * NN + (size_t)yy * N + z;
-        hp[k] = (f == 0 ? A.src[0] : A.src[NF - 1])[o];
-        hq[k] = (f == 0 ? A.src[2] : A.src[2 + NF - 1])[o];
+      if (hl[k] >= 0) {
+        hp[k] = load_g(hsrc[k], (size_t)x * NN);
+        hq[k] = load_g(hsrq[k], (size_t)x * NN);
       }
     }
   };
@@ -137,21 +212,20 @@ __device__ __forceinline__ void scalar_rows(const ScalarArgs<T>& A, int tile, in
   // the drifted plane into LDS buffer b: own rows from registers, halo rows
   // drifted here
   auto store_lds = [&](int b) {
+    if (!active) return;
 #pragma unroll
-    for (int f = 0; f < NF; ++f) lds[b][f][ly][tz] = pc[f];
+    for (int f = 0; f < NF; ++f) lds[b * bst + f * fst + own] = pc[f];
+    T* const row = reinterpret_cast<T*>(lds + b * bst);
 #pragma unroll
-    for (int k = 0; k < KH; ++k) {
-      int r, f, z;
-      if (halo_item(k, r, f, z)) {
-        T* row = reinterpret_cast<T*>(&lds[b][f][r == 0 ? 0 : BY + 1][0]);
-        row[z] = fma_c(cdrift, hq[k], hp[k]);
-      }
-    }
+    for (int k = 0; k < KH; ++k)
+      if (hl[k] >= 0) row[hl[k]] = fma_c(cdrift, hq[k], hp[k]);
   };
+  if (active) {
 #pragma unroll
-  for (int f = 0; f < NF; ++f) {
-    lds[1][f][ly][tz] = drift(qf[f], pm[f]);
-    pc[f] = drift(qc[f], pc[f]);
+    for (int f = 0; f < NF; ++f) {
+      lds[bst + f * fst + own] = drift(qf[f], pm[f]);
+      pc[f] = drift(qc[f], pc[f]);
+    }
   }
   store_lds(0);
 
@@ -166,61 +240,64 @@ __device__ __forceinline__ void scalar_rows(const ScalarArgs<T>& A, int tile, in
       load_halo((x + 1) % N);
     }
     __syncthreads();
-    const size_t o = (size_t)x * NN + (size_t)y * N + W * tz;
-    // plane x+1 drifted, in place
+    if (active) {
+      const size_t o = (size_t)x * NN + (size_t)y * N + W * tz;
+      // plane x+1 drifted, in place
 #pragma unroll
-    for (int f = 0; f < NF; ++f) pn[f] = drift(qn[f], pn[f]);
-    // the potential at the lane's W sites, summed pairwise in storage
-    // precision and added to the FP64 total once per plane
-    {
-      T v4[W];
+      for (int f = 0; f < NF; ++f) pn[f] = drift(qn[f], pn[f]);
+      // the potential at the lane's W sites, summed pairwise in storage
+      // precision and added to the FP64 total once per plane
+      {
+        T v4[W];
 #pragma unroll
-      for (int e = 0; e < W; ++e) {
-        const T p2 = pc[0][e] * pc[0][e];
-        T v = p2 * fma_t(qlam, p2, hm2_0);
-        if constexpr (NF > 1) {
-          const T c2 = pc[1][e] * pc[1][e];
-          v = fma_t(c2, fma_t(hqq, p2, hm2_1), v);
+        for (int e = 0; e < W; ++e) {
+          const T p2 = pc[0][e] * pc[0][e];
+          T v = p2 * fma_t(qlam, p2, hm2_0);
+          if constexpr (NF > 1) {
+            const T c2 = pc[1][e] * pc[1][e];
+            v = fma_t(c2, fma_t(hqq, p2, hm2_1), v);
+          }
+          v4[e] = v;
         }
-        v4[e] = v;
+        acc[3] += (double)lane_sum<T, W>(v4);
       }
-      acc[3] += (double)lane_sum<T, W>(v4);
-    }
 #pragma unroll
-    for (int f = 0; f < NF; ++f) {
-      const VW xm4 = lds[1 - B][f][ly][tz];
-      const VW yp = lds[B][f][ly + 1][tz], ym = lds[B][f][ly - 1][tz];
-      // the z-neighbours outside the lane's four sites, periodic in the row
-      const T zlo = lds[B][f][ly][(tz + NL - 1) % NL][W - 1];
-      const T zhi = lds[B][f][ly][(tz + 1) % NL][0];
-      VW pout;
-      T s0 = T(0), s1 = T(0), s2 = T(0);
+      for (int f = 0; f < NF; ++f) {
+        const VW* const pl = lds + B * bst + f * fst;
+        const VW xm4 = lds[(1 - B) * bst + f * fst + own];
+        const VW yp = pl[own + NL], ym = pl[own - NL];
+        // the z-neighbours outside the lane's sites
+        const T zlo = reinterpret_cast<const T*>(pl)[zl];
+        const T zhi = reinterpret_cast<const T*>(pl)[zh];
+        VW pout;
+        T s0 = T(0), s1 = T(0), s2 = T(0);
 #pragma unroll
-      for (int e = 0; e < W; ++e) {
-        T cur[NF];
+        for (int e = 0; e < W; ++e) {
+          T cur[NF];
 #pragma unroll
-        for (int g = 0; g < NF; ++g) cur[g] = pc[g][e];
-        const T c = cur[f];
-        const T zp = e == W - 1 ? zhi : pc[f][e + 1];
-        const T zm = e == 0 ? zlo : pc[f][e - 1];
-        // the general tile's Laplacian, term for term
-        const T lap = ((xm4[e] - c) + (pn[f][e] - c)) + ((yp[e] - c) + (ym[e] - c)) + ((zp - c) + (zm - c));
-        const T K = fma_c(clap, lap, -mul_c(cpot, dpot<T, NF>(f, cur, m2_0c, m2_1c, lamc, qc_)));
-        const T pin = qc[f][e];
-        pout[e] = fma_c(ckick, K, pin);
-        const T pe = fma_c(cE, K, pin);
-        const T gx = pn[f][e] - c, gy = yp[e] - c, gz = zp - c;
-        s0 = fma_t(pin, pin, s0);
-        s1 = fma_t(pe, pe, s1);
-        s2 += gx * gx + gy * gy + gz * gz;
+          for (int g = 0; g < NF; ++g) cur[g] = pc[g][e];
+          const T c = cur[f];
+          const T zp = e == W - 1 ? zhi : pc[f][e + 1];
+          const T zm = e == 0 ? zlo : pc[f][e - 1];
+          // the general tile's Laplacian, term for term
+          const T lap = ((xm4[e] - c) + (pn[f][e] - c)) + ((yp[e] - c) + (ym[e] - c)) + ((zp - c) + (zm - c));
+          const T K = fma_c(clap, lap, -mul_c(cpot, dpot<T, NF>(f, cur, m2_0c, m2_1c, lamc, qc_)));
+          const T pin = qc[f][e];
+          pout[e] = fma_c(ckick, K, pin);
+          const T pe = fma_c(cE, K, pin);
+          const T gx = pn[f][e] - c, gy = yp[e] - c, gz = zp - c;
+          s0 = fma_t(pin, pin, s0);
+          s1 = fma_t(pe, pe, s1);
+          s2 += gx * gx + gy * gy + gz * gz;
+        }
+        // the W sites' terms summed in storage precision, then into the FP64 totals
+        if (lf) acc[0] += (double)s0;
+        acc[1] += (double)s1;
+        acc[2] += (double)s2;
+        // streaming stores of the new state (read again only by the next pass)
+        store(pc[f], A.dst[f], o);
+        store(pout, A.dst[2 + f], o);
       }
-      // the W sites' terms summed in storage precision, then into the FP64 totals
-      if (lf) acc[0] += (double)s0;
-      acc[1] += (double)s1;
-      acc[2] += (double)s2;
-      // streaming stores of the new state (read again only by the next pass)
-      __builtin_nontemporal_store(pc[f], reinterpret_cast<VW*>(A.dst[f] + o));
-      __builtin_nontemporal_store(pout, reinterpret_cast<VW*>(A.dst[2 + f] + o));
     }
     __syncthreads();
 #pragma unroll
@@ -235,13 +312,12 @@ __device__ __forceinline__ void scalar_rows(const ScalarArgs<T>& A, int tile, in
     plane(i, std::integral_constant<int, 0>{}, pn, qn, pf, qf);
     if (i + 1 < A.XC) plane(i + 1, std::integral_constant<int, 1>{}, pf, qf, pn, qn);
   }
-  block_partials<T, NF, false, NT>(A, acc, pidx);
+  rows_partials<NACC>(A.partials, acc, pidx);
 }
 
-// About 145 VGPRs: one 512-lane block per CU.  Holding it to 128 (two
-// blocks per CU) spills inside the plane loop and is slower.
-template <typename T, int W, int NF, int NL, int BY>
-__global__ __launch_bounds__(NL* BY) void scalar_rows_kernel(ScalarArgs<T> A) {
+// Blocks of up to 768 lanes: at 168 VGPRs or fewer twelve waves share a CU.
+template <typename T, int W, int NF, int BY>
+__global__ __launch_bounds__(kRowsMaxThreads) void scalar_rows_kernel(ScalarArgs<T> A) {
   int bid = blockIdx.x;
   if (A.swizzle) bid = (bid & 7) * (gridDim.x >> 3) + (bid >> 3);
   auto get_ab = [&](double& a_in, double& b_in) {
@@ -249,7 +325,7 @@ __global__ __launch_bounds__(NL* BY) void scalar_rows_kernel(ScalarArgs<T> A) {
       constexpr int NP = Acc<NF, false>::N;
       __shared__ double ab[2];
       double S[NP];
-      if (reduce_partials<NP, NL * BY>(A.prev.partials, 0, A.prev.nblocks, S)) {
+      if (rows_reduce_partials<NP>(A.prev.partials, 0, A.prev.nblocks, S)) {
         double an, bn;
         finish_state<T, NF, false>(A, A.prev.pd, A.st, S, blockIdx.x == 0 ? A.prev.out : nullptr, an, bn);
         ab[0] = an;
@@ -263,7 +339,7 @@ __global__ __launch_bounds__(NL* BY) void scalar_rows_kernel(ScalarArgs<T> A) {
       b_in = A.st->b;
     }
   };
-  scalar_rows<T, W, NF, NL, BY>(A, bid, blockIdx.x, get_ab);
+  scalar_rows<T, W, NF, (2 * NF * W + BY - 1) / BY, false>(A, BY, bid, blockIdx.x, get_ab);
 }
 
 }  // namespace cl

@@ -143,3 +143,36 @@ def test_chained_finish_of_each_run_is_its_own():
         assert sb["a"] == ss["a"] and sb["b"] == ss["b"] and sb["eta"] == ss["eta"], r
         S.close()
     B.close()
+
+
+@pytest.mark.parametrize("precision,width,tol", [("fp32", 4, 1e-5), ("fp64", 2, 1e-10)])
+def test_full_row_batch_tile_against_oracle(precision, width, tol):
+    """Whole z-rows per block in a batch of every size they take (a block holds
+    the whole plane at 32^3, leaves lanes idle at 96^3), each x-chunk, against
+    the oracle; a wider lattice in the batch refuses the tile."""
+    from paper_2006_15122_amd.lattice import Batch, LatticeError
+
+    cfgs = [dict(c, precision=precision) for c in _runs(sizes=(32, 96, 64, 128))]
+    states = [synth.random_state(c, seed=60 + r, amp=0.2, mom=0.2) for r, c in enumerate(cfgs)]
+    ref = []
+    for c, st in zip(cfgs, states):
+        m = oracle.scalar_model(c)
+        phi, pi = st["phi"].copy(), st["pi"].copy()
+        a, b = oracle.vv_steps(m, phi, pi, 1.0, 0.3, c["dt"], "vv2", 5, omp=True)
+        ref.append((phi, pi, a, b))
+    B = Batch(cfgs)
+    for xc in (8, 16, 32):
+        B.set_tiling(width, 256, 1, xc)
+        for r, st in enumerate(states):
+            B.runs[r].set_state(st["phi"], st["pi"], 1.0, 0.3)
+        B.step(5)
+        for run, (phi, pi, a, b) in zip(B.runs, ref):
+            s = run.get_state()
+            assert _rel(s["a"], a) < tol and _rel(s["b"], b) < tol, (xc, run.N)
+            assert np.max(np.abs(s["phi"] - phi)) < tol * np.max(np.abs(phi)), (xc, run.N)
+            assert np.max(np.abs(s["pi"] - pi)) < tol * np.max(np.abs(pi)), (xc, run.N)
+    B.close()
+    W = Batch([dict(c, precision=precision) for c in _runs(sizes=(32, 160))])
+    with pytest.raises(LatticeError):
+        W.set_tiling(width, 256, 1, 8)
+    W.close()
