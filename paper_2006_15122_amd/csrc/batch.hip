@@ -108,7 +108,7 @@ __global__ __launch_bounds__(kBatchRowLanes) void batch_rows_kernel(
   const int first = tile_offset[r], nrec = tile_offset[r + 1] - first;
   DevState* const out = slots[2 * r + (rd ^ 1)];
   // (at most two halo sites per lane up to N = 128)
-  scalar_rows<T, W, NF, NF, true>(A, batch_rows(A.N, W), local, b, [&](double& a_in, double& b_in) {
+  scalar_rows<T, W, NF, NF, true, kRowsStep>(A, batch_rows(A.N, W), local, b, [&](double& a_in, double& b_in) {
     if (prev.partials) {
       constexpr int NP = Acc<NF, false>::N;
       __shared__ double ab[2];

@@ -8,7 +8,9 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <algorithm>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "common.hpp"
@@ -72,12 +74,32 @@ __device__ __forceinline__ Cx<R> twiddle(const Cx<double>* __restrict__ W, int q
   return Cx<R>{(R)w.x, (R)(sg * w.y)};
 }
 
-// Length-RAD DFT o[m] = sum_r v[r] e^{sgn 2 pi i r m / RAD}; radices 2 and 4
-// in closed form, others with roots from the table (index r m N/RAD mod N).
-template <typename R, int RAD, bool PAD = false>
-__device__ __forceinline__ void small_dft(const Cx<R>* v, Cx<R>* o, const Cx<double>* __restrict__ W, int N,
-                                          double sg) {
-  if constexpr (RAD == 2) {
+// Length-RAD DFT o[m] = sum_r v[r] e^{sgn 2 pi i r m / RAD}, RAD <= 5 or 8, in
+// closed form: for the odd radices the inputs are paired as v[r] +- v[RAD-r],
+// whose cosine and sine parts are real multiples.
+template <typename R, int RAD>
+__device__ __forceinline__ void small_dft(const Cx<R>* v, Cx<R>* o, double sg) {
+  if constexpr (RAD == 3) {
+    const R s = (R)sg * (R)0.86602540378443864676372317075293618;  // sin(2 pi/3)
+    const Cx<R> p{v[1].x + v[2].x, v[1].y + v[2].y}, q{v[1].x - v[2].x, v[1].y - v[2].y};
+    const Cx<R> c{v[0].x - R(0.5) * p.x, v[0].y - R(0.5) * p.y};
+    o[0] = Cx<R>{v[0].x + p.x, v[0].y + p.y};
+    o[1] = Cx<R>{c.x - s * q.y, c.y + s * q.x};
+    o[2] = Cx<R>{c.x + s * q.y, c.y - s * q.x};
+  } else if constexpr (RAD == 5) {
+    const R c1 = (R)0.30901699437494742410229341718281906, c2 = (R)-0.80901699437494742410229341718281906;
+    const R s1 = (R)sg * (R)0.95105651629515357211643933337938214, s2 = (R)sg * (R)0.58778525229247312916870595463907277;
+    const Cx<R> p{v[1].x + v[4].x, v[1].y + v[4].y}, q{v[1].x - v[4].x, v[1].y - v[4].y};
+    const Cx<R> t{v[2].x + v[3].x, v[2].y + v[3].y}, u{v[2].x - v[3].x, v[2].y - v[3].y};
+    const Cx<R> a{v[0].x + c1 * p.x + c2 * t.x, v[0].y + c1 * p.y + c2 * t.y};
+    const Cx<R> b{v[0].x + c2 * p.x + c1 * t.x, v[0].y + c2 * p.y + c1 * t.y};
+    const Cx<R> f{s1 * q.x + s2 * u.x, s1 * q.y + s2 * u.y}, g{s2 * q.x - s1 * u.x, s2 * q.y - s1 * u.y};
+    o[0] = Cx<R>{v[0].x + p.x + t.x, v[0].y + p.y + t.y};
+    o[1] = Cx<R>{a.x - f.y, a.y + f.x};
+    o[4] = Cx<R>{a.x + f.y, a.y - f.x};
+    o[2] = Cx<R>{b.x - g.y, b.y + g.x};
+    o[3] = Cx<R>{b.x + g.y, b.y - g.x};
+  } else if constexpr (RAD == 2) {
     o[0] = Cx<R>{v[0].x + v[1].x, v[0].y + v[1].y};
     o[1] = Cx<R>{v[0].x - v[1].x, v[0].y - v[1].y};
   } else if constexpr (RAD == 4) {
@@ -96,8 +118,8 @@ __device__ __forceinline__ void small_dft(const Cx<R>* v, Cx<R>* o, const Cx<dou
     const R s = (R)sg, hf = (R)0.70710678118654752440084436210484904;
     const Cx<R> ev[4] = {v[0], v[2], v[4], v[6]}, od[4] = {v[1], v[3], v[5], v[7]};
     Cx<R> a[4], b[4];
-    small_dft<R, 4>(ev, a, W, N, sg);
-    small_dft<R, 4>(od, b, W, N, sg);
+    small_dft<R, 4>(ev, a, sg);
+    small_dft<R, 4>(od, b, sg);
     b[1] = Cx<R>{hf * (b[1].x - s * b[1].y), hf * (b[1].y + s * b[1].x)};
     b[2] = Cx<R>{-s * b[2].y, s * b[2].x};
     b[3] = Cx<R>{-hf * (b[3].x + s * b[3].y), hf * (s * b[3].x - b[3].y)};
@@ -107,17 +129,7 @@ __device__ __forceinline__ void small_dft(const Cx<R>* v, Cx<R>* o, const Cx<dou
       o[m + 4] = Cx<R>{a[m].x - b[m].x, a[m].y - b[m].y};
     }
   } else {
-#pragma unroll
-    for (int m = 0; m < RAD; ++m) {
-      double sx = (double)v[0].x, sy = (double)v[0].y;
-#pragma unroll
-      for (int r = 1; r < RAD; ++r) {
-        const Cx<R> w = twiddle<R, PAD>(W, ((r * m) % RAD) * (N / RAD), sg);
-        sx += (double)v[r].x * (double)w.x - (double)v[r].y * (double)w.y;
-        sy += (double)v[r].x * (double)w.y + (double)v[r].y * (double)w.x;
-      }
-      o[m] = Cx<R>{(R)sx, (R)sy};
-    }
+    static_assert(RAD == 8, "radix in closed form");
   }
 }
 
@@ -137,7 +149,7 @@ __device__ __forceinline__ void fft_stage(const Cx<R>* in, Cx<R>* out, const Cx<
       if (r > 0 && k > 0) x = cmul(x, twiddle<R>(W, k * r * stride, sg));
       v[r] = x;
     }
-    small_dft<R, RAD>(v, o, W, N, sg);
+    small_dft<R, RAD>(v, o, sg);
     const int idxD = (j / Ns) * Ns * RAD + k;
 #pragma unroll
     for (int r = 0; r < RAD; ++r) out[b * N + idxD + r * Ns] = o[r];
@@ -172,18 +184,24 @@ __device__ void fft_stage_any(const Cx<R>* in, Cx<R>* out, const Cx<double>* __r
   }
 }
 
-// Quotient and remainder by d; P2: d is a power of two (shift and mask
-// instead of an integer division).
+// Division by a run-time number without the integer division's instruction
+// sequence: a shift where it is a power of two (P2), else a product with its
+// reciprocal.  x + 1/2 is at least 1/(2d) away from a multiple of d in units of
+// d, and the reciprocal and the product are each within 2^-23 of exact, so the
+// quotient is exact for x below 2^20 (elements of a batch, batches of a pass).
 template <bool P2>
-__device__ __forceinline__ int idiv(int x, int d) {
-  if constexpr (P2) return x >> __builtin_ctz((unsigned)d);
-  else return x / d;
-}
-template <bool P2>
-__device__ __forceinline__ int imod(int x, int d) {
-  if constexpr (P2) return x & (d - 1);
-  else return x % d;
-}
+struct Div {
+  int d;
+  float inv;
+  __device__ __forceinline__ explicit Div(int d_) : d(d_), inv(0.f) {
+    if constexpr (!P2) inv = __builtin_amdgcn_rcpf((float)d_);
+  }
+  __device__ __forceinline__ int quo(int x) const {
+    if constexpr (P2) return x >> __builtin_ctz((unsigned)d);
+    else return (int)(((float)x + 0.5f) * inv);
+  }
+  __device__ __forceinline__ int rem(int x, int q) const { return x - q * d; }
+};
 
 // LDS position of element x of line b in the single-buffer kernel: one
 // complex of padding after every 16 and lines lane_stride(N) apart.  A 16-byte
@@ -207,14 +225,15 @@ template <typename R, int RAD, int PMAX, bool P2 = false>
 __device__ __forceinline__ void fft_stage_inplace(Cx<R>* buf, const Cx<double>* Wl, int N, int B, int LS, int Ns,
                                                   double sg) {
   const int M = N / RAD;
-  const int stride = N / (Ns * RAD);
+  const int stride = Div<P2>(Ns).quo(M);
   const int nbf = B * M;
+  const Div<P2> dM(M), dNs(Ns);
   Cx<R> v[PMAX][RAD];
 #pragma unroll
   for (int p = 0; p < PMAX; ++p) {
     const int t = threadIdx.x + p * blockDim.x;
     if (t < nbf) {
-      const int b = idiv<P2>(t, M), j = t - b * M, k = imod<P2>(j, Ns);
+      const int b = dM.quo(t), j = dM.rem(t, b), k = dNs.rem(j, dNs.quo(j));
 #pragma unroll
       for (int r = 0; r < RAD; ++r) {
         Cx<R> x = buf[lpos(b, j + r * M, LS)];
@@ -228,10 +247,10 @@ __device__ __forceinline__ void fft_stage_inplace(Cx<R>* buf, const Cx<double>* 
   for (int p = 0; p < PMAX; ++p) {
     const int t = threadIdx.x + p * blockDim.x;
     if (t < nbf) {
-      const int b = idiv<P2>(t, M), j = t - b * M, k = imod<P2>(j, Ns);
+      const int b = dM.quo(t), j = dM.rem(t, b), jn = dNs.quo(j), k = dNs.rem(j, jn);
       Cx<R> o[RAD];
-      small_dft<R, RAD, true>(v[p], o, Wl, N, sg);
-      const int idxD = idiv<P2>(j, Ns) * Ns * RAD + k;
+      small_dft<R, RAD>(v[p], o, sg);
+      const int idxD = jn * Ns * RAD + k;
 #pragma unroll
       for (int r = 0; r < RAD; ++r) buf[lpos(b, idxD + r * Ns, LS)] = o[r];
     }
@@ -239,8 +258,14 @@ __device__ __forceinline__ void fft_stage_inplace(Cx<R>* buf, const Cx<double>* 
   __syncthreads();
 }
 
-// Butterflies per thread the in-place stages hold in registers, by radix.
-__host__ __device__ constexpr int inplace_pmax(int rad) { return rad == 2 ? 4 : rad == 3 ? 3 : rad == 8 ? 1 : 2; }
+// Butterflies per thread the in-place stages hold in registers, by radix, in
+// blocks of at most 256 threads (512 on the y pass) for powers of two and of a
+// thread per four elements (up to 512) for other sizes, whose odd radices need
+// the registers (sizes with a factor 3: 72 VGPRs against 106 with three radix-3
+// butterflies and two radix-4 ones).
+__host__ __device__ constexpr int inplace_pmax(int rad, bool p2) {
+  return p2 ? (rad == 2 ? 4 : rad == 8 ? 1 : 2) : rad <= 3 ? 2 : 1;
+}
 
 // radices the in-place kernel and the two-buffer kernel without the generic
 // stage take (8: the binning pass's in-place kernel only)
@@ -257,18 +282,33 @@ __device__ __forceinline__ int shell_of(int64_t n2s) {
   return b;
 }
 
-// Input and output of a line pass: the plain pass reads and writes the
-// complex array; the first (z) pass of a power spectrum reads the real field
-// in storage precision instead, and its last (x) pass adds |f(n~)|^2 to
-// per-block shell histograms instead of storing the transform.
+// Input and output of a line pass.  The plain pass reads and writes the
+// complex array, rows of nz elements along z (N, or N/2 inside a power
+// spectrum).  A power spectrum's field is real, so its transform needs half
+// the modes along z only:
+// - its first (z) pass reads the real field in storage precision, two
+//   neighbouring z-lines as the real and imaginary parts of one complex line,
+//   and stores the modes 0 .. N/2 - 1 of each: with C the transform of
+//   a + i b, A(k) = (C(k) + C*(N-k))/2 and B(k) = (C(k) - C*(N-k))/2i.  The
+//   modes 0 and N/2 of a real line are real; they share element 0 as its real
+//   and imaginary parts.
+// - its last (x) pass adds |f(n~)|^2 to per-block shell histograms instead of
+//   storing the transform, twice for the modes n3 > 0 that stand for -n3 as
+//   well.  The lines of element 0 hold G = F_0 + i F_{N/2}, and
+//   F_0(k) = (G(k) + G*(-k))/2, F_{N/2}(k) = (G(k) - G*(-k))/2i, so a batch is
+//   half its lines at n2 and the other half at -n2 (0 and N/2 together).
 enum LineMode { kLinePlain = 0, kLineRealIn = 1, kLineBinOut = 2 };
 struct LineIO {
   const void* rin;  // kLineRealIn: the real field
   double* pS;       // kLineBinOut: nbins sums per block
   int nbins;
   int per_block;    // kLineBinOut: line batches per block
+  int nz;           // row length along z
 };
 
+// Measured per spectrum, host call included: 256^3 198 us (transform of all
+// modes: 380), 384^3 0.89 ms (2.4), 320^3 0.70 ms (1.5), 96^3 62 us (105).
+//
 // Launch shape of the line passes, measured at 256^3 (a pass is held by the
 // latency of its loads and LDS stages, not by HBM bandwidth):
 // - a thread loads LU of its batch elements before it writes them to LDS:
@@ -288,19 +328,27 @@ constexpr int kThreadsY = 512;
 
 // Sizes whose factors are all 2, 3, 4 or 5: one LDS buffer of B lines plus
 // the N roots of unity, so that more blocks fit on a compute unit.
-template <typename R, bool POW2, int MODE = kLinePlain, typename TIN = float, int LU = 1>
+// FAC: the factors of N are 2 and 4 only (kFac2), with 3 (kFac3), with 5
+// (kFac5): a kernel holds no wider radix's registers than its sizes need (71,
+// 72 and 88 VGPRs against 158 with one kernel for all that are not powers of two).
+enum LineFactors { kFac2 = 0, kFac3 = 1, kFac5 = 2 };
+template <typename R, int FAC, int MODE = kLinePlain, typename TIN = float, int LU = 1>
 __global__ __launch_bounds__(512) void fft_lines_inplace_kernel(Cx<R>* data, const Cx<double>* __restrict__ W,
                                                                  FFTPlan P, int axis, int B, double sgn,
                                                                  double scale, LineIO io) {
   extern __shared__ unsigned char smem_raw[];
+  constexpr bool POW2 = FAC == kFac2;
   const int N = P.N;
   Cx<double>* Wl = reinterpret_cast<Cx<double>*>(smem_raw);
   const int LS = lane_stride(N, axis != 2 && MODE != kLineBinOut);
   Cx<R>* buf = reinterpret_cast<Cx<R>*>(Wl + lane_stride(N));  // the padded root table
   double* hist = reinterpret_cast<double*>(buf + (size_t)B * LS);  // kLineBinOut
-  const size_t NN = (size_t)N * N;
+  const int nz = io.nz;
+  const size_t NN = (size_t)N * nz;
   const int tid = threadIdx.x, NT = blockDim.x;
-  const int nzb = idiv<POW2>(N, B);
+  // z columns of a batch, and batches along z (a binning batch has two lines per column)
+  const int Bz = MODE == kLineBinOut ? B >> 1 : B;
+  const Div<POW2> dN(N), dB(B), dnzb(Div<POW2>(Bz).quo(nz));
   // Blocks are dealt to the XCDs in turn; on the strided axes give each XCD
   // a contiguous range of batches instead, so that the row segments of
   // neighbouring batches (B elements each, under a cache line in FP32) are
@@ -315,11 +363,19 @@ __global__ __launch_bounds__(512) void fft_lines_inplace_kernel(Cx<R>* data, con
   }
   for (int m = tid; m < N; m += NT) Wl[m + (m >> 4)] = W[m];
   for (int lb = lb0; lb < lb1; ++lb) {
-    const int o = idiv<POW2>(lb, nzb), z0 = imod<POW2>(lb, nzb) * B;
+    const int o = dnzb.quo(lb), z0 = dnzb.rem(lb, o) * Bz;
+    const int o2 = o == 0 ? N >> 1 : N - o;  // kLineBinOut: the n2 of the second half of the lines
     auto addr = [&](int b, int i) -> size_t {
       if (axis == 2) return ((size_t)lb * B + b) * N + i;
-      if (axis == 1) return (size_t)o * NN + (size_t)i * N + z0 + b;
-      return (size_t)i * NN + (size_t)o * N + z0 + b;
+      if (axis == 1) return (size_t)o * NN + (size_t)i * nz + z0 + b;
+      if constexpr (MODE == kLineBinOut)
+        return (size_t)i * NN + (size_t)(b < Bz ? o : o2) * nz + z0 + (b < Bz ? b : b - Bz);
+      return (size_t)i * NN + (size_t)o * nz + z0 + b;
+    };
+    // element e of a batch: line b, place i (neighbouring threads on
+    // neighbouring elements of memory)
+    auto split = [&](int e, int& b, int& i) {
+      if (axis == 2) { b = dN.quo(e); i = dN.rem(e, b); } else { i = dB.quo(e); b = dB.rem(e, i); }
     };
     if (lb != lb0) __syncthreads();  // every thread is done with the previous batch
     // LU of a thread's elements are loaded before the first of them goes to LDS
@@ -330,10 +386,11 @@ __global__ __launch_bounds__(512) void fft_lines_inplace_kernel(Cx<R>* data, con
         const int e = e0 + k * NT;
         if (e < B * N) {
           int b, i;
-          if (axis == 2) { b = idiv<POW2>(e, N); i = imod<POW2>(e, N); } else { i = idiv<POW2>(e, B); b = imod<POW2>(e, B); }
-          if constexpr (MODE == kLineRealIn)
-            in[k] = Cx<R>{(R) static_cast<const TIN*>(io.rin)[addr(b, i)], R(0)};
-          else
+          split(e, b, i);
+          if constexpr (MODE == kLineRealIn) {
+            const TIN* f = static_cast<const TIN*>(io.rin) + 2 * ((size_t)lb * B + b) * N + i;
+            in[k] = Cx<R>{(R)f[0], (R)f[N]};
+          } else
             in[k] = data[addr(b, i)];
         }
       }
@@ -342,7 +399,7 @@ __global__ __launch_bounds__(512) void fft_lines_inplace_kernel(Cx<R>* data, con
         const int e = e0 + k * NT;
         if (e < B * N) {
           int b, i;
-          if (axis == 2) { b = idiv<POW2>(e, N); i = imod<POW2>(e, N); } else { i = idiv<POW2>(e, B); b = imod<POW2>(e, B); }
+          split(e, b, i);
           buf[lpos(b, i, LS)] = in[k];
         }
       }
@@ -357,17 +414,15 @@ __global__ __launch_bounds__(512) void fft_lines_inplace_kernel(Cx<R>* data, con
       // other passes blocks per CU
       constexpr bool R8 = MODE == kLineBinOut;
       if (R8 && Rr == 8) {
-        if constexpr (R8) fft_stage_inplace<R, 8, inplace_pmax(8), POW2>(buf, Wl, N, B, LS, Ns, sg);
+        if constexpr (R8) fft_stage_inplace<R, 8, inplace_pmax(8, POW2), POW2>(buf, Wl, N, B, LS, Ns, sg);
       } else if constexpr (POW2) {  // power-of-two sizes: only radices 4 and 2 (fewer registers)
-        if (Rr == 4) fft_stage_inplace<R, 4, inplace_pmax(4), true>(buf, Wl, N, B, LS, Ns, sg);
-        else fft_stage_inplace<R, 2, inplace_pmax(2), true>(buf, Wl, N, B, LS, Ns, sg);
+        if (Rr == 4) fft_stage_inplace<R, 4, inplace_pmax(4, true), true>(buf, Wl, N, B, LS, Ns, sg);
+        else fft_stage_inplace<R, 2, inplace_pmax(2, true), true>(buf, Wl, N, B, LS, Ns, sg);
       } else {
-        switch (Rr) {
-          case 2: fft_stage_inplace<R, 2, inplace_pmax(2)>(buf, Wl, N, B, LS, Ns, sg); break;
-          case 3: fft_stage_inplace<R, 3, inplace_pmax(3)>(buf, Wl, N, B, LS, Ns, sg); break;
-          case 4: fft_stage_inplace<R, 4, inplace_pmax(4)>(buf, Wl, N, B, LS, Ns, sg); break;
-          default: fft_stage_inplace<R, 5, inplace_pmax(5)>(buf, Wl, N, B, LS, Ns, sg); break;
-        }
+        if (Rr == 4) fft_stage_inplace<R, 4, inplace_pmax(4, false)>(buf, Wl, N, B, LS, Ns, sg);
+        else if (Rr == 2) fft_stage_inplace<R, 2, inplace_pmax(2, false)>(buf, Wl, N, B, LS, Ns, sg);
+        else if (FAC == kFac3 || Rr == 3) fft_stage_inplace<R, 3, inplace_pmax(3, false)>(buf, Wl, N, B, LS, Ns, sg);
+        else if constexpr (FAC == kFac5) fft_stage_inplace<R, 5, inplace_pmax(5, false)>(buf, Wl, N, B, LS, Ns, sg);
       }
       Ns *= Rr;
     }
@@ -379,30 +434,70 @@ __global__ __launch_bounds__(512) void fft_lines_inplace_kernel(Cx<R>* data, con
       const int tpl = NT / B, b = tid / tpl;
       if (b < B) {
         const int run = (N + tpl - 1) / tpl, i0 = (tid - b * tpl) * run, i1 = min(N, i0 + run);
-        const int n2 = wrapk(o, N), n3 = wrapk(z0 + b, N);
-        const int64_t r23 = (int64_t)n2 * n2 + (int64_t)n3 * n3;
-        int sh = -1;
-        double acc = 0.0;
-        for (int i = i0; i < i1; ++i) {
-          const int n1 = wrapk(i, N);
-          const int64_t n2s = (int64_t)n1 * n1 + r23;
-          int s2 = sh < 0 ? shell_of(n2s) : sh;
-          while ((int64_t)(s2 + 1) * (s2 + 1) <= n2s) ++s2;
-          while ((int64_t)s2 * s2 > n2s) --s2;
-          if (s2 != sh) {
-            if (sh >= 0) atomicAdd(&hist[sh], acc);
-            sh = s2;
-            acc = 0.0;
+        const int n2 = wrapk(b < Bz ? o : o2, N), n3 = z0 + (b < Bz ? b : b - Bz);
+        const Cx<R>* line = buf + b * LS;
+        const Cx<R>* conj = buf + (o == 0 ? b : b < Bz ? b + Bz : b - Bz) * LS;  // the line of -n2
+        // sums |F|^2 of the modes (i0 .. i1 - 1, n2, m3) into their shells
+        auto walk = [&](int m3, double w, auto power) {
+          const int64_t r23 = (int64_t)n2 * n2 + (int64_t)m3 * m3;
+          int sh = -1;
+          double acc = 0.0;
+          for (int i = i0; i < i1; ++i) {
+            const int n1 = wrapk(i, N);
+            const int64_t n2s = (int64_t)n1 * n1 + r23;
+            int s2 = sh < 0 ? shell_of(n2s) : sh;
+            while ((int64_t)(s2 + 1) * (s2 + 1) <= n2s) ++s2;
+            while ((int64_t)s2 * s2 > n2s) --s2;
+            if (s2 != sh) {
+              if (sh >= 0) atomicAdd(&hist[sh], w * acc);
+              sh = s2;
+              acc = 0.0;
+            }
+            acc += power(i);
           }
-          const Cx<R> v = buf[lpos(b, i, LS)];
-          acc += (double)v.x * (double)v.x + (double)v.y * (double)v.y;
+          if (sh >= 0) atomicAdd(&hist[sh], w * acc);
+        };
+        if (n3 > 0) {
+          walk(n3, 2.0, [&](int i) {
+            const Cx<R> v = line[i + (i >> 4)];
+            return (double)v.x * (double)v.x + (double)v.y * (double)v.y;
+          });
+        } else {
+          // (1/4)|G(k) +- G*(-k)|^2
+          auto part = [&](int i, double sg2) {
+            const int q = i == 0 ? 0 : N - i;
+            const Cx<R> g = line[i + (i >> 4)], h = conj[q + (q >> 4)];
+            const double x = (double)g.x + sg2 * (double)h.x, y = (double)g.y - sg2 * (double)h.y;
+            return x * x + y * y;
+          };
+          walk(0, 0.25, [&](int i) { return part(i, 1.0); });
+          walk(N >> 1, 0.25, [&](int i) { return part(i, -1.0); });
         }
-        if (sh >= 0) atomicAdd(&hist[sh], acc);
+      }
+    } else if constexpr (MODE == kLineRealIn) {
+      // the two lines of each transform, modes 0 .. N/2 - 1
+      const int M = N >> 1;
+      const Div<POW2> dM(M);
+      for (int e = tid; e < B * M; e += NT) {
+        const int b = dM.quo(e), k = dM.rem(e, b);
+        const int q = k == 0 ? M : N - k;
+        const Cx<R> c = buf[lpos(b, k, LS)], d = buf[lpos(b, q, LS)];
+        Cx<R> u, v;
+        if (k == 0) {
+          u = Cx<R>{c.x, d.x};
+          v = Cx<R>{c.y, d.y};
+        } else {
+          u = Cx<R>{R(0.5) * (c.x + d.x), R(0.5) * (c.y - d.y)};
+          v = Cx<R>{R(0.5) * (c.y + d.y), R(0.5) * (d.x - c.x)};
+        }
+        Cx<R>* out = data + 2 * ((size_t)lb * B + b) * M + k;
+        out[0] = u;
+        out[M] = v;
       }
     } else {
       for (int e = tid; e < B * N; e += NT) {
         int b, i;
-        if (axis == 2) { b = idiv<POW2>(e, N); i = imod<POW2>(e, N); } else { i = idiv<POW2>(e, B); b = imod<POW2>(e, B); }
+        split(e, b, i);
         Cx<R> v = buf[lpos(b, i, LS)];
         v.x = (R)(v.x * scale);
         v.y = (R)(v.y * scale);
@@ -474,6 +569,16 @@ __global__ __launch_bounds__(256) void fft_lines_kernel(Cx<R>* data, const Cx<do
   }
 }
 
+// go(std::integral_constant<int, F>) with the factor class of plan P.
+template <typename Go>
+static void with_factors(const FFTPlan& P, Go go) {
+  int f = kFac2;
+  for (int k = 0; k < P.nfac; ++k) f = std::max(f, P.fac[k] == 5 ? (int)kFac5 : P.fac[k] == 3 ? (int)kFac3 : (int)kFac2);
+  if (f == kFac2) go(std::integral_constant<int, kFac2>{});
+  else if (f == kFac3) go(std::integral_constant<int, kFac3>{});
+  else go(std::integral_constant<int, kFac5>{});
+}
+
 // Three line passes (z, y, x).  Lines per block B: the most that fit (one
 // buffer of at most 2048 elements plus the roots for the in-place kernel,
 // two buffers within 64 KiB for the generic one), at most kLinesZ along z,
@@ -493,40 +598,37 @@ static int fft3d(Cx<R>* data, const Cx<double>* W, int N, double sgn, double sca
   else
     while (Bmax > 1 && Bmax * N > 2048) Bmax >>= 1;
   while (Bmax > 1 && N % Bmax) Bmax >>= 1;
+  const bool p2 = (N & (N - 1)) == 0;
+  const LineIO io{nullptr, nullptr, 0, 0, N};
   for (int axis = 2; axis >= 0; --axis) {
     const int minB = axis == 2 ? 1 : std::min(Bmax, 8);
     int B = axis == 2 ? std::min(Bmax, kLinesZ) : Bmax;
     while (B > minB && (size_t)N * N / B < 2048) B >>= 1;
     const int nblk = (int)((size_t)N * N / B);
     // (the two-buffer kernel is built for 256 threads)
-    const int nt = std::min(axis == 1 && !any ? kThreadsY : 256, std::max(64, (B * N / 4 + 63) / 64 * 64));
+    const int nt = std::min(!any && (axis == 1 || !p2) ? kThreadsY : 256, std::max(64, (B * N / 4 + 63) / 64 * 64));
     const double sc = axis == 0 ? scale : 1.0;
     if (any) {
       const size_t shm = (size_t)2 * B * N * sizeof(Cx<R>);
       hipLaunchKernelGGL((fft_lines_kernel<R, true>), dim3(nblk), dim3(nt), shm, s, data, W, P, axis, B, sgn, sc);
     } else {
       for (int f = 0; f < P.nfac; ++f)
-        if ((B * N / P.fac[f] + nt - 1) / nt > inplace_pmax(P.fac[f])) {
+        if ((B * N / P.fac[f] + nt - 1) / nt > inplace_pmax(P.fac[f], p2)) {
           set_error("FFT: in-place stage does not cover the batch");
           return LAT_EINVAL;
         }
       const size_t shm =
           (size_t)lane_stride(N) * sizeof(Cx<double>) + (size_t)B * lane_stride(N, axis != 2) * sizeof(Cx<R>);
-      const bool p2 = (N & (N - 1)) == 0;
-      if (axis == 2) {
-        if (p2)
-          hipLaunchKernelGGL((fft_lines_inplace_kernel<R, true, kLinePlain, float, kLineLoadsZ>), dim3(nblk), dim3(nt),
-                             shm, s, data, W, P, axis, B, sgn, sc, LineIO{});
+      auto go = [&](auto fac) {
+        constexpr int F = decltype(fac)::value;
+        if (axis == 2)
+          hipLaunchKernelGGL((fft_lines_inplace_kernel<R, F, kLinePlain, float, kLineLoadsZ>), dim3(nblk), dim3(nt),
+                             shm, s, data, W, P, axis, B, sgn, sc, io);
         else
-          hipLaunchKernelGGL((fft_lines_inplace_kernel<R, false, kLinePlain, float, kLineLoadsZ>), dim3(nblk),
-                             dim3(nt), shm, s, data, W, P, axis, B, sgn, sc, LineIO{});
-      } else if (p2) {
-        hipLaunchKernelGGL((fft_lines_inplace_kernel<R, true>), dim3(nblk), dim3(nt), shm, s, data, W, P, axis, B,
-                           sgn, sc, LineIO{});
-      } else {
-        hipLaunchKernelGGL((fft_lines_inplace_kernel<R, false>), dim3(nblk), dim3(nt), shm, s, data, W, P, axis, B,
-                           sgn, sc, LineIO{});
-      }
+          hipLaunchKernelGGL((fft_lines_inplace_kernel<R, F>), dim3(nblk), dim3(nt), shm, s, data, W, P, axis, B, sgn,
+                             sc, io);
+      };
+      with_factors(P, go);
     }
     CL_HIP(hipGetLastError());
   }
@@ -534,9 +636,11 @@ static int fft3d(Cx<R>* data, const Cx<double>* W, int N, double sgn, double sca
 }
 
 // Forward transform of a real field (stored as TIN) for its power spectrum,
-// in precision R (FP64 roots; FP64 histograms): the z pass reads the field
-// itself (no complex copy), the x pass bins |f(n~)|^2 into nblk per-block
-// histograms pS (nbins each) instead of storing the transform.
+// in precision R (FP64 roots; FP64 histograms), of half the modes along z: the
+// z pass reads the field itself (no complex copy), the x pass bins |f(n~)|^2
+// into nblk per-block histograms pS (nbins each) instead of storing the
+// transform.  From FP32 storage that moves 36 bytes a site (4 + 8, 8 + 8, 8)
+// where the transform of all modes moved 68.
 // *nblk = 0 (nothing launched) where these passes do not apply: a radix
 // above 5, or the x pass's buffer, roots and histogram above 64 KiB of LDS.
 template <typename R, typename TIN = R>
@@ -546,21 +650,23 @@ static int fft3d_bins(const TIN* f, Cx<R>* data, const Cx<double>* W, int N, int
   const FFTPlan P = make_plan(N), P8 = make_plan(N, true);  // P8: the x (binning) pass
   for (int k = 0; k < P.nfac; ++k)
     if (!fixed_radix(P.fac[k])) return LAT_OK;
+  const bool p2 = (N & (N - 1)) == 0;
+  const int M = N / 2;  // modes along z
   int Bmax = 32;
   while (Bmax > 1 && Bmax * N > 2048) Bmax >>= 1;
-  while (Bmax > 1 && N % Bmax) Bmax >>= 1;
-  // lines per batch and threads per block of each pass, as in fft3d (an FP32
-  // batch takes half the LDS of an FP64 one, so more blocks share a CU)
+  while (Bmax > 1 && M % Bmax) Bmax >>= 1;
+  // lines per batch and threads per block of each pass, as in fft3d
   int Bs[3], nts[3];
   for (int axis = 2; axis >= 0; --axis) {
     const int minB = axis == 2 ? 1 : std::min(Bmax, 8);
     int B = axis == 2 ? std::min(Bmax, kLinesZ) : Bmax;
-    while (B > minB && (size_t)N * N / B < 2048) B >>= 1;
+    while (B > minB && (size_t)N * M / B < 2048) B >>= 1;
+    if (axis == 0) B = std::max(B, 2);
     Bs[axis] = B;
-    nts[axis] = std::min(axis == 1 ? kThreadsY : 256, std::max(64, (B * N / 4 + 63) / 64 * 64));
+    nts[axis] = std::min(axis == 1 || !p2 ? kThreadsY : 256, std::max(64, (B * N / 4 + 63) / 64 * 64));
     const FFTPlan& PL = axis == 0 ? P8 : P;
     for (int k = 0; k < PL.nfac; ++k)
-      if ((B * N / PL.fac[k] + nts[axis] - 1) / nts[axis] > inplace_pmax(PL.fac[k])) {
+      if ((B * N / PL.fac[k] + nts[axis] - 1) / nts[axis] > inplace_pmax(PL.fac[k], p2)) {
         set_error("FFT: in-place stage does not cover the batch");
         return LAT_EINVAL;
       }
@@ -571,29 +677,28 @@ static int fft3d_bins(const TIN* f, Cx<R>* data, const Cx<double>* W, int N, int
            (axis == 0 ? (size_t)nbins * sizeof(double) : 0);
   };
   if (shm_of(0) > 65536) return LAT_OK;
-  const int nbatch0 = (int)((size_t)N * N / Bs[0]);
+  const int nbatch0 = (int)((size_t)N * M / Bs[0]);
   const int per = (nbatch0 + max_blocks - 1) / max_blocks;
   const int nb_bin = (nbatch0 + per - 1) / per;
-  const LineIO io{f, pS, nbins, per};
-  const bool pow2 = (N & (N - 1)) == 0;
-#define CL_LINES(MODE, ...)                                                                                     \
-  do {                                                                                                          \
-    if (pow2)                                                                                                   \
-      hipLaunchKernelGGL((fft_lines_inplace_kernel<R, true, MODE, ##__VA_ARGS__>), dim3(grid), dim3(nts[axis]), \
-                         shm_of(axis), s, data, W, PL, axis, Bs[axis], 1.0, 1.0, io);                           \
-    else                                                                                                        \
-      hipLaunchKernelGGL((fft_lines_inplace_kernel<R, false, MODE, ##__VA_ARGS__>), dim3(grid),                  \
-                         dim3(nts[axis]), shm_of(axis), s, data, W, PL, axis, Bs[axis], 1.0, 1.0, io);          \
-  } while (0)
+  const LineIO io{f, pS, nbins, per, M};
   for (int axis = 2; axis >= 0; --axis) {
-    const int grid = axis == 0 ? nb_bin : (int)((size_t)N * N / Bs[axis]);
+    const int grid = axis == 0 ? nb_bin : (int)((size_t)N * M / Bs[axis]);
     const FFTPlan& PL = axis == 0 ? P8 : P;
-    if (axis == 2) CL_LINES(kLineRealIn, TIN, kLineLoadsZ);
-    else if (axis == 1) CL_LINES(kLinePlain);
-    else CL_LINES(kLineBinOut);
+    auto go = [&](auto fac) {
+      constexpr int F = decltype(fac)::value;
+      if (axis == 2)
+        hipLaunchKernelGGL((fft_lines_inplace_kernel<R, F, kLineRealIn, TIN, kLineLoadsZ>), dim3(grid),
+                           dim3(nts[axis]), shm_of(axis), s, data, W, PL, axis, Bs[axis], 1.0, 1.0, io);
+      else if (axis == 1)
+        hipLaunchKernelGGL((fft_lines_inplace_kernel<R, F>), dim3(grid), dim3(nts[axis]), shm_of(axis), s, data, W,
+                           PL, axis, Bs[axis], 1.0, 1.0, io);
+      else
+        hipLaunchKernelGGL((fft_lines_inplace_kernel<R, F, kLineBinOut>), dim3(grid), dim3(nts[axis]), shm_of(axis),
+                           s, data, W, PL, axis, Bs[axis], 1.0, 1.0, io);
+    };
+    with_factors(P, go);
     CL_HIP(hipGetLastError());
   }
-#undef CL_LINES
   *nblk = nb_bin;
   return LAT_OK;
 }
@@ -1106,13 +1211,19 @@ extern "C" int lattice_spectrum(lattice_t* h, int which, int nbins_cap, double* 
   Bins B;
   int rc = spectrum_bins(h, which, &B);
   if (rc) return rc;
-  std::vector<unsigned long long> hC(nb);
-  CL_HIP(hipMemcpyAsync(sum_sq, B.S, nb * 8, hipMemcpyDeviceToHost, h->stream));
-  CL_HIP(hipMemcpyAsync(k, B.K, nb * 8, hipMemcpyDeviceToHost, h->stream));
-  CL_HIP(hipMemcpyAsync(delta, B.D, nb * 8, hipMemcpyDeviceToHost, h->stream));
-  CL_HIP(hipMemcpyAsync(hC.data(), B.C, nb * 8, hipMemcpyDeviceToHost, h->stream));
+  // S, K, D, C and the two arrays of a summed spectrum lie one after the other
+  // (nb words each): one copy, then apart
+  const char* base = h->spec + (size_t)spec_blocks(h->p.N) * nb * 24;
+  std::vector<double> all((size_t)6 * nb);
+  CL_HIP(hipMemcpyAsync(all.data(), base, (size_t)48 * nb, hipMemcpyDeviceToHost, h->stream));
   CL_HIP(hipStreamSynchronize(h->stream));
-  for (int b = 0; b < nb; ++b) counts[b] = (int64_t)hC[b];
+  auto take = [&](void* dst, const void* src) {
+    std::memcpy(dst, reinterpret_cast<const char*>(all.data()) + (static_cast<const char*>(src) - base), (size_t)nb * 8);
+  };
+  take(sum_sq, B.S);
+  take(k, B.K);
+  take(delta, B.D);
+  take(counts, B.C);
   return LAT_OK;
 }
 

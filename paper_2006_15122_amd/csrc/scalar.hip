@@ -24,6 +24,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "internal.hpp"
 #include "scalar_rows.hpp"
 #include "scalar_tile.hpp"
 
@@ -55,18 +56,19 @@ hipError_t launch_shape(const ScalarArgs<T>& A, int nblocks, hipStream_t s, hipE
 }
 
 // Full-row tiles (stepping passes): tz = N, ry = 1, by y-rows per block.
-template <typename T, int W, int NF, int BY>
+template <typename T, int W, int NF, int BY, int MODE = kRowsStep>
 hipError_t launch_rows(const ScalarArgs<T>& A, int nblocks, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1,
                        DevState* fin) {
   const dim3 blk(A.N / W * BY);
   const size_t shm = rows_lds_bytes<T>(NF, A.N, BY);
   if (ev0)
-    hipExtLaunchKernelGGL((scalar_rows_kernel<T, W, NF, BY>), dim3(nblocks), blk, shm, s, ev0, ev1, 0, A);
+    hipExtLaunchKernelGGL((scalar_rows_kernel<T, W, NF, BY, MODE>), dim3(nblocks), blk, shm, s, ev0, ev1, 0, A);
   else
-    hipLaunchKernelGGL((scalar_rows_kernel<T, W, NF, BY>), dim3(nblocks), blk, shm, s, A);
+    hipLaunchKernelGGL((scalar_rows_kernel<T, W, NF, BY, MODE>), dim3(nblocks), blk, shm, s, A);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !fin) return e;
-  hipLaunchKernelGGL((scalar_finish_kernel<T, NF, false>), dim3(1), dim3(kFinishThreads), 0, s, A, nblocks, fin);
+  hipLaunchKernelGGL((scalar_finish_kernel<T, NF, MODE != kRowsStep>), dim3(1), dim3(kFinishThreads), 0, s, A, nblocks,
+                     fin);
   return hipGetLastError();
 }
 
@@ -105,18 +107,51 @@ static const Shape kShapesMain[] = {{64, 4, 2},  {64, 8, 2}, {32, 8, 2}, {128, 8
 static const Shape kShapesSmall[] = {{64, 4, 2}, {32, 8, 2}, {32, 4, 4}, {0, 4, 1}, {0, 8, 1}, {0, 16, 1}};
 static const Shape kShapesF64[] = {{64, 4, 2}, {32, 8, 2}, {32, 4, 4}, {0, 2, 1}, {0, 4, 1}, {0, 8, 1}};
 
-// Observation passes always use the 32 x 16 tile with 8 planes, which
-// divides every supported N.
+// Observation passes: the 32 x 16 general tile with 8 planes, which divides
+// every supported N, where no full-row block fits; else full rows, as many
+// planes as leave 512 blocks (256^3 FP32: 90 us on the general tile, see
+// obs_tiling).
 static const int kObsTz = 32, kObsBy = 8, kObsRy = 2, kObsXc = 8;
 
 int64_t scalar_obs_blocks(int N) {
   return (int64_t)(N / kObsTz) * (N / (kObsBy * kObsRy)) * (N / kObsXc);
 }
 
+static Tiling obs_tiling(int fp32, int nf, int N) {
+  const int ns = num_shapes(fp32, nf);
+  for (int by : {8, 4, 2})
+    for (int i = 0; i < ns; ++i) {
+      Tiling t{};
+      if (!get_shape(fp32, nf, N, i, &t.tz, &t.by, &t.ry) || t.ry != 1 || t.by != by || t.tz != N) continue;
+      // (at most 2048 records at 512^3: lattice_energies_noalloc's scratch
+      // takes them wherever it takes the general tile's)
+      for (int xc : {32, 16, 8, 4, 2}) {
+        t.xc = xc;
+        if ((int64_t)(N / by) * (N / xc) >= 512) return t;
+      }
+      return t;
+    }
+  return Tiling{kObsTz, kObsBy, kObsRy, kObsXc};
+}
+
 template <typename T, int NF>
 hipError_t launch_scalar_pass_t(const ScalarArgs<T>& A, const Shape& sh, int nblocks, hipStream_t s, bool full,
                                 hipEvent_t ev0, hipEvent_t ev1, DevState* fin) {
-  if (full) return launch_shape<T, NF, true, 32, 8, 2>(A, nblocks, s, ev0, ev1, fin);
+  if (full) {
+    if (sh.ry > 1) return launch_shape<T, NF, true, 32, 8, 2>(A, nblocks, s, ev0, ev1, fin);
+    const bool sync = A.pd.mode == MODE_VV && A.pd.wk1 == 0.0;  // no kick in E_K
+#define XF(TT, NFF, w, b) \
+  if (sh.by == b)            \
+    return sync ? launch_rows<TT, w, NFF, b, kRowsObsSync>(A, nblocks, s, ev0, ev1, fin) \
+                : launch_rows<TT, w, NFF, b, kRowsObs>(A, nblocks, s, ev0, ev1, fin);
+    if constexpr (std::is_same<T, float>::value) {
+      CL_ROWS_F32(XF, T, NF)
+    } else {
+      CL_ROWS_F64(XF, T, NF)
+    }
+#undef XF
+    return hipErrorInvalidValue;
+  }
 #define X(TT, NFF, a, b, c) \
   if (sh.tz == a && sh.by == b && sh.ry == c)  \
     return launch_shape<TT, NFF, false, a, b, c>(A, nblocks, s, ev0, ev1, fin);
@@ -164,10 +199,11 @@ hipError_t launch_scalar_pass(int fp32, int nf, const void* const* src, void* co
   if (full && (prev.partials || !fin)) return hipErrorInvalidValue;  // observation passes finish themselves
   if ((pd.write != 0) == (full != 0)) return hipErrorInvalidValue;    // stepping passes store, observations do not
   if (full) {
-    tz = kObsTz;
-    by = kObsBy;
-    ry = kObsRy;
-    xc = kObsXc;
+    const Tiling t = obs_tiling(fp32, nf, N);
+    tz = t.tz;
+    by = t.by;
+    ry = t.ry;
+    xc = t.xc;
   }
   const Shape sh{tz, by, ry};
   const int ty = by * ry;

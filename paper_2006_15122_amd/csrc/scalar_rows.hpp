@@ -103,10 +103,16 @@ __host__ __device__ constexpr size_t rows_lds_bytes(int nf, int N, int by) {
 // KH: halo sites per lane, at least 2 NF W / BY.  IDLE: the block may have more
 // lanes than the NL BY its rows take (batches of several N); the lanes beyond
 // only join the barriers and sums.
-template <typename T, int W, int NF, int KH, bool IDLE, typename GetAB>
+// MODE kRowsObs: an observation pass, which neither drifts nor stores; its
+// sums are the general tile's, each site's terms added in FP64.  kRowsObsSync:
+// the same of a synchronised state, where no part of a kick enters E_K and the
+// stencil is left out.
+enum RowsMode { kRowsStep = 0, kRowsObs = 1, kRowsObsSync = 2 };
+template <typename T, int W, int NF, int KH, bool IDLE, int MODE, typename GetAB>
 __device__ __forceinline__ void scalar_rows(const ScalarArgs<T>& A, const int BY, int tile, int pidx, GetAB get_ab) {
   using VW = typename RowVec<T, W>::type;  // W consecutive sites
-  constexpr int NACC = Acc<NF, false>::N;
+  constexpr bool FULL = MODE != kRowsStep;
+  constexpr int NACC = Acc<NF, FULL>::N;
   // drifted planes in two buffers: plane x0 + i in buffer i & 1 (x0 - 1 in
   // buffer 1), rows y0-1 .. y0+BY, each a whole z-row; the x-1 neighbours of
   // the stencil are read from the other buffer
@@ -183,7 +189,7 @@ __device__ __forceinline__ void scalar_rows(const ScalarArgs<T>& A, const int BY
     for (int k = 0; k < KH; ++k) {
       if (hl[k] >= 0) {
         hp[k] = load_g(hsrc[k], (size_t)x * NN);
-        hq[k] = load_g(hsrq[k], (size_t)x * NN);
+        if constexpr (!FULL) hq[k] = load_g(hsrq[k], (size_t)x * NN);
       }
     }
   };
@@ -204,6 +210,7 @@ __device__ __forceinline__ void scalar_rows(const ScalarArgs<T>& A, const int BY
   const Coef<T> clap = ucoef<T>(apow(anew, 1.0 + A.alpha) / (A.dx * A.dx));
   const Coef<T> cpot = ucoef<T>(apow(anew, 3.0 + A.alpha));
   auto drift = [&](const VW& qv, const VW& pv) {
+    if constexpr (FULL) return pv;
     VW r;
 #pragma unroll
     for (int e = 0; e < W; ++e) r[e] = fma_c(cdrift, qv[e], pv[e]);
@@ -218,7 +225,7 @@ __device__ __forceinline__ void scalar_rows(const ScalarArgs<T>& A, const int BY
     T* const row = reinterpret_cast<T*>(lds + b * bst);
 #pragma unroll
     for (int k = 0; k < KH; ++k)
-      if (hl[k] >= 0) row[hl[k]] = fma_c(cdrift, hq[k], hp[k]);
+      if (hl[k] >= 0) row[hl[k]] = FULL ? hp[k] : fma_c(cdrift, hq[k], hp[k]);
   };
   if (active) {
 #pragma unroll
@@ -245,9 +252,24 @@ __device__ __forceinline__ void scalar_rows(const ScalarArgs<T>& A, const int BY
       // plane x+1 drifted, in place
 #pragma unroll
       for (int f = 0; f < NF; ++f) pn[f] = drift(qn[f], pn[f]);
-      // the potential at the lane's W sites, summed pairwise in storage
-      // precision and added to the FP64 total once per plane
-      {
+      if constexpr (FULL) {
+        const T half = T(0.5), quarter = T(0.25);
+        const T m2_0 = (T)A.m2_0, m2_1 = (T)A.m2_1, lam = (T)A.lam, q = (T)A.q;
+#pragma unroll
+        for (int e = 0; e < W; ++e) {
+          const T p2 = pc[0][e] * pc[0][e];
+          if constexpr (NF > 1) {
+            const T c2 = pc[1][e] * pc[1][e];
+            acc[5 * NF + 0] += (double)(half * (m2_0 * p2 + m2_1 * c2));
+            acc[5 * NF + 2] += (double)(half * q * p2 * c2);
+          } else {
+            acc[5 * NF + 0] += (double)(half * m2_0 * p2);
+          }
+          acc[5 * NF + 1] += (double)(quarter * lam * p2 * p2);
+        }
+      } else {
+        // the potential at the lane's W sites, summed pairwise in storage
+        // precision and added to the FP64 total once per plane
         T v4[W];
 #pragma unroll
         for (int e = 0; e < W; ++e) {
@@ -279,24 +301,37 @@ __device__ __forceinline__ void scalar_rows(const ScalarArgs<T>& A, const int BY
           const T c = cur[f];
           const T zp = e == W - 1 ? zhi : pc[f][e + 1];
           const T zm = e == 0 ? zlo : pc[f][e - 1];
-          // the general tile's Laplacian, term for term
-          const T lap = ((xm4[e] - c) + (pn[f][e] - c)) + ((yp[e] - c) + (ym[e] - c)) + ((zp - c) + (zm - c));
-          const T K = fma_c(clap, lap, -mul_c(cpot, dpot<T, NF>(f, cur, m2_0c, m2_1c, lamc, qc_)));
           const T pin = qc[f][e];
-          pout[e] = fma_c(ckick, K, pin);
-          const T pe = fma_c(cE, K, pin);
+          T pe = pin;
+          if constexpr (MODE != kRowsObsSync) {
+            // the general tile's Laplacian, term for term
+            const T lap = ((xm4[e] - c) + (pn[f][e] - c)) + ((yp[e] - c) + (ym[e] - c)) + ((zp - c) + (zm - c));
+            const T K = fma_c(clap, lap, -mul_c(cpot, dpot<T, NF>(f, cur, m2_0c, m2_1c, lamc, qc_)));
+            pout[e] = fma_c(ckick, K, pin);
+            pe = fma_c(cE, K, pin);
+          }
           const T gx = pn[f][e] - c, gy = yp[e] - c, gz = zp - c;
-          s0 = fma_t(pin, pin, s0);
-          s1 = fma_t(pe, pe, s1);
-          s2 += gx * gx + gy * gy + gz * gz;
+          if constexpr (FULL) {
+            acc[5 * f + 0] += (double)(pin * pin);
+            acc[5 * f + 1] += (double)(pe * pe);
+            acc[5 * f + 2] += (double)(gx * gx + gy * gy + gz * gz);
+            acc[5 * f + 3] += (double)c;
+            acc[5 * f + 4] += (double)(c * c);
+          } else {
+            s0 = fma_t(pin, pin, s0);
+            s1 = fma_t(pe, pe, s1);
+            s2 += gx * gx + gy * gy + gz * gz;
+          }
         }
-        // the W sites' terms summed in storage precision, then into the FP64 totals
-        if (lf) acc[0] += (double)s0;
-        acc[1] += (double)s1;
-        acc[2] += (double)s2;
-        // streaming stores of the new state (read again only by the next pass)
-        store(pc[f], A.dst[f], o);
-        store(pout, A.dst[2 + f], o);
+        if constexpr (!FULL) {
+          // the W sites' terms summed in storage precision, then into the FP64 totals
+          if (lf) acc[0] += (double)s0;
+          acc[1] += (double)s1;
+          acc[2] += (double)s2;
+          // streaming stores of the new state (read again only by the next pass)
+          store(pc[f], A.dst[f], o);
+          store(pout, A.dst[2 + f], o);
+        }
       }
     }
     __syncthreads();
@@ -316,7 +351,7 @@ __device__ __forceinline__ void scalar_rows(const ScalarArgs<T>& A, const int BY
 }
 
 // Blocks of up to 768 lanes: at 168 VGPRs or fewer twelve waves share a CU.
-template <typename T, int W, int NF, int BY>
+template <typename T, int W, int NF, int BY, int MODE = kRowsStep>
 __global__ __launch_bounds__(kRowsMaxThreads) void scalar_rows_kernel(ScalarArgs<T> A) {
   int bid = blockIdx.x;
   if (A.swizzle) bid = (bid & 7) * (gridDim.x >> 3) + (bid >> 3);
@@ -339,7 +374,7 @@ __global__ __launch_bounds__(kRowsMaxThreads) void scalar_rows_kernel(ScalarArgs
       b_in = A.st->b;
     }
   };
-  scalar_rows<T, W, NF, (2 * NF * W + BY - 1) / BY, false>(A, BY, bid, blockIdx.x, get_ab);
+  scalar_rows<T, W, NF, (2 * NF * W + BY - 1) / BY, false, MODE>(A, BY, bid, blockIdx.x, get_ab);
 }
 
 }  // namespace cl

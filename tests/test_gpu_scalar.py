@@ -555,6 +555,32 @@ def test_full_row_tiles_of_any_length_against_oracle(precision, nf, N, shapes):
         assert np.max(np.abs(s["pi"] - pi)) < tol * np.max(np.abs(pi)), t
 
 
+@pytest.mark.parametrize("N", [32, 96, 160])
+def test_spectrum_of_single_modes_on_the_half_volume(N):
+    """The transform keeps half the modes along z and counts the others through
+    their conjugates: single plane waves on its seams (n3 = 0 and N/2, which
+    share storage, n1 or n2 = 0 and N/2, self-conjugate corners) each put their
+    whole power, N^6/2 for a cosine and N^6 for a self-conjugate mode, into
+    their own shell."""
+    cfg = dict(synth.small(synth.config2(q=100.0), N), precision="fp64")
+    lat = _lattice(cfg)
+    h = N // 2
+    n = np.arange(N)
+    zero = np.zeros((2, N, N, N))
+    for m in ((0, 0, 0), (3, 5, 0), (0, 0, 4), (h, 0, 0), (0, h, 0), (0, 0, h), (h, h, h), (h, 0, 7), (2, h, h),
+              (-2, 4, h - 1), (5, -3, h), (1, 0, h), (0, 2, 0), (-7, h, 0)):
+        ph = 2.0 * np.pi * ((m[0] * n[:, None, None] + m[1] * n[:, None] + m[2] * n) % N) / N
+        phi = zero.copy()
+        phi[1] = np.cos(ph)
+        lat.set_state(phi, zero, 1.0, 0.5)
+        s = lat.spectrum(1)["S"]
+        sh = int(math.isqrt(sum(k * k for k in m)))
+        selfconj = all(k % h == 0 for k in m)
+        assert abs(s[sh] / (N ** 6 * (1.0 if selfconj else 0.5)) - 1.0) < 1e-12, (m, s[sh] / N ** 6)
+        assert np.sum(np.delete(s, sh)) < 1e-24 * N ** 6, m
+    lat.close()
+
+
 def test_bitwise_determinism():
     cfg = synth.small(synth.config2(q=100.0), 64)
     st = synth.random_state(cfg, seed=3)
