@@ -243,7 +243,8 @@ int lattice_destroy(lattice_t* h);
 const char* lattice_last_error(void);
 
 /* Tile shape of the fused pass: threads along z, rows of threads along y,
-   rows per thread, x-planes per block.  Scalar lattices compile (64,4,2)
+   rows per thread, x-planes per block (at most: where the blocks would leave
+   a part of the GPU idle, a pass shares the planes among more of them).  Scalar lattices compile (64,4,2)
    (64,8,2) (32,8,2) (128,8,2) (256,4,2) (128,4,2) for FP32 two fields and
    (64,4,2) (32,8,2) (32,4,4) for other storage and field counts, and for all
    of them the full-row tiles (N,by,1): a block holds by whole z-rows, four

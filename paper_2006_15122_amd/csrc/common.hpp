@@ -129,6 +129,17 @@ struct PrevPass {
   DevState* out;
 };
 
+// Element `off` bytes from a wave-uniform address: the address sits in scalar
+// registers and only the 32-bit offset in vector ones.  The address space is
+// named, so that accesses through an address the compiler cannot trace stay
+// global ones (flat ones would count against the LDS wait counter too).
+template <typename T>
+using GlobalPtr = __attribute__((address_space(1))) T*;
+template <typename T>
+__device__ __forceinline__ GlobalPtr<T> at_offset(GlobalPtr<const char> base, unsigned off) {
+  return (GlobalPtr<T>)(base + off);
+}
+
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11), device and host.
 struct Philox4 {
   uint32_t v[4];

@@ -708,34 +708,25 @@ void default_tiling(lattice* h) {
     h->tile = Tiling{0, 0, 0, 0};
     return;
   }
-  if (is_u1(h->p)) {
-    // the 64-wide tile where it divides N; the largest x-chunk that still
-    // gives 1024 blocks
-    const bool wide = h->p.precision == LAT_FP32 && N % 64 == 0;
-    Tiling t = wide ? Tiling{64, 4, 2, 4} : Tiling{32, 8, 1, 4};
-    const int64_t tiles = (int64_t)(N / t.tz) * (N / (t.by * t.ry));
-    for (int c : {16, 8})
-      if (N % c == 0 && tiles * (N / c) >= 1024) { t.xc = c; break; }
-    h->tile = t;
-    return;
-  }
-  // Below 128^3 (where no tuner runs) a pass is latency: as many blocks as the
-  // record regions take, 1024 sites each, marching as few planes as that
-  // gives.  FP64 two-field lattices take full rows (32^3, 64^3, 96^3: 9.8, 9.8
-  // and 18.9 us a pass against 12.2, 13.1 and 27.4 for the best general tile),
-  // the others the two-row tile (FP32 64^3: 9.1 us with two planes a block, 21.5
-  // with sixteen), from 512 blocks on with more planes rather than more blocks
-  // (FP32 96^3: 12.8 us with four, 14.6 with two).
-  const bool rows = h->p.precision == LAT_FP64 && h->p.nf == 2;
-  Tiling t = rows ? Tiling{N, N % 64 ? 4 : 8, 1, 1} : N % 64 == 0 ? Tiling{64, 4, 2, 1} : Tiling{32, 8, 2, 1};
-  if (rows && N == 32) t.by = 8;
+  // Below 128^3 (where no tuner runs) a pass is latency: many blocks that march
+  // few planes, down to the 1024 sites a block needs for its record, up to 512
+  // blocks (scalar FP32 64^3: 9.1 us a pass with two planes a block, 21.5 with
+  // sixteen; 96^3: 12.8 with four, 14.6 with two; U(1) 64^3: 22.9 with two,
+  // 29.4 with four; 96^3: 37.9 with eight, 46.1 with four).  FP64 two-field
+  // lattices take full rows (32^3, 64^3, 96^3: 9.8, 9.8 and 18.9 us against
+  // 12.2, 13.1 and 27.4 for the best general tile).
+  const bool rows = !is_u1(h->p) && h->p.precision == LAT_FP64 && h->p.nf == 2;
+  Tiling t;
+  if (rows) t = Tiling{N, N == 96 ? 4 : 8, 1, 1};
+  else if (N % 64 == 0 && !(is_u1(h->p) && h->p.precision == LAT_FP64)) t = Tiling{64, 4, 2, 1};
+  else t = is_u1(h->p) ? Tiling{32, 8, 1, 1} : Tiling{32, 8, 2, 1};
   const int64_t plane = (int64_t)t.tz * t.by * t.ry, tiles = (int64_t)N * N / plane;
   for (int c = 1; c <= N; ++c) {
     if (N % c) continue;
     t.xc = c;
     if (plane * c >= 1024 && (rows || tiles * (N / c) <= 512) && tiling_ok(h, t)) break;
   }
-  h->tile = tiling_ok(h, t) ? t : Tiling{32, 8, 2, 8};
+  h->tile = tiling_ok(h, t) ? t : is_u1(h->p) ? Tiling{32, 8, 1, 8} : Tiling{32, 8, 2, 8};
 }
 
 // Time every compiled tile shape and x-chunk on zeroed state buffers with

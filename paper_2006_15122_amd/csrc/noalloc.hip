@@ -59,7 +59,8 @@ static size_t energy_partial_bytes(const lattice* h) {
   if (is_u1(h->p)) {
     const Tiling& t = h->tile;
     const size_t tiles = (N / (size_t)t.tz) * (N / (size_t)(t.by * t.ry)) * (N / (size_t)t.xc);
-    return std::max(V / 256 * 4, tiles * 11) * sizeof(double);
+    // (a pass may take more blocks along x than N / xc, of 16 planes or more)
+    return std::max(V / 256 * 4, std::max(tiles, V / 4096) * 11) * sizeof(double);
   }
   return (size_t)scalar_obs_blocks(h->p.N) * (size_t)(5 * h->p.nf + 3) * sizeof(double);
 }

@@ -52,7 +52,11 @@ struct U1Args {
   DevState* st;
 };
 
-constexpr int kU1Acc = 11;
+// Sums of an observation pass: 0,1 |pi|^2 (in, e), 2 sum_i |V_i phi_{+i} - phi|^2,
+// 3 lambda|phi|^4, 4 m2|phi|^2, 5,6 pi_A^2 (in, e), 7 sum_{i<j}(1 - cos Phi_ij),
+// 8,9 phi, 10 |phi|^2.  A stepping pass keeps what the scale factor needs:
+// |pi|^2, the gradient, V, pi_A^2, 1 - cos (LF: in and out of the kick added).
+constexpr int kU1Acc = 11, kU1StepAcc = 5;
 // the workspace reserves 16 FP64 partials per 256-site block
 static_assert(kU1Acc <= 16, "U(1) partials exceed the reserved region");
 
@@ -127,14 +131,22 @@ __global__ __launch_bounds__(1024) void u1_gauss_finish_kernel(const double* par
 }
 
 // ---------------------------------------------------------------------------
-// The pass kernel.  A block owns a TY x TZ tile of the (y, z) plane and marches along x over XC
-// planes.  Each plane enters LDS already drifted (phi and the link phases,
+// The pass kernel.  A block owns a TY x TZ tile of the (y, z) plane and marches along x over its
+// share of planes.  Each plane enters LDS already drifted (phi and the link phases,
 // with a one-site ring including corners, the ring drifted redundantly); two
 // planes are held, x and x+1.  Per plane the block first computes the
 // plaquette sines S_01, S_02, S_12 of its sites and of the y-1 row and z-1
 // column, shared through LDS, so that every plaquette sine is evaluated once
 // instead of once per use.  Values of plane x-1 that the kick needs (phi,
 // theta_0, S_01, S_02 of the own column) stay in registers.
+//
+// Bound by vector instruction issue (a sine, a cosine and an arctangent per
+// link), then by memory: ten fields in, ten out.  Addresses are a
+// scalar base per component and one 32-bit offset per lane, a stepping pass
+// sums only what the scale factor needs, and the blocks share the planes so
+// that all places on the GPU are taken: FP32 192^3 160 us a pass (3.5 TB/s;
+// 196 with 64-bit lane addresses and equal blocks, 178 with equal blocks), 96^3
+// 38 us against 56, 64^3 23 against 34.
 // ---------------------------------------------------------------------------
 // One pass (as PassDesc of the scalar path, Sec. 3.3.2 merged kicks):
 //   a'  = a + wd h b,  a_mid = (a + a')/2
@@ -144,9 +156,9 @@ __global__ __launch_bounds__(1024) void u1_gauss_finish_kernel(const double* par
 // <pi_out^2> (LF), likewise for piA.
 template <typename T>
 struct U1PassArgs {
-  const T* src[10];
-  T* dst[10];
-  int N, XC, swizzle;
+  const T* src;  // component c at src + c N^3
+  T* dst;
+  int N, nx, swizzle;  // nx blocks along x
   double dx, alpha, fmp2, lam, m2, e, wf2, h;
   int expand;
   PassDesc pd;
@@ -155,11 +167,11 @@ struct U1PassArgs {
   PrevPass prev;  // finish of the previous pass of a chain (partials == nullptr: none)
 };
 
-template <typename T>
-__device__ void u1_finish_state(const U1PassArgs<T>& A, const PassDesc& pd, const DevState* in,
-                                const double (&S)[kU1Acc], DevState* out, double& a_next, double& b_next);
-template <int NT>
-__device__ bool u1_reduce_partials(const double* partials, int nb, double (&S)[kU1Acc]);
+template <typename T, bool OBS>
+__device__ void u1_finish_state(const U1PassArgs<T>& A, const PassDesc& pd, const DevState* in, const double* S,
+                                DevState* out, double& a_next, double& b_next);
+template <int NACC, int NT>
+__device__ bool u1_reduce_partials(const double* partials, int nb, double (&S)[NACC]);
 
 template <typename T>
 __device__ __forceinline__ T wrap_phase(T t) {
@@ -174,12 +186,16 @@ __device__ __forceinline__ T wrap_phase(T t) {
 // plaquette terms are the angles themselves (Phi = -e dx^2 F_ij; Phi^2/2 for
 // the magnetic energy), which turns the compact kernels into the quadratic
 // ones with the same coefficients.
-template <typename T, int TZ, int BY, int RY, bool NC>
+template <typename T, int TZ, int BY, int RY, bool NC, bool OBS>
 __global__ __launch_bounds__(TZ* BY) void u1_pass_kernel(U1PassArgs<T> A) {
   constexpr int TY = BY * RY, NT = TZ * BY, LY = TY + 2, LZ = TZ + 2;
+  constexpr int NACC = OBS ? kU1Acc : kU1StepAcc;
   constexpr int NH = 2 * LZ + 2 * TY;  // ring of the (TY+2) x (TZ+2) plane tile
   static_assert(NH <= NT, "ring larger than block");
-  static_assert(TZ + TY <= NT, "low ring larger than block");
+  // first threads of the row y0-1 and of the column z0-1, whose plaquette
+  // sines the last waves compute: the first ones have the ring to drift
+  constexpr int ROW0 = NT - TZ, COL0 = ROW0 - 64;
+  static_assert(TY <= 64 && COL0 >= 0, "low ring larger than block");
   static_assert(NT == 256, "partials and LDS sized for four waves");
   __shared__ T Lp[2][2][LY][LZ];       // drifted phi (Re, Im), planes in flight
   __shared__ T Lt[2][3][LY][LZ];       // drifted link phases (own sites are stored)
@@ -194,7 +210,7 @@ __global__ __launch_bounds__(TZ* BY) void u1_pass_kernel(U1PassArgs<T> A) {
   const int nzt = N / TZ, nyt = N / TY;
   const int z0 = (bid % nzt) * TZ;
   const int y0 = ((bid / nzt) % nyt) * TY;
-  const int x0 = (bid / (nzt * nyt)) * A.XC;
+  const int xb = bid / (nzt * nyt), x0 = x_first(N, xb, A.nx), XC = x_first(N, xb + 1, A.nx) - x0;
 
   // ring site owned by this thread (one at most)
   const bool has_ring = tid < NH;
@@ -205,25 +221,36 @@ __global__ __launch_bounds__(TZ* BY) void u1_pass_kernel(U1PassArgs<T> A) {
   else { rly = 1 + tid - 2 * LZ - TY; rlz = TZ + 1; }
   const int ry_g = (y0 - 1 + rly + N) % N, rz_g = (z0 - 1 + rlz + N) % N;
   // low-ring site whose plaquette sines this thread computes (row y0-1 or column z0-1)
-  const bool has_low = tid < TZ + TY;
-  const int sly = tid < TZ ? 0 : 1 + tid - TZ;
-  const int slz = tid < TZ ? 1 + tid : 0;
+  const bool low_row = tid >= ROW0, has_low = low_row || (tid >= COL0 && tid < COL0 + TY);
+  const int sly = low_row ? 0 : 1 + tid - COL0;
+  const int slz = low_row ? 1 + tid - ROW0 : 0;
 
-  auto site = [&](int x, int y, int z) -> int { return x * NN + y * N + z; };
+  // Byte offsets of the own column (row r: r BY rows on) and of the ring site
+  // in a plane; a component's plane through a scalar base address (the offset
+  // alone is in vector registers: formed per component, an address takes two
+  // vector instructions a load)
+  const size_t V = (size_t)NN * N;
+  const unsigned col = (unsigned)((y0 + ty) * N + z0 + tz) * (unsigned)sizeof(T);
+  const unsigned row = (unsigned)(BY * N) * (unsigned)sizeof(T);
+  const unsigned rcol = (unsigned)(ry_g * N + rz_g) * (unsigned)sizeof(T);
+  auto base = [&](const T* p, int c, int x) -> GlobalPtr<const char> {
+    GlobalPtr<const char> q = (GlobalPtr<const char>)(p + (size_t)c * V + (size_t)x * NN);
+    asm volatile("" : "+s"(q));
+    return q;
+  };
 
   // raw values: own column (RY rows) and the ring site of plane x
   T raw[10][RY], rraw[10];
   auto load_plane = [&](int x) {
 #pragma unroll
-    for (int r = 0; r < RY; ++r) {
-      const int o = site(x, y0 + r * BY + ty, z0 + tz);
+    for (int c = 0; c < 10; ++c) {
+      const GlobalPtr<const char> b = base(A.src, c, x);
 #pragma unroll
-      for (int c = 0; c < 10; ++c) raw[c][r] = A.src[c][o];
+      for (int r = 0; r < RY; ++r) raw[c][r] = *at_offset<const T>(b, col + r * row);
     }
     if (has_ring) {
-      const int o = site(x, ry_g, rz_g);
 #pragma unroll
-      for (int c = 0; c < 10; ++c) rraw[c] = A.src[c][o];
+      for (int c = 0; c < 10; ++c) rraw[c] = *at_offset<const T>(base(A.src, c, x), rcol);
     }
   };
   // plane x0-1 is loaded before the previous pass's finish is applied (the
@@ -235,10 +262,10 @@ __global__ __launch_bounds__(TZ* BY) void u1_pass_kernel(U1PassArgs<T> A) {
   double a_in, b_in;
   if (A.prev.partials) {
     __shared__ double ab[2];
-    double S[kU1Acc];
-    if (u1_reduce_partials<NT>(A.prev.partials, A.prev.nblocks, S)) {
+    double S[kU1StepAcc];
+    if (u1_reduce_partials<kU1StepAcc, NT>(A.prev.partials, A.prev.nblocks, S)) {
       double an, bn;
-      u1_finish_state<T>(A, A.prev.pd, A.st, S, blockIdx.x == 0 ? A.prev.out : nullptr, an, bn);
+      u1_finish_state<T, false>(A, A.prev.pd, A.st, S, blockIdx.x == 0 ? A.prev.out : nullptr, an, bn);
       ab[0] = an;
       ab[1] = bn;
     }
@@ -264,10 +291,18 @@ __global__ __launch_bounds__(TZ* BY) void u1_pass_kernel(U1PassArgs<T> A) {
   const Coef<T> cb = ucoef<T>(apow(anew, A.alpha - 1.0) / (A.e * A.dx * A.dx * A.dx));
   const Coef<T> ck = ucoef<T>((A.pd.wk1 + A.pd.wk2) * A.h);
   const Coef<T> cE = ucoef<T>((A.pd.mode == MODE_LF ? A.pd.wk1 + A.pd.wk2 : A.pd.wk1) * A.h);
-  const bool wr = A.pd.write != 0;
+  const bool lf = A.pd.mode == MODE_LF;
   const T lam = (T)A.lam, m2 = (T)A.m2;
   const Coef<T> lam2c = ucoef<T>(2.0 * A.lam), m2c = ucoef<T>(A.m2);
 
+  // (sin, cos - 1) of a link's phase: compact links are wrapped to one turn,
+  // the non-compact field is any number
+  auto link = [&](T th) -> C2<T> {
+    T sn, cm;
+    if constexpr (NC) sincos_m1(mul_c(mth, th), &sn, &cm);
+    else sincos_m1_near(th, &sn, &cm);
+    return C2<T>{cm, sn};
+  };
   // drift the raw values into LDS buffer b
   // (the only transcendentals of the pass: one arctangent and one sincos per link)
   auto drift_into = [&](int b) {
@@ -282,12 +317,10 @@ __global__ __launch_bounds__(TZ* BY) void u1_pass_kernel(U1PassArgs<T> A) {
         if constexpr (NC) {
           th = fma_c(cA, raw[7 + i][r], raw[4 + i][r]);  // A_i after the drift
         } else {
-          th = dr ? wrap_phase(raw[4 + i][r] - T(2) * atan_t(mul_c(cu, raw[7 + i][r]))) : raw[4 + i][r];
+          th = wrap_phase(dr ? raw[4 + i][r] - T(2) * atan_t(mul_c(cu, raw[7 + i][r])) : raw[4 + i][r]);
         }
         Lt[b][i][ly][lz] = th;
-        T sn, cm;
-        sincos_m1(NC ? mul_c(mth, th) : th, &sn, &cm);
-        Lu[b][i][ly][lz] = C2<T>{cm, sn};
+        Lu[b][i][ly][lz] = link(th);
       }
     }
     if (has_ring) {
@@ -300,11 +333,9 @@ __global__ __launch_bounds__(TZ* BY) void u1_pass_kernel(U1PassArgs<T> A) {
           th = fma_c(cA, rraw[7 + i], rraw[4 + i]);
           Lt[b][i][rly][rlz] = th;  // the plaquette angles need A on the ring
         } else {
-          th = dr ? wrap_phase(rraw[4 + i] - T(2) * atan_t(mul_c(cu, rraw[7 + i]))) : rraw[4 + i];
+          th = wrap_phase(dr ? rraw[4 + i] - T(2) * atan_t(mul_c(cu, rraw[7 + i])) : rraw[4 + i]);
         }
-        T sn, cm;
-        sincos_m1(NC ? mul_c(mth, th) : th, &sn, &cm);
-        Lu[b][i][rly][rlz] = C2<T>{cm, sn};
+        Lu[b][i][rly][rlz] = link(th);
       }
     }
   };
@@ -336,9 +367,9 @@ __global__ __launch_bounds__(TZ* BY) void u1_pass_kernel(U1PassArgs<T> A) {
     }
   };
 
-  double acc[kU1Acc];
+  double acc[NACC];
 #pragma unroll
-  for (int k = 0; k < kU1Acc; ++k) acc[k] = 0.0;
+  for (int k = 0; k < NACC; ++k) acc[k] = 0.0;
 
   // registers: plane x-1 (own column) and raw momenta of planes x, x+1
   T pm[2][RY], s01m[RY], s02m[RY];
@@ -374,13 +405,13 @@ __global__ __launch_bounds__(TZ* BY) void u1_pass_kernel(U1PassArgs<T> A) {
 #pragma unroll
     for (int c = 0; c < 5; ++c) qn[c][r] = raw[c < 2 ? 2 + c : 5 + c][r];
 
-  for (int i = 0; i < A.XC; ++i) {
+  for (int i = 0; i < XC; ++i) {
     const int x = x0 + i;
     const int cb_ = i & 1, nb_ = cb_ ^ 1;
     // plane x+2 is in flight during the compute below; the last iteration
     // re-reads plane x+1 (unused) so that the loads are unconditional and
     // the compiler need not wait for them at the first barrier
-    load_plane(i + 1 < A.XC ? (x + 2) % N : (x + 1) % N);
+    load_plane(i + 1 < XC ? (x + 2) % N : (x + 1) % N);
     __syncthreads();
     // plaquette sines of the own sites and the low ring of plane x; the
     // handful of terms a thread adds per plane are summed in T, the running
@@ -397,7 +428,7 @@ __global__ __launch_bounds__(TZ* BY) void u1_pass_kernel(U1PassArgs<T> A) {
         mg += om[k];
       }
     }
-    acc[7] += (double)mg;
+    acc[OBS ? 7 : 4] += (double)mg;
     if (has_low) {
       T sn[3], om[3];
       plaq(cb_, nb_, sly, slz, sn, om);
@@ -406,13 +437,14 @@ __global__ __launch_bounds__(TZ* BY) void u1_pass_kernel(U1PassArgs<T> A) {
     }
     __syncthreads();
     // kick of the own sites of plane x
-    T ts[kU1Acc];
-#pragma unroll
-    for (int k = 0; k < kU1Acc; ++k) ts[k] = T(0);
+    T kin = T(0), kin0 = T(0), eg = T(0), v4 = T(0), v2 = T(0), ka = T(0), ka0 = T(0), mx = T(0), my = T(0), m22 = T(0);
 #pragma unroll
     for (int r = 0; r < RY; ++r) {
       const int ly = 1 + r * BY + ty, lz = 1 + tz;
-      const int o = site(x, y0 + r * BY + ty, z0 + tz);
+      const unsigned o = col + r * row;
+      auto put = [&](int c, T v) {
+        if constexpr (!OBS) __builtin_nontemporal_store(v, at_offset<T>(base(A.dst, c, x), o));
+      };
       const C2<T> p{Lp[cb_][0][ly][lz], Lp[cb_][1][ly][lz]};
       const C2<T> fw[3] = {C2<T>{Lp[nb_][0][ly][lz], Lp[nb_][1][ly][lz]},
                            C2<T>{Lp[cb_][0][ly + 1][lz], Lp[cb_][1][ly + 1][lz]},
@@ -436,7 +468,7 @@ __global__ __launch_bounds__(TZ* BY) void u1_pass_kernel(U1PassArgs<T> A) {
         const C2<T> gb{ub1.x + (bw[k].x - p.x), ub1.y + (bw[k].y - p.y)};
         lap.x += g.x + gb.x;
         lap.y += g.y + gb.y;
-        ts[2] += g.x * g.x + g.y * g.y;
+        eg += g.x * g.x + g.y * g.y;
         Kcur[k] = mul_c(cj, p.x * g.y - p.y * g.x);
       }
       const T r2 = p.x * p.x + p.y * p.y;
@@ -450,30 +482,28 @@ __global__ __launch_bounds__(TZ* BY) void u1_pass_kernel(U1PassArgs<T> A) {
       const C2<T> pin{qc[0][r], qc[1][r]};
       const C2<T> pout{fma_c(ck, Kp.x, pin.x), fma_c(ck, Kp.y, pin.y)};
       const C2<T> pe{fma_c(cE, Kp.x, pin.x), fma_c(cE, Kp.y, pin.y)};
-      ts[0] += pin.x * pin.x + pin.y * pin.y;
-      ts[1] += pe.x * pe.x + pe.y * pe.y;
-      ts[3] += lam * r2 * r2;
-      ts[4] += m2 * r2;
-      ts[8] += p.x;
-      ts[9] += p.y;
-      ts[10] += r2;
-      if (wr) {
-        __builtin_nontemporal_store(p.x, &A.dst[0][o]);
-        __builtin_nontemporal_store(p.y, &A.dst[1][o]);
-        __builtin_nontemporal_store(pout.x, &A.dst[2][o]);
-        __builtin_nontemporal_store(pout.y, &A.dst[3][o]);
+      kin0 += pin.x * pin.x + pin.y * pin.y;
+      kin += pe.x * pe.x + pe.y * pe.y;
+      v4 += lam * r2 * r2;
+      v2 += m2 * r2;
+      if constexpr (OBS) {
+        mx += p.x;
+        my += p.y;
+        m22 += r2;
       }
+      put(0, p.x);
+      put(1, p.y);
+      put(2, pout.x);
+      put(3, pout.y);
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
         const T ain = qc[2 + k][r];
         const T KA = fma_c(cb, curl[k], Kcur[k]);
         const T aout = fma_c(ck, KA, ain), ae = fma_c(cE, KA, ain);
-        ts[5] += ain * ain;
-        ts[6] += ae * ae;
-        if (wr) {
-          __builtin_nontemporal_store(th[k], &A.dst[4 + k][o]);
-          __builtin_nontemporal_store(aout, &A.dst[7 + k][o]);
-        }
+        ka0 += ain * ain;
+        ka += ae * ae;
+        put(4 + k, th[k]);
+        put(7 + k, aout);
       }
       // plane x becomes plane x-1 of the next step
       pm[0][r] = p.x;
@@ -482,9 +512,22 @@ __global__ __launch_bounds__(TZ* BY) void u1_pass_kernel(U1PassArgs<T> A) {
       s01m[r] = S01;
       s02m[r] = S02;
     }
+    if constexpr (OBS) {
+      const T ts[kU1Acc] = {kin0, kin, eg, v4, v2, ka0, ka, T(0), mx, my, m22};
 #pragma unroll
-    for (int k = 0; k < kU1Acc; ++k)
-      if (k != 7) acc[k] += (double)ts[k];
+      for (int k = 0; k < kU1Acc; ++k)
+        if (k != 7) acc[k] += (double)ts[k];
+    } else {
+      acc[0] += (double)kin;
+      acc[1] += (double)eg;
+      acc[2] += (double)v4;
+      acc[2] += (double)v2;
+      acc[3] += (double)ka;
+      if (lf) {
+        acc[0] += (double)kin0;
+        acc[3] += (double)ka0;
+      }
+    }
 #pragma unroll
     for (int r = 0; r < RY; ++r)
 #pragma unroll
@@ -493,9 +536,9 @@ __global__ __launch_bounds__(TZ* BY) void u1_pass_kernel(U1PassArgs<T> A) {
         qn[c][r] = raw[c < 2 ? 2 + c : 5 + c][r];
       }
     __syncthreads();
-    if (i + 1 < A.XC) drift_into(cb_);  // plane x+2 replaces plane x
+    if (i + 1 < XC) drift_into(cb_);  // plane x+2 replaces plane x
   }
-  u1_block_partials<NT, kU1Acc>(acc, A.partials);
+  u1_block_partials<NT, NACC>(acc, A.partials);
 }
 
 // Energies of Sec. 5.4.1 at a' from the lattice sums S of pass `pd`, which
@@ -506,34 +549,48 @@ __global__ __launch_bounds__(TZ* BY) void u1_pass_kernel(U1PassArgs<T> A) {
 //   b_out = b + (wk1 + wk2) h K_a;  a, b, eta advanced when the pass updates.
 // The state goes to `out` (may be `in`; nullptr: not stored); a and b after
 // the pass are returned in a_next, b_next.
-template <typename T>
-__device__ void u1_finish_state(const U1PassArgs<T>& A, const PassDesc& pd, const DevState* in,
-                                const double (&S)[kU1Acc], DevState* out, double& a_next, double& b_next) {
-  constexpr int NACC = kU1Acc;
+template <typename T, bool OBS>
+__device__ void u1_finish_state(const U1PassArgs<T>& A, const PassDesc& pd, const DevState* in, const double* S,
+                                DevState* out, double& a_next, double& b_next) {
   const double V = (double)A.N * A.N * A.N;
   const double a_in = in->a, b_in = in->b, al = A.alpha;
   const double a = A.expand ? a_in + pd.wd * A.h * b_in : a_in;
   const bool lf = pd.mode == MODE_LF;
   const double a2 = a * a, a4 = a2 * a2, a6 = a4 * a2, dx2 = A.dx * A.dx;
   lattice_obs o;
-  o.EK = (lf ? 0.5 * (S[0] + S[1]) : S[1]) / V / a6;
-  o.EG = S[2] / V / (a2 * dx2);
-  o.EV_term[0] = S[4] / V;
-  o.EV_term[1] = S[3] / V;
-  o.EV_term[2] = 0.0;
-  o.EV = o.EV_term[0] + o.EV_term[1];
-  o.EK_A = A.wf2 * (lf ? 0.5 * (S[5] + S[6]) : S[6]) / V / (2.0 * a4);
-  o.EG_A = A.wf2 * S[7] / V / (a4 * dx2 * dx2 * A.e * A.e);
+  double kin, grad, kA, mA;
+  if constexpr (OBS) {
+    kin = lf ? 0.5 * (S[0] + S[1]) : S[1];
+    grad = S[2];
+    o.EV_term[0] = S[4] / V;
+    o.EV_term[1] = S[3] / V;
+    o.EV_term[2] = 0.0;
+    o.EV = o.EV_term[0] + o.EV_term[1];
+    kA = lf ? 0.5 * (S[5] + S[6]) : S[6];
+    mA = S[7];
+    o.mean_f[0] = S[8] / V;
+    o.mean_f[1] = S[9] / V;
+    o.meansq_f[0] = S[10] / V;
+    o.meansq_f[1] = 0.0;
+  } else {
+    kin = (lf ? 0.5 : 1.0) * S[0];
+    grad = S[1];
+    o.EV = S[2] / V;
+    kA = (lf ? 0.5 : 1.0) * S[3];
+    mA = S[4];
+    o.EV_term[0] = o.EV_term[1] = o.EV_term[2] = NAN;
+    o.mean_f[0] = o.mean_f[1] = o.meansq_f[0] = o.meansq_f[1] = NAN;
+  }
+  o.EK = kin / V / a6;
+  o.EG = grad / V / (a2 * dx2);
+  o.EK_A = A.wf2 * kA / V / (2.0 * a4);
+  o.EG_A = A.wf2 * mA / V / (a4 * dx2 * dx2 * A.e * A.e);
   o.EK_f[0] = o.EK;
   o.EK_f[1] = 0.0;
   o.EG_f[0] = o.EG;
   o.EG_f[1] = 0.0;
-  o.mean_f[0] = S[8] / V;
-  o.mean_f[1] = S[9] / V;
-  o.meansq_f[0] = S[10] / V;
-  o.meansq_f[1] = 0.0;
   bool bad = false;
-  for (int k = 0; k < NACC; ++k) bad = bad || !isfinite(S[k]);
+  for (int k = 0; k < (OBS ? kU1Acc : kU1StepAcc); ++k) bad = bad || !isfinite(S[k]);
   const double rho = o.EK + o.EG + o.EV + o.EK_A + o.EG_A;
   double b_out = b_in, b_sync = b_in, hc = 0.0;
   if (A.expand) {
@@ -573,15 +630,15 @@ __device__ void u1_finish_state(const U1PassArgs<T>& A, const PassDesc& pd, cons
 
 // Sums of NB partial records in block order by one block of NT threads
 // (strided per thread, then waves in order); thread 0 returns them in S.
-template <int NT>
-__device__ bool u1_reduce_partials(const double* partials, int nb, double (&S)[kU1Acc]) {
+template <int NACC, int NT>
+__device__ bool u1_reduce_partials(const double* partials, int nb, double (&S)[NACC]) {
   // Thread t < NL reads doubles t, t + NL, t + 2 NL, ... of the nb records
   // laid end to end; NL is a multiple of the record length, so the loads are
   // coalesced and every value a thread reads belongs to accumulator t mod
   // NACC (reading whole records per thread touched a cache line per lane and
   // load).  The threads of each accumulator are then summed in thread order
   // by one lane each of the first wave: a fixed order, the same in every block.
-  constexpr int NACC = kU1Acc, NL = (NT / NACC) * NACC;
+  constexpr int NL = (NT / NACC) * NACC;
   static_assert(NT >= 64 && NACC <= 64, "the first wave finishes the sums");
   __shared__ double red[NL];
   const int tid = threadIdx.x;
@@ -607,12 +664,13 @@ __device__ bool u1_reduce_partials(const double* partials, int nb, double (&S)[k
 // its FP64 sums; 1024 threads, held to 128 VGPRs, spilled them).
 constexpr int kU1FinishThreads = 256;
 
-template <typename T>
+template <typename T, bool OBS>
 __global__ __launch_bounds__(kU1FinishThreads) void u1_pass_finish(U1PassArgs<T> A, int nblocks, DevState* out) {
-  double S[kU1Acc];
-  if (!u1_reduce_partials<kU1FinishThreads>(A.partials, nblocks, S)) return;
+  constexpr int NACC = OBS ? kU1Acc : kU1StepAcc;
+  double S[NACC];
+  if (!u1_reduce_partials<NACC, kU1FinishThreads>(A.partials, nblocks, S)) return;
   double an, bn;
-  u1_finish_state<T>(A, A.pd, A.st, S, out, an, bn);
+  u1_finish_state<T, OBS>(A, A.pd, A.st, S, out, an, bn);
 }
 
 template <typename T>
@@ -650,17 +708,15 @@ static int u1_gauss_t(lattice* h) {
 template <typename T, int TZ, int BY, int RY, bool NC>
 static int u1_pass_t(lattice* h, const PassDesc& pd, PassChain* chain) {
   U1PassArgs<T> A;
-  for (int c = 0; c < 10; ++c) {
-    A.src[c] = static_cast<const T*>(h->buf[h->cur][c]);
-    A.dst[c] = static_cast<T*>(h->buf[1 - h->cur][c]);
-  }
+  A.src = static_cast<const T*>(h->buf[h->cur][0]);
+  A.dst = static_cast<T*>(h->buf[1 - h->cur][0]);
   const int N = h->p.N;
   constexpr int TY = BY * RY;
   const int tiles = (N / TZ) * (N / TY);
-  const int xc = h->tile.xc;
   A.N = N;
-  A.XC = xc;
-  const int nb = tiles * (N / xc);
+  // two blocks share a CU; a block reads two planes and computes one beyond its own
+  A.nx = x_blocks(N, h->tile.xc, tiles, 512, 2.5, 16);
+  const int nb = tiles * A.nx;
   A.swizzle = (nb % 8 == 0) ? 1 : 0;
   A.dx = h->dx;
   A.alpha = h->p.alpha;
@@ -688,21 +744,29 @@ static int u1_pass_t(lattice* h, const PassDesc& pd, PassChain* chain) {
     ev1 = h->timer[2 * h->timer_used + 1];
     ++h->timer_used;
   }
+  if (!pd.write) {
+    if (chain) { set_error("U(1) pass: an observation does not chain"); return LAT_EINVAL; }
+    hipLaunchKernelGGL((u1_pass_kernel<T, TZ, BY, RY, NC, true>), dim3(nb), dim3(TZ * BY), 0, h->stream, A);
+    CL_HIP(hipGetLastError());
+    hipLaunchKernelGGL((u1_pass_finish<T, true>), dim3(1), dim3(kU1FinishThreads), 0, h->stream, A, nb, h->st);
+    CL_HIP(hipGetLastError());
+    return LAT_OK;
+  }
   if (ev0)
-    hipExtLaunchKernelGGL((u1_pass_kernel<T, TZ, BY, RY, NC>), dim3(nb), dim3(TZ * BY), 0, h->stream, ev0, ev1, 0,
-                          A);
+    hipExtLaunchKernelGGL((u1_pass_kernel<T, TZ, BY, RY, NC, false>), dim3(nb), dim3(TZ * BY), 0, h->stream, ev0, ev1,
+                          0, A);
   else
-    hipLaunchKernelGGL((u1_pass_kernel<T, TZ, BY, RY, NC>), dim3(nb), dim3(TZ * BY), 0, h->stream, A);
+    hipLaunchKernelGGL((u1_pass_kernel<T, TZ, BY, RY, NC, false>), dim3(nb), dim3(TZ * BY), 0, h->stream, A);
   CL_HIP(hipGetLastError());
   if (chain) {
     if (A.prev.partials) chain->rd ^= 1;
     chain->prev = PrevPass{A.partials, nb, pd, nullptr};
     ++chain->k;
   } else {
-    hipLaunchKernelGGL(u1_pass_finish<T>, dim3(1), dim3(kU1FinishThreads), 0, h->stream, A, nb, h->st);
+    hipLaunchKernelGGL((u1_pass_finish<T, false>), dim3(1), dim3(kU1FinishThreads), 0, h->stream, A, nb, h->st);
     CL_HIP(hipGetLastError());
   }
-  if (pd.write) h->cur ^= 1;
+  h->cur ^= 1;
   return LAT_OK;
 }
 
@@ -724,7 +788,8 @@ static int u1_chain_finish(lattice* h, const PassChain& c) {
   A.pd = c.prev.pd;
   A.partials = const_cast<double*>(c.prev.partials);
   A.st = c.rd ? h->st2 : h->st;
-  hipLaunchKernelGGL(u1_pass_finish<T>, dim3(1), dim3(kU1FinishThreads), 0, h->stream, A, c.prev.nblocks, h->st);
+  hipLaunchKernelGGL((u1_pass_finish<T, false>), dim3(1), dim3(kU1FinishThreads), 0, h->stream, A, c.prev.nblocks,
+                     h->st);
   CL_HIP(hipGetLastError());
   return LAT_OK;
 }

@@ -372,3 +372,32 @@ def test_u1_energy_constraint_ladder_and_orders():
     assert hc[0.0025, "vv10"] < 1e-13
     # the staggered leapfrog is of the same (second) order as VV2
     assert 0.5 < hc[0.0025, "lf2"] / hc[0.0025, "vv2"] < 4.0
+
+
+@pytest.mark.parametrize("model,precision,N,tile,tol", [
+    ("u1", "fp32", 192, (64, 4, 2, 64), 2e-5), ("u1nc", "fp32", 192, (64, 4, 2, 32), 2e-5),
+    ("u1", "fp64", 96, (32, 8, 1, 32), 1e-10), ("u1nc", "fp64", 160, (32, 8, 1, 160), 1e-10),
+    ("u1", "fp32", 32, (32, 8, 1, 4), 2e-5)])
+def test_u1_blocks_share_the_planes(model, precision, N, tile, tol):
+    """A pass takes more blocks along x than N / xc where that fills the GPU
+    (27 and 28 planes a block at 192^3): every component of every site against
+    the oracle after two leapfrog steps from a rough state.  FP32: single
+    sites, a few hundred roundings of 6e-8 each."""
+    cfg = dict((synth.config3 if model == "u1" else synth.config3_noncompact)(N), precision=precision)
+    st = synth.random_u1_state(N, seed=41, amp=0.6, link_angle=3.0, emom=5.0)
+    if model == "u1nc":
+        edx = cfg["e"] * oracle.lattice_dx(N, cfg["kIR"])
+        st["links"] = np.ascontiguousarray(np.arctan2(st["links"][:, 1], st["links"][:, 0]) / edx)
+    lat = _lattice(cfg)
+    lat.set_tiling(*tile)
+    lat.set_state(st["phi"], st["pi"], 1.0, 0.5, links=st["links"], piA=st["piA"])
+    lat.step(2)
+    m = oracle.u1_model(cfg)
+    o = {k: v.copy() for k, v in st.items()}
+    o["a"], o["b"] = 1.0, 0.5
+    oracle.u1_lf_startup(m, o, cfg["dt"])
+    oracle.u1_lf_steps(m, o, cfg["dt"], 2, omp=True)
+    s = lat.get_state()
+    for key in ("phi", "pi", "links", "piA"):
+        scale = np.max(np.abs(o[key]))
+        assert np.max(np.abs(s[key] - o[key])) < tol * scale, (key, np.max(np.abs(s[key] - o[key])) / scale)
