@@ -20,6 +20,7 @@
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -207,7 +208,10 @@ hipError_t launch_scalar_pass(int fp32, int nf, const void* const* src, void* co
   }
   const Shape sh{tz, by, ry};
   const int ty = by * ry;
-  const int nblocks = (N / tz) * (N / ty) * (N / xc);
+  // full rows: 168 VGPRs let twelve waves share a CU; a block reads two planes
+  // beyond its own
+  const int nx = ry == 1 ? x_blocks(N, xc, N / ty, 256 * std::max(1, 12 / (N / (fp32 ? 4 : 2) * by / 64)), 2.0, 8) : 0;
+  const int nblocks = (N / tz) * (N / ty) * (nx ? nx : N / xc);
   if (nblocks_out) *nblocks_out = nblocks;
   const int swz = (swizzle && (nblocks % 8 == 0)) ? 1 : 0;
   auto fill = [&](auto& A, auto* tag) {
@@ -218,6 +222,7 @@ hipError_t launch_scalar_pass(int fp32, int nf, const void* const* src, void* co
     }
     A.N = N;
     A.XC = xc;
+    A.nx = nx;
     A.swizzle = swz;
     A.dx = phys[0];
     A.alpha = phys[1];

@@ -25,6 +25,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "internal.hpp"
 #include "scalar_tile.hpp"
 
 namespace cl {
@@ -126,7 +127,8 @@ __device__ __forceinline__ void scalar_rows(const ScalarArgs<T>& A, const int BY
   const int fst = (BY + 2) * NL, bst = NF * fst;  // field and buffer strides
   const int nyt = N / BY;
   const int yt = tile % nyt, xcI = tile / nyt;
-  const int y0 = yt * BY, x0 = xcI * A.XC;
+  const int nx = A.nx ? A.nx : N / A.XC;
+  const int y0 = yt * BY, x0 = x_first(N, xcI, nx), XC = x_first(N, xcI + 1, nx) - x0;
   const size_t NN = (size_t)N * N;
   const int own = (1 + ty) * NL + tz;  // this lane's place in a row buffer
   // its z-neighbours' places, in sites (periodic in the row)
@@ -242,7 +244,7 @@ __device__ __forceinline__ void scalar_rows(const ScalarArgs<T>& A, const int BY
   auto plane = [&](int i, auto bsel, VW (&pn)[NF], VW (&qn)[NF], VW (&pf)[NF], VW (&qf)[NF]) {
     constexpr int B = decltype(bsel)::value;
     const int x = x0 + i;
-    if (i + 1 < A.XC) {
+    if (i + 1 < XC) {
       load_own((x + 2) % N, pf, qf);
       load_halo((x + 1) % N);
     }
@@ -341,11 +343,11 @@ __device__ __forceinline__ void scalar_rows(const ScalarArgs<T>& A, const int BY
       qc[f] = qn[f];
     }
     // plane x+1 into the buffer of x-1, which no lane reads any more
-    if (i + 1 < A.XC) store_lds(1 - B);
+    if (i + 1 < XC) store_lds(1 - B);
   };
-  for (int i = 0; i < A.XC; i += 2) {
+  for (int i = 0; i < XC; i += 2) {
     plane(i, std::integral_constant<int, 0>{}, pn, qn, pf, qf);
-    if (i + 1 < A.XC) plane(i + 1, std::integral_constant<int, 1>{}, pf, qf, pn, qn);
+    if (i + 1 < XC) plane(i + 1, std::integral_constant<int, 1>{}, pf, qf, pn, qn);
   }
   rows_partials<NACC>(A.partials, acc, pidx);
 }

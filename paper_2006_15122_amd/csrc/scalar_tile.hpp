@@ -17,6 +17,7 @@ struct ScalarArgs {
   T* dst[4];
   int N;
   int XC;            // x-planes per block
+  int nx;            // full-row tiles: blocks along x sharing the planes (0: N / XC)
   int swizzle;       // map consecutive blocks of one XCD to neighbouring tiles
   double dx, alpha, fmp2, m2_0, m2_1, lam, q, h;
   int expand;

@@ -137,8 +137,8 @@ __device__ void su2_block_partials(double (&acc)[NACC], double* partials) {
 // ---------------------------------------------------------------------------
 // The pass kernel: drift and kick of one pass in one sweep.
 //
-// A block owns a TY x TZ tile of the (y, z) plane and marches along x over XC
-// planes.  Each plane enters LDS drifted (Phi, the U(1) phases and the SU(2)
+// A block owns a TY x TZ tile of the (y, z) plane and marches along x over its
+// share of planes.  Each plane enters LDS drifted (Phi, the U(1) phases and the SU(2)
 // links of the tile and a one-site ring with corners); planes x and x+1 are
 // held.
 //
@@ -153,19 +153,19 @@ __device__ void su2_block_partials(double (&acc)[NACC], double* partials) {
 // row y0-1 and the column z0-1 are computed by the waves without ring sites.
 //
 // Bound by its instruction stream: about 1600 VALU instructions a wave and
-// plane (45% of the issue slots at two waves per SIMD, which 252 VGPRs and
-// 79 KB of LDS per block allow).  At 128^3 in FP32 a pass takes 219 us, 64^3
-// 38 us and 192^3 700 us; a pointwise drift and a kick that read every
+// plane (45% of the issue slots at two waves per SIMD, which 251 VGPRs and
+// 79 KB of LDS per block allow).  In FP32 a pass takes 211 us at 128^3, 38 us
+// at 64^3 and 634 us at 192^3; a pointwise drift and a kick that read every
 // neighbour's links from memory took 484, 67 and 1560 us.  Ring threads in
 // waves of their own (six waves a block at 168 VGPRs) left one block on a CU
 // and spilled: 395 us.  FP64 takes half the tile so that a block's planes fit
-// (64^3: 129 us against 137, 96^3: 370 against 550).
+// (64^3: 126 us against 137, 96^3: 334 against 550).
 // ---------------------------------------------------------------------------
 template <typename T>
 struct Su2PassArgs {
   const T* src;  // component c at src + c N^3
   T* dst;
-  int N, XC, swizzle;
+  int N, nx, swizzle;  // nx blocks along x
   double dx, alpha, fmp2, lam, m2, e, g, wf2, h;
   int expand;
   PassDesc pd;
@@ -237,7 +237,8 @@ __global__ __launch_bounds__(TZ* TY, WPE) void su2_pass_kernel(Su2PassArgs<T> A)
   int bid = blockIdx.x;
   if (A.swizzle) bid = (bid & 7) * (gridDim.x >> 3) + (bid >> 3);
   const int nzt = N / TZ, nyt = N / TY;
-  const int z0 = (bid % nzt) * TZ, y0 = ((bid / nzt) % nyt) * TY, x0 = (bid / (nzt * nyt)) * A.XC;
+  const int z0 = (bid % nzt) * TZ, y0 = ((bid / nzt) % nyt) * TY, xb = bid / (nzt * nyt),
+            x0 = x_first(N, xb, A.nx), XC = x_first(N, xb + 1, A.nx) - x0;
 
   // places in the LDS tile of this thread's site and of its ring site
   const int tz = tid % TZ, ty = tid / TZ, ly = 1 + ty, lz = 1 + tz;
@@ -254,21 +255,26 @@ __global__ __launch_bounds__(TZ* TY, WPE) void su2_pass_kernel(Su2PassArgs<T> A)
   const unsigned col = column(ly, lz), rcol = has_ring ? column(rly, rlz) : 0u;
   const bool low_row = tid >= ROW0 && tid < ROW0 + TZ, low_col = tid >= COL0 && tid < COL0 + TY;
 
-  // Component c of the state through a scalar base address that steps from one
-  // component to the next and is opaque to the compiler: 70 bases kept across
-  // the loop overflow the scalar registers, and formed from the component
-  // number they become 64-bit vector arithmetic, three instructions a load.
+  // Component c of the state through an address that steps from one component
+  // to the next and is opaque to the compiler: 70 bases kept across the loop
+  // overflow the scalar registers, and formed from the component number they
+  // become 64-bit vector arithmetic, three instructions a load.  FP32 steps a
+  // scalar base; FP64, whose constants fill the scalar registers, a vector one.
   struct Walk {
-    const char* p;
+    GlobalPtr<const char> p;
     size_t st;
-    __device__ __forceinline__ Walk(const T* base, size_t V) : p(reinterpret_cast<const char*>(base)), st(V * sizeof(T)) {
-      asm volatile("" : "+s"(p));
+    __device__ __forceinline__ Walk(const T* base, size_t V) : p((GlobalPtr<const char>)base), st(V * sizeof(T)) {
+      hide();
     }
-    __device__ __forceinline__ T* next(unsigned o) {
-      const char* q = p;
+    __device__ __forceinline__ GlobalPtr<T> next(unsigned o) {
+      const GlobalPtr<const char> q = p;
       p += st;
-      asm volatile("" : "+s"(p));
-      return reinterpret_cast<T*>(const_cast<char*>(q) + o);
+      hide();
+      return at_offset<T>(q, o);
+    }
+    __device__ __forceinline__ void hide() {
+      if constexpr (sizeof(T) == 4) asm volatile("" : "+s"(p));
+      else asm volatile("" : "+v"(p));
     }
   };
   Su2Raw<T> raw, rraw;
@@ -324,19 +330,25 @@ __global__ __launch_bounds__(TZ* TY, WPE) void su2_pass_kernel(Su2PassArgs<T> A)
   // per-pass coefficients as hi + lo pairs (no coherent rounding of them)
   const double p1 = apow(amid, 1.0 - A.alpha), pl = apow(anew, 1.0 + A.alpha), pb = apow(anew, A.alpha - 1.0);
   const double dx3 = A.dx * A.dx * A.dx;
-  const Coef<T> cd = ucoef<T>(hw * apow(amid, -(3.0 - A.alpha)));
-  const Coef<T> cu = ucoef<T>(A.e * hw * A.dx / (2.0 * p1));
-  const Coef<T> cw = ucoef<T>(A.g * hw * A.dx / (4.0 * p1));
-  const Coef<T> cl = ucoef<T>(pl / (A.dx * A.dx));
-  const Coef<T> cp = ucoef<T>(apow(anew, 3.0 + A.alpha));
-  const Coef<T> cjA = ucoef<T>(pl * 2.0 * A.e / A.dx / A.wf2);
-  const Coef<T> cjB = ucoef<T>(pl * A.g / A.dx / A.wf2);
-  const Coef<T> cbA = ucoef<T>(pb / (A.e * dx3));
-  const Coef<T> cbB = ucoef<T>(pb * 2.0 / (A.g * dx3));
-  const Coef<T> ck = ucoef<T>((A.pd.wk1 + A.pd.wk2) * A.h);
-  const Coef<T> cE = ucoef<T>((A.pd.mode == MODE_LF ? A.pd.wk1 + A.pd.wk2 : A.pd.wk1) * A.h);
+  // (FP64 keeps them in vector registers, of which one wave per SIMD has plenty:
+  // in scalar ones they overflow that file)
+  auto uc = [](double v) -> Coef<T> {
+    if constexpr (sizeof(T) == 8) return coef<T>(v);
+    else return ucoef<T>(v);
+  };
+  const Coef<T> cd = uc(hw * apow(amid, -(3.0 - A.alpha)));
+  const Coef<T> cu = uc(A.e * hw * A.dx / (2.0 * p1));
+  const Coef<T> cw = uc(A.g * hw * A.dx / (4.0 * p1));
+  const Coef<T> cl = uc(pl / (A.dx * A.dx));
+  const Coef<T> cp = uc(apow(anew, 3.0 + A.alpha));
+  const Coef<T> cjA = uc(pl * 2.0 * A.e / A.dx / A.wf2);
+  const Coef<T> cjB = uc(pl * A.g / A.dx / A.wf2);
+  const Coef<T> cbA = uc(pb / (A.e * dx3));
+  const Coef<T> cbB = uc(pb * 2.0 / (A.g * dx3));
+  const Coef<T> ck = uc((A.pd.wk1 + A.pd.wk2) * A.h);
+  const Coef<T> cE = uc((A.pd.mode == MODE_LF ? A.pd.wk1 + A.pd.wk2 : A.pd.wk1) * A.h);
   const T lam = (T)A.lam, m2 = (T)A.m2;
-  const Coef<T> lam2c = ucoef<T>(2.0 * A.lam), m2c = ucoef<T>(A.m2);
+  const Coef<T> lam2c = uc(2.0 * A.lam), m2c = uc(A.m2);
   const bool lf = A.pd.mode == MODE_LF;
 
   // Drift of the raw site into LDS buffer b (Sec. 6.2.1 and 6.2.2):
@@ -444,7 +456,7 @@ __global__ __launch_bounds__(TZ* TY, WPE) void su2_pass_kernel(Su2PassArgs<T> A)
   momenta(qn);
   __syncthreads();
 
-  for (int i = 0; i < A.XC; ++i) {
+  for (int i = 0; i < XC; ++i) {
     const int x = x0 + i, c = i & 1, n = c ^ 1;
     // ---- what every site of plane x computes once
     Cx2<T> lap[2];
@@ -585,7 +597,7 @@ __global__ __launch_bounds__(TZ* TY, WPE) void su2_pass_kernel(Su2PassArgs<T> A)
     // plane x+2 is in flight during the kick (its ring after the kick's
     // registers are free); the last iteration re-reads plane x+1 (unused) so
     // that the loads are unconditional
-    const int xn = i + 1 < A.XC ? (x + 2) % N : (x + 1) % N;
+    const int xn = i + 1 < XC ? (x + 2) % N : (x + 1) % N;
     load_ring(xn);
     load_own(xn);
     __builtin_amdgcn_sched_barrier(0);
@@ -671,7 +683,7 @@ __global__ __launch_bounds__(TZ* TY, WPE) void su2_pass_kernel(Su2PassArgs<T> A)
 #pragma unroll
     for (int k = 0; k < 16; ++k) qc[k] = qn[k];
     __syncthreads();
-    if (i + 1 < A.XC) {
+    if (i + 1 < XC) {
       drift_into(c);  // plane x+2 replaces plane x
       momenta(qn);
       __syncthreads();
@@ -938,22 +950,6 @@ static void su2_pass_args(lattice* h, Su2PassArgs<T>& A, const PassDesc& pd) {
   A.st = h->st;
 }
 
-// Planes per block: every block pays about three planes' work before its
-// first (planes x0-1, x0, x0+1 and what x0-1 hands on), and the chip holds
-// `slots` blocks at once.  At least 256 sites per block, the record regions'
-// size.
-static int su2_xc(int N, int tiles, int slots, int least) {
-  int best = N;
-  double cost = 1e30;
-  for (int xc = least; xc <= N; ++xc) {
-    if (N % xc) continue;
-    const int nb = tiles * (N / xc);
-    const double c = (double)((nb + slots - 1) / slots) * (xc + 3.0);
-    if (c < cost) { cost = c; best = xc; }
-  }
-  return best;
-}
-
 // One pass of the shared schedule in one kernel; the buffers swap when it
 // writes.  Within a chain the finish is the next pass's, else a kernel of its
 // own follows.
@@ -964,8 +960,11 @@ static int su2_pass_t(lattice* h, const PassDesc& pd, PassChain* chain) {
   const int N = h->p.N;
   constexpr int NT = Su2Tile<TZ, TY>::NT;
   const int tiles = (N / TZ) * (N / TY);
-  A.XC = su2_xc(N, tiles, 256 * (4 * WPE / (NT / 64)), (256 + NT - 1) / NT);
-  const int nb = tiles * (N / A.XC);
+  // every block pays about three planes' work before its first (planes x0-1,
+  // x0, x0+1 and what x0-1 hands on); at least 256 sites per block, the record
+  // regions' size
+  A.nx = x_blocks(N, N, tiles, 256 * (4 * WPE / (NT / 64)), 3.0, (256 + NT - 1) / NT);
+  const int nb = tiles * A.nx;
   if ((int64_t)nb * 256 > (int64_t)N * N * N) { set_error("SU(2) pass: records exceed their region"); return LAT_EINVAL; }
   A.swizzle = nb % 8 == 0 ? 1 : 0;
   DevState* slot[2] = {h->st, h->st2};
