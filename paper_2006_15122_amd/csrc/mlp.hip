@@ -52,12 +52,13 @@ constexpr int LDH = WID + 8;     // LDS row pitch of the fused forward (BF16), 1
 typedef uint16_t bf16_t;
 typedef __bf16 bf16x8 __attribute__((__vector_size__(8 * sizeof(__bf16))));
 typedef float f4 __attribute__((__vector_size__(4 * sizeof(float))));
+typedef f4 f4_any __attribute__((aligned(4)));  // at any FP32 address
 
-// FP32 -> BF16, round to nearest, ties to even (finite inputs)
-__device__ __forceinline__ bf16_t to_bf16(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (bf16_t)(u >> 16);
+// FP32 -> BF16, round to nearest, ties to even (one v_cvt_pk_bf16_f32 for two)
+__device__ __forceinline__ bf16_t to_bf16(float f) { return __builtin_bit_cast(bf16_t, (__bf16)f); }
+typedef __bf16 bf16x2 __attribute__((__vector_size__(2 * sizeof(__bf16))));
+__device__ __forceinline__ uint32_t to_bf16x2(float lo, float hi) {
+  return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)lo, (__bf16)hi});
 }
 __device__ __forceinline__ float from_bf16(bf16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
@@ -103,32 +104,41 @@ struct Norm {
   float in_shift[NIN], in_scale[NIN], out_shift[NOUT], out_scale[NOUT], enc_freq[NIN];
 };
 
-// sin and cos of 2^k (p + e) for k = 0 .. K-1, where p + e is an angle held
-// as an FP32 number and its rounding error: the octave doubles both exactly,
-// and the first-order term 2^k e keeps the high octaves as accurate as the
-// low ones (the rounding of the angle would otherwise grow with 2^k).
-template <int K>
-__device__ __forceinline__ void octaves(float p, float e, float* f) {
-#pragma unroll
-  for (int k = 0; k < K; ++k, p *= 2.0f, e *= 2.0f) {
-    float s, c;
-    sincosf(p, &s, &c);
-    f[2 * k] = fmaf(e, c, s);
-    f[2 * k + 1] = fmaf(-e, s, c);
-  }
+// The first layer's inputs of a raw row (x0, x1): the normalised inputs u_c,
+// then sin and cos of 2^k enc_freq[c] u_c for the octaves of input 0, then
+// those of input 1.  One call gives one octave o (0 .. NOCT - 1) of a row; the
+// call with o = 0 also stores u_0, that with o = NFQ0 u_1.  The angle is held as
+// an FP32 number p and its rounding error e: the octave scales both exactly, and
+// the first-order term 2^k e keeps the high octaves as accurate as the low ones
+// (the rounding of the angle would otherwise grow with 2^k).
+constexpr int NOCT = NFQ0 + NFQ1;
+__device__ __forceinline__ void feature(const float* X, int o, const Norm* nm, float* f) {
+  const int c = o < NFQ0 ? 0 : 1, k = c ? o - NFQ0 : o;
+  const float u = (X[c] - nm->in_shift[c]) * nm->in_scale[c], fr = nm->enc_freq[c];
+  const float p = fr * u, q = (float)(1 << k);
+  const float e = fmaf(fr, u, -p) * q;
+  float sn, cs;
+  sincosf(p * q, &sn, &cs);
+  if (k == 0) f[c] = u;
+  f[NIN + 2 * o] = fmaf(e, cs, sn);
+  f[NIN + 2 * o + 1] = fmaf(-e, sn, cs);
 }
-
-// The first layer's inputs of one raw row (x0, x1): the normalised inputs
-// u_c, then sin and cos of 2^k enc_freq[c] u_c for the octaves of input 0,
-// then those of input 1.
-__device__ __forceinline__ void features(float x0, float x1, const Norm* nm, float* f) {
-  const float u0 = (x0 - nm->in_shift[0]) * nm->in_scale[0];
-  const float u1 = (x1 - nm->in_shift[1]) * nm->in_scale[1];
-  f[0] = u0;
-  f[1] = u1;
-  const float p0 = nm->enc_freq[0] * u0, p1 = nm->enc_freq[1] * u1;
-  octaves<NFQ0>(p0, fmaf(nm->enc_freq[0], u0, -p0), f + NIN);
-  octaves<NFQ1>(p1, fmaf(nm->enc_freq[1], u1, -p1), f + NIN + 2 * NFQ0);
+// the features of NR rows (row r at X + 2 src(r), padding rows past nvalid zero)
+// by a block of NT threads, one octave of one row per thread and turn: a row's
+// 11 octaves on one thread were a chain of 22 library calls, 8 us
+template <int NR, int NT, typename Src>
+__device__ __forceinline__ void block_features(const float* X, const Norm* nm, int t, Src src, float (*xs)[NFEAT]) {
+  static_assert(NT % NR == 0 && NIN == 2, "whole rows per turn");
+  const int r = t % NR;
+  const int64_t i = src(r);
+  for (int o = t / NR; o < NOCT; o += NT / NR) {
+    if (i >= 0) {
+      feature(X + 2 * i, o, nm, xs[r]);
+    } else {
+      if (o == 0 || o == NFQ0) xs[r][o ? 1 : 0] = 0.0f;
+      xs[r][NIN + 2 * o] = xs[r][NIN + 2 * o + 1] = 0.0f;
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -223,16 +233,10 @@ __global__ __launch_bounds__(64 * NWAVE) void step_rows_kernel(RowArgs g) {
 
   // layer 1 (K = NFEAT, plain FMA): thread t is unit t % 256 for L1R rows;
   // padding rows (past nvalid) take zero features
-  if (t < RB) {
-    const int i = r0 + t;
-    if (i < g.nvalid) {
-      const int64_t src = g.rows ? (int64_t)g.rows[i] : (int64_t)i;
-      features(g.X[2 * src], g.X[2 * src + 1], g.nm, xs[t]);
-    } else {
-#pragma unroll
-      for (int c = 0; c < NFEAT; ++c) xs[t][c] = 0.0f;
-    }
-  }
+  block_features<RB, 64 * NWAVE>(g.X, g.nm, t, [&](int r) -> int64_t {
+    const int i = r0 + r;
+    return i < g.nvalid ? (g.rows ? (int64_t)g.rows[i] : (int64_t)i) : -1;
+  }, xs);
   __syncthreads();
   {
     const int j = t & (WID - 1), rh = (t / WID) * L1R;
@@ -574,98 +578,130 @@ __global__ __launch_bounds__(256) void finish_kernel(FinishArgs f) {
 }
 
 // ---------------------------------------------------------------------------
-// fused inference: 64 query rows per block, activations stay in LDS
+// fused inference: 16 RT query rows per block of NW waves, activations stay in LDS
+//
+// Bound by vector instruction issue: a GELU is 22 instructions and two
+// transcendentals, 768 of them a row, the first layer 6144 multiply-adds a row
+// (47 of 63 us at 65536 rows; the matrix products alone would take 17).  The
+// kernel before (one thread of four forming all features of a row, one unit per
+// thread in the first layer, lanes holding one unit of four rows and storing
+// them as 16-bit words, integer rounding to BF16, two blocks a CU): 88 us.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void predict_kernel(const float* __restrict__ X, int64_t n,
-                                                      const Norm* __restrict__ nm, const bf16_t* __restrict__ W1b,
-                                                      const float* __restrict__ b1, const bf16_t* __restrict__ W2b,
-                                                      const float* __restrict__ b2, const bf16_t* __restrict__ W3b,
-                                                      const float* __restrict__ b3, const bf16_t* __restrict__ W4b,
-                                                      const float* __restrict__ b4, float* __restrict__ Y) {
-  __shared__ __align__(16) bf16_t H[64 * LDH];
-  __shared__ float xs[64][NFEAT];
+template <int RT, int NW>
+__global__ __launch_bounds__(64 * NW, NW == 16 ? 4 : 3) void predict_kernel(const float* __restrict__ X, int64_t n,
+                                                               const Norm* __restrict__ nm, WCopies c,
+                                                               const float* __restrict__ b1,
+                                                               const float* __restrict__ b2,
+                                                               const float* __restrict__ b3,
+                                                               const float* __restrict__ b4, float* __restrict__ Y) {
+  constexpr int NR = 16 * RT, NT = 64 * NW, CT = WID / 16 / NW;
+  __shared__ __align__(16) bf16_t H[NR * LDH];
+  __shared__ __align__(16) float xs[NR][NFEAT];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int r16 = lane & 15, kq = (lane >> 4) * 8;
-  const int64_t r0 = (int64_t)blockIdx.x * 64;
-  if (t < 64) {
-    const int64_t i = r0 + t;
-    if (i < n) {
-      features(X[2 * i], X[2 * i + 1], nm, xs[t]);
-    } else {
-#pragma unroll
-      for (int c = 0; c < NFEAT; ++c) xs[t][c] = 0.0f;
+  const int r16 = lane & 15, kq = (lane >> 4) * 8, uq = (lane >> 4) * 4;
+  const int64_t r0 = (int64_t)blockIdx.x * NR;
+  // each wave's priority by the block's place on its CU: four blocks in step
+  // share the vector units and then leave them idle for the matrix units (65536
+  // rows 68 us without)
+  if constexpr (NW == 4) {
+    switch ((blockIdx.x >> 8) & 3) {
+      case 1: __builtin_amdgcn_s_setprio(1); break;
+      case 2: __builtin_amdgcn_s_setprio(2); break;
+      case 3: __builtin_amdgcn_s_setprio(3); break;
     }
   }
+  block_features<NR, NT>(X, nm, t, [&](int r) -> int64_t { return r0 + r < n ? r0 + r : -1; }, xs);
   __syncthreads();
-  {
-    const int j = t;
-    float wf[NFEAT];
+  // layer 1 (K = NFEAT, plain FMA): a thread takes two neighbouring units of its
+  // share of the rows, so that a row's features, the same for all lanes, are read
+  // from LDS once for both and the result goes back as one 32-bit word
+  constexpr int G = NT / (WID / 2), RG = NR / G;
+  const int u = 2 * (t % (WID / 2)), g0 = (t / (WID / 2)) * RG;
+  float wf[2][NFEAT], bu[2];
 #pragma unroll
-    for (int c = 0; c < NFEAT; ++c) wf[c] = from_bf16(W1b[NFEAT * j + c]);
-    const float bj = b1[j];
-    for (int r = 0; r < 64; ++r) {
-      float a = bj;
+  for (int q = 0; q < 2; ++q) {
+    bu[q] = b1[u + q];
 #pragma unroll
-      for (int c = 0; c < NFEAT; ++c) a = fmaf(xs[r][c], wf[c], a);
-      H[r * LDH + j] = to_bf16(gelu(a));
+    for (int k = 0; k < NFEAT; k += 8) {
+      const bf16x8 v = load8(c.W1b + NFEAT * (u + q) + k);
+#pragma unroll
+      for (int m = 0; m < 8; ++m) wf[q][k + m] = (float)v[m];
     }
   }
+#pragma unroll 2
+  for (int r = g0; r < g0 + RG; ++r) {
+    float a0 = bu[0], a1 = bu[1];
+#pragma unroll
+    for (int k = 0; k < NFEAT; ++k) {
+      a0 = fmaf(xs[r][k], wf[0][k], a0);
+      a1 = fmaf(xs[r][k], wf[1][k], a1);
+    }
+    *reinterpret_cast<uint32_t*>(H + r * LDH + u) = to_bf16x2(gelu(a0), gelu(a1));
+  }
   __syncthreads();
-  // hidden layers 2 and 3: wave w owns columns 64w .. 64w+63 of all 64 rows
+  // hidden layers 2 and 3: wave w owns units 16 CT w .. 16 CT (w + 1) - 1 of all
+  // rows.  The weights are the first operand, so a lane receives four
+  // neighbouring units of one row.
+#pragma unroll 1
   for (int layer = 0; layer < 2; ++layer) {
-    const bf16_t* W = layer ? W3b : W2b;
+    const bf16_t* W = layer ? c.W3b : c.W2b;
     const float* bias = layer ? b3 : b2;
-    f4 acc[4][4];
+    f4 acc[RT][CT];
 #pragma unroll
-    for (int rt = 0; rt < 4; ++rt)
+    for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-      for (int ct = 0; ct < 4; ++ct) acc[rt][ct] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-    const bf16_t* wb = W + (size_t)(64 * w + r16) * WID + kq;
-#pragma unroll 2
+      for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+    const bf16_t* wb = W + (size_t)(16 * CT * w + r16) * WID + kq;
+#pragma unroll CT == 1 ? 8 : 2
     for (int kk = 0; kk < WID; kk += 32) {
-      bf16x8 a[4], b[4];
+      bf16x8 a[RT], b[CT];
 #pragma unroll
-      for (int ct = 0; ct < 4; ++ct) b[ct] = load8(wb + (size_t)ct * 16 * WID + kk);
+      for (int ct = 0; ct < CT; ++ct) b[ct] = load8(wb + (size_t)ct * 16 * WID + kk);
 #pragma unroll
-      for (int rt = 0; rt < 4; ++rt) a[rt] = load8(&H[(rt * 16 + r16) * LDH + kk + kq]);
+      for (int rt = 0; rt < RT; ++rt) a[rt] = load8(&H[(rt * 16 + r16) * LDH + kk + kq]);
 #pragma unroll
-      for (int rt = 0; rt < 4; ++rt)
+      for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-        for (int ct = 0; ct < 4; ++ct) acc[rt][ct] = mma(a[rt], b[ct], acc[rt][ct]);
+        for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = mma(b[ct], a[rt], acc[rt][ct]);
     }
     __syncthreads();
 #pragma unroll
-    for (int ct = 0; ct < 4; ++ct) {
-      const int j = 64 * w + ct * 16 + r16;
-      const float bj = bias[j];
+    for (int ct = 0; ct < CT; ++ct) {
+      const int j = 16 * (CT * w + ct) + uq;
+      const f4 bj = *reinterpret_cast<const f4*>(bias + j);
 #pragma unroll
-      for (int rt = 0; rt < 4; ++rt)
+      for (int rt = 0; rt < RT; ++rt) {
+        float v[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          H[(rt * 16 + (lane >> 4) * 4 + e) * LDH + j] = to_bf16(gelu(acc[rt][ct][e] + bj));
+        for (int e = 0; e < 4; ++e) v[e] = gelu(acc[rt][ct][e] + bj[e]);
+        *reinterpret_cast<uint2*>(H + (rt * 16 + r16) * LDH + j) = uint2{to_bf16x2(v[0], v[1]), to_bf16x2(v[2], v[3])};
+      }
     }
     __syncthreads();
   }
-  // output layer: wave w owns columns 16w .. 16w+15
-  f4 acc[4];
+  // output layer: wave w owns outputs 16w .. 16w+15
+  if (w >= NOUT / 16) return;
+  f4 acc[RT];
 #pragma unroll
-  for (int rt = 0; rt < 4; ++rt) acc[rt] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-  const bf16_t* wb = W4b + (size_t)(16 * w + r16) * WID + kq;
-#pragma unroll 2
+  for (int rt = 0; rt < RT; ++rt) acc[rt] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+  const bf16_t* wb = c.W4b + (size_t)(16 * w + r16) * WID + kq;
+#pragma unroll CT == 1 ? 8 : 2
   for (int kk = 0; kk < WID; kk += 32) {
     const bf16x8 b = load8(wb + kk);
 #pragma unroll
-    for (int rt = 0; rt < 4; ++rt) acc[rt] = mma(load8(&H[(rt * 16 + r16) * LDH + kk + kq]), b, acc[rt]);
+    for (int rt = 0; rt < RT; ++rt) acc[rt] = mma(b, load8(&H[(rt * 16 + r16) * LDH + kk + kq]), acc[rt]);
   }
-  const int j = 16 * w + r16;
-  const float bj = b4[j], sh = nm->out_shift[j], sc = nm->out_scale[j];
+  const int j = 16 * w + uq;
+  const f4 bj = *reinterpret_cast<const f4*>(b4 + j);
 #pragma unroll
-  for (int rt = 0; rt < 4; ++rt)
+  for (int rt = 0; rt < RT; ++rt) {
+    const int64_t i = r0 + rt * 16 + r16;
+    if (i >= n) continue;
+    f4 y;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int64_t i = r0 + rt * 16 + (lane >> 4) * 4 + e;
-      if (i < n) Y[i * NOUT + j] = (acc[rt][e] + bj) / sc + sh;
-    }
+    for (int e = 0; e < 4; ++e) y[e] = (acc[rt][e] + bj[e]) / nm->out_scale[j + e] + nm->out_shift[j + e];
+    *reinterpret_cast<f4_any*>(Y + i * NOUT + j) = y;
+  }
 }
 
 }  // namespace
@@ -1030,8 +1066,20 @@ extern "C" int surrogate_predict(surrogate_t* h, const float* dev_x, int64_t n, 
   if (n < 0 || n > ((int64_t)1 << 36)) { set_error("n out of range"); return LAT_EINVAL; }
   if (n == 0) return LAT_OK;
   const WCopies& c = h->wc;
-  hipLaunchKernelGGL(predict_kernel, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, h->stream, dev_x, n, h->nm,
-                     c.W1b, h->P + OB1, c.W2b, h->P + OB2, c.W3b, h->P + OB3, c.W4b, h->P + OB4, dev_y);
+  auto launch = [&](auto kernel, int rows, int threads) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((n + rows - 1) / rows)), dim3(threads), 0, h->stream, dev_x, n, h->nm, c,
+                       h->P + OB1, h->P + OB2, h->P + OB3, h->P + OB4, dev_y);
+  };
+  // The rows a block takes: as few as give every CU at most one block of sixteen
+  // waves, whose wave has a single tile of units per layer (up to 4096 rows 14-16
+  // us with 16 rows a block, 27 with 64; up to 8192 20 us with 32 against 27; at
+  // 16384 37 against 30).  From there on four waves with four tiles each,
+  // which read a row's activations from LDS a quarter as often and leave room for
+  // four blocks on a CU (65536 rows: 63 us, sixteen waves 102, eight 76).
+  constexpr int CUS = 256;
+  if (n <= 16 * CUS) launch(predict_kernel<1, 16>, 16, 1024);
+  else if (n <= 32 * CUS) launch(predict_kernel<2, 16>, 32, 1024);
+  else launch(predict_kernel<4, 4>, 64, 256);
   CL_HIP(hipGetLastError());
   return LAT_OK;
 }

@@ -87,6 +87,26 @@ def test_predict_matches_oracle_forward(n):
     assert np.linalg.norm(d) < 1e-4 * np.linalg.norm(yn), np.linalg.norm(d) / np.linalg.norm(yn)
 
 
+@pytest.mark.parametrize("n", [15, 17, 4096, 4097, 8192, 8193, 16400])
+def test_predict_gives_a_row_the_same_bits_in_any_batch(n):
+    """Blocks of 16, 32 and 64 rows and the last, partial one: a row's answer
+    depends neither on the batch it comes in nor on its place there, and rows
+    go to any FP32 address."""
+    torch = _torch()
+    osh, osc = _out_norm(3)
+    m = _model(64, osh, osc)
+    m.set_weights(_weights(11))
+    x = torch.from_numpy(_inputs(21, n)[0]).cuda()
+    y = m.predict(x)
+    z = torch.full((n * 64 + 2,), 7.0, dtype=torch.float32, device="cuda")
+    m.predict(x.flip(0).contiguous(), z[1:-1].view(n, 64))
+    torch.cuda.synchronize()
+    assert torch.equal(z[1:-1].view(n, 64).flip(0), y)
+    assert z[0] == 7.0 and z[-1] == 7.0
+    for a in (0, n // 2, n - 9):
+        assert torch.equal(m.predict(x[a:a + 9].contiguous()), y[a:a + 9])
+
+
 def test_loss_and_gradients_match_oracle_with_bf16_rounding():
     torch = _torch()
     osh, osc = _out_norm(4)
