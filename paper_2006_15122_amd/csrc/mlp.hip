@@ -6,13 +6,14 @@
 //   forward          a_l   = h_{l-1} W_l^T            (A = h_{l-1},  Bt = W_l)
 //   input gradient   dh    = da_l W_l                 (A = da_l,     Bt = W_l^T)
 //   weight gradient  gW_l  = da_l^T h_{l-1}           (A = da_l^T,   Bt = h_{l-1}^T)
-// A training step is three kernels.  The first takes 16 batch rows per block
+// A training step is two kernels.  The first takes 16 batch rows per block
 // through the forward pass, the loss and the input-gradient chain with the
-// activations in LDS (all of that is local to a row), and writes BF16
-// transposed copies of h_l and da_l.  The second computes the three weight
-// gradients in one launch, split over the batch (KSPLIT rows per split).  The
-// third sums every partial (splits, bias columns, loss) in a fixed order and
-// applies Adam, so a training step is deterministic.
+// activations in LDS (all of that is local to a row), and writes BF16 copies
+// of h_l and da_l in blocks of 16 batch rows, each unit's 16 values together.
+// The second computes the weight gradients (KSPLIT rows per split, the splits
+// of a tile in the waves of one block), sums every partial (splits, bias
+// columns, loss) in a fixed order and applies Adam, so a training step is
+// deterministic.
 //
 // Operand layout of one 16x16x32 product on a 64-lane wave (verified on the
 // device): lane l holds A[l%16][8(l/16) .. 8(l/16)+7] and
@@ -25,6 +26,7 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "common.hpp"
@@ -146,10 +148,10 @@ __device__ __forceinline__ void block_features(const float* X, const Norm* nm, i
 // takes RB = 16 rows through the forward pass, the loss and the backward pass
 // down to the input layer; the 16 x 256 activations and gradients stay in
 // LDS between layers.  Sixteen waves; wave w owns hidden units 16w .. 16w+15
-// (waves 0-3 also output units 16w .. 16w+15), so the thread that writes a
-// pre-activation a_l[i][j] is the one that reads it back for GELU'(a_l) on
-// the way down.  It writes what the
-// weight-gradient products need (h_l^T, da_l^T, BF16) and per-block partial
+// (waves 0-3 also output units 16w .. 16w+15), so the pre-activations that
+// GELU'(a_l) needs on the way down stay in the registers of the thread that
+// formed them.  It writes what the
+// weight-gradient products need (h_l, da_l, BF16) and per-block partial
 // sums of the bias gradients, of the first layer's weight gradient and of the
 // loss.
 // ---------------------------------------------------------------------------
@@ -165,21 +167,22 @@ struct RowArgs {
   const Norm* nm;
   const bf16_t *W1b, *W2b, *W3b, *W4b, *W2t, *W3t, *W4t;
   const float *b1, *b2, *b3, *b4;
-  float *A1, *A2, *A3;              // FP32 pre-activations [Bp][WID]
-  bf16_t *H1t, *H2t, *H3t;          // BF16 h_l^T [WID][ldt]
-  bf16_t *DYt, *D3t, *D2t;          // BF16 dL/dy^T [NOUT][ldt], dL/da_l^T [WID][ldt]
-  int ldt;
+  bf16_t *H1t, *H2t, *H3t;          // BF16 h_l, [R][WID][RB]
+  bf16_t *DYt, *D3t, *D2t;          // BF16 dL/dy [R][NOUT][RB], dL/da_l [R][WID][RB]
   float *bp1, *bp2, *bp3, *bp4;     // per-block bias-gradient columns [R][width]
-  float* w1p;                       // per-block first-layer weight gradient [R][WID][NFEAT]
+  float* w1p;                       // per-block first-layer weight gradient [R][NFEAT][WID]
   double* lpart;                    // per-block sum of squared residuals [R]
 };
 
 // sum over the block's 16 rows of per-lane column values (lanes l, l^16, l^32,
-// l^48 share a column); lanes 0..15 return the column sums
+// l^48 share a column; every one of them returns the column sum).  The lane
+// swaps are vector instructions, where a shuffle is a trip through LDS.
+typedef uint32_t u32x2 __attribute__((__vector_size__(2 * sizeof(uint32_t))));
 __device__ __forceinline__ float col_sum16(float v) {
-  v += __shfl_xor(v, 16);
-  v += __shfl_xor(v, 32);
-  return v;
+  const u32x2 a = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false));
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const u32x2 b = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false));
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
 // one 16 x (16 CT) slab of C = A Bt^T: A is the block's 16 rows in LDS (pitch
@@ -210,120 +213,103 @@ __device__ __forceinline__ void slab16(const bf16_t* As, int lda, const bf16_t* 
     for (int ct = 0; ct < CT; ++ct) acc[ct] = mma(a[s], b[s][ct], acc[ct]);
 }
 
-__device__ __forceinline__ void store_t4(bf16_t* Ht, int j, int ldt, int i0, const bf16_t (&hb)[4]) {
-  uint2 v;
-  v.x = hb[0] | ((uint32_t)hb[1] << 16);
-  v.y = hb[2] | ((uint32_t)hb[3] << 16);
-  *reinterpret_cast<uint2*>(Ht + (size_t)j * ldt + i0) = v;
+// four rows i0 .. i0+3 of unit j into a block's [units][RB] copy
+__device__ __forceinline__ void store_t4(bf16_t* Ht, int j, int i0, const float (&v)[4]) {
+  *reinterpret_cast<uint2*>(Ht + j * RB + i0) = uint2{to_bf16x2(v[0], v[1]), to_bf16x2(v[2], v[3])};
 }
 
 constexpr int NWAVE = WID / (16 * CT);       // 16
-constexpr int L1R = RB * WID / (64 * NWAVE);  // layer-1 rows per thread (4)
+static_assert(RB * WID == 4 * 64 * NWAVE && CT == 1, "four rows of one unit per thread");
 
 __global__ __launch_bounds__(64 * NWAVE) void step_rows_kernel(RowArgs g) {
   __shared__ __align__(16) bf16_t HA[RB * LDH];
   __shared__ __align__(16) bf16_t HB[RB * LDH];
   __shared__ __align__(16) bf16_t DY[RB * LDY];
-  __shared__ float xs[RB][NFEAT];
+  __shared__ __align__(16) float xs[RB][NFEAT];
   __shared__ double lred[4];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int rq = (lane >> 4) * 4;  // first of this lane's 4 rows in a 16-row tile
   const int rb = blockIdx.x, r0 = rb * RB;
-  const int ldt = g.ldt;
-
-  // layer 1 (K = NFEAT, plain FMA): thread t is unit t % 256 for L1R rows;
-  // padding rows (past nvalid) take zero features
-  block_features<RB, 64 * NWAVE>(g.X, g.nm, t, [&](int r) -> int64_t {
+  const int j = 16 * w + (lane & 15);  // this lane's unit
+  auto row_of = [&](int r) -> int64_t {
     const int i = r0 + r;
     return i < g.nvalid ? (g.rows ? (int64_t)g.rows[i] : (int64_t)i) : -1;
-  }, xs);
+  };
+  auto blk = [&](bf16_t* p, int width) { return p + (size_t)rb * width * RB; };
+
+  block_features<RB, 64 * NWAVE>(g.X, g.nm, t, row_of, xs);
   __syncthreads();
+  // layer 1 (K = NFEAT, plain FMA); padding rows (past nvalid) have zero features
+  float a1[4], a2[4], a3[4];
   {
-    const int j = t & (WID - 1), rh = (t / WID) * L1R;
-    float wf[NFEAT];
+    float wf[NFEAT], hv[4];
 #pragma unroll
-    for (int c = 0; c < NFEAT; ++c) wf[c] = from_bf16(g.W1b[NFEAT * j + c]);
+    for (int c = 0; c < NFEAT; c += 8) {
+      const bf16x8 v = load8(g.W1b + NFEAT * j + c);
+#pragma unroll
+      for (int m = 0; m < 8; ++m) wf[c + m] = (float)v[m];
+    }
     const float bj = g.b1[j];
-    uint32_t packed[L1R / 2];
 #pragma unroll
-    for (int q = 0; q < L1R; ++q) {
-      const int r = rh + q;
+    for (int e = 0; e < 4; ++e) {
       float a = bj;
 #pragma unroll
-      for (int c = 0; c < NFEAT; ++c) a = fmaf(xs[r][c], wf[c], a);
-      const bf16_t hv = to_bf16(gelu(a));
-      g.A1[(size_t)(r0 + r) * WID + j] = a;
-      HA[r * LDH + j] = hv;
-      if (q & 1) packed[q >> 1] |= (uint32_t)hv << 16;
-      else packed[q >> 1] = hv;
+      for (int c = 0; c < NFEAT; ++c) a = fmaf(xs[rq + e][c], wf[c], a);
+      a1[e] = a;
+      hv[e] = gelu(a);
+      HA[(rq + e) * LDH + j] = to_bf16(hv[e]);
     }
-    static_assert(L1R == 4, "layer-1 rows per thread");
-    *reinterpret_cast<uint2*>(g.H1t + (size_t)j * ldt + r0 + rh) = uint2{packed[0], packed[1]};
+    store_t4(blk(g.H1t, WID), j, rq, hv);
   }
   __syncthreads();
 
   // hidden layers 2 and 3: a = h W^T + b, h' = BF16(GELU(a))
-  {
-    const bf16_t* Wl[2] = {g.W2b, g.W3b};
-    const float* bl[2] = {g.b2, g.b3};
-    float* Al[2] = {g.A2, g.A3};
-    bf16_t* Htl[2] = {g.H2t, g.H3t};
-    bf16_t* src[2] = {HA, HB};
-    bf16_t* dstb[2] = {HB, HA};
+  auto hidden = [&](const bf16_t* src, bf16_t* dst, const bf16_t* W, const float* bias, bf16_t* Ht, float (&av)[4]) {
+    f4 acc[CT];
+    slab16<WID / 32>(src, LDH, W, WID, 16 * w, lane, acc);
+    const float bj = bias[j];
+    float hv[4];
 #pragma unroll
-    for (int l = 0; l < 2; ++l) {
-      f4 acc[CT];
-      slab16<WID / 32>(src[l], LDH, Wl[l], WID, 16 * CT * w, lane, acc);
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct) {
-        const int j = 16 * CT * w + 16 * ct + (lane & 15);
-        const float bj = bl[l][j];
-        bf16_t hb[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int r = rq + e;
-          const float a = acc[ct][e] + bj;
-          Al[l][(size_t)(r0 + r) * WID + j] = a;
-          hb[e] = to_bf16(gelu(a));
-          dstb[l][r * LDH + j] = hb[e];
-        }
-        store_t4(Htl[l], j, ldt, r0 + rq, hb);
-      }
-      __syncthreads();
+    for (int e = 0; e < 4; ++e) {
+      av[e] = acc[0][e] + bj;
+      hv[e] = gelu(av[e]);
+      dst[(rq + e) * LDH + j] = to_bf16(hv[e]);
     }
-  }
+    store_t4(blk(Ht, WID), j, rq, hv);
+    __syncthreads();
+  };
+  hidden(HA, HB, g.W2b, g.b2, g.H2t, a2);
+  hidden(HB, HA, g.W3b, g.b3, g.H3t, a3);
 
   // output layer, loss and dL/dy = 2 (y - t) / (n NOUT) in normalised units;
   // waves 0-3 own outputs 16w .. 16w+15
   if (w < NOUT / 16) {
-    const int r16 = lane & 15, kq = (lane >> 4) * 8;
-    f4 acc = f4{0.0f, 0.0f, 0.0f, 0.0f};
-    const bf16_t* pb = g.W4b + (size_t)(16 * w + r16) * WID + kq;
-#pragma unroll
-    for (int s = 0; s < WID / 32; ++s) acc = mma(load8(HA + r16 * LDH + 32 * s + kq), load8(pb + 32 * s), acc);
-    // (8 independent 16-byte loads: the compiler issues them together)
-    const int j = 16 * w + r16;
-    const float bj = g.b4[j], sh = g.nm->out_shift[j], sc = g.nm->out_scale[j];
-    double lsum = 0.0;
-    float cs = 0.0f;
-    bf16_t hb[4];
+    f4 acc[CT];
+    float tv[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const int r = rq + e, i = r0 + r;
-      const float y = acc[e] + bj;
+      const int64_t src = row_of(rq + e);
+      tv[e] = src >= 0 ? g.T[src * NOUT + j] : 0.0f;
+    }
+    slab16<WID / 32>(HA, LDH, g.W4b, WID, 16 * w, lane, acc);
+    const float bj = g.b4[j], sh = g.nm->out_shift[j], sc = g.nm->out_scale[j];
+    double lsum = 0.0;
+    float cs = 0.0f, dv[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float y = acc[0][e] + bj;
       float dy = 0.0f;
-      if (i < g.nvalid) {
-        const int64_t src = g.rows ? (int64_t)g.rows[i] : (int64_t)i;
-        const float tn = (g.T[src * NOUT + j] - sh) * sc;
+      if (r0 + rq + e < g.nvalid) {
+        const float tn = (tv[e] - sh) * sc;
         const float res = y - tn;
         lsum += (double)res * (double)res;
         dy = res * g.dscale;
       }
-      hb[e] = to_bf16(dy);
-      DY[r * LDY + j] = hb[e];
+      dv[e] = dy;
+      DY[(rq + e) * LDY + j] = to_bf16(dy);
       cs += dy;
     }
-    store_t4(g.DYt, j, ldt, r0 + rq, hb);
+    store_t4(blk(g.DYt, NOUT), j, rq, dv);
     cs = col_sum16(cs);
     if (lane < 16) g.bp4[(size_t)rb * NOUT + j] = cs;
 #pragma unroll
@@ -335,127 +321,48 @@ __global__ __launch_bounds__(64 * NWAVE) void step_rows_kernel(RowArgs g) {
   if (t == 0) g.lpart[rb] = ((lred[0] + lred[1]) + lred[2]) + lred[3];
 
   // backward through layers 4 -> 3 -> 2 (da_l = (da_{l+1} W_{l+1}) GELU'(a_l)) and 2 -> 1
-  {
-    const bf16_t* Wt[3] = {g.W4t, g.W3t, g.W2t};
-    const float* Al[3] = {g.A3, g.A2, g.A1};
-    bf16_t* Dt[2] = {g.D3t, g.D2t};
-    float* bp[3] = {g.bp3, g.bp2, g.bp1};
-    const bf16_t* src[3] = {DY, HB, HA};
-    const int lds[3] = {LDY, LDH, LDH};
-    bf16_t* dstb[2] = {HB, HA};
+  float da[4];
+  auto back = [&](auto nk, const bf16_t* src, int lds, const bf16_t* Wt, const float (&av)[4], float* bp) {
+    constexpr int NK = decltype(nk)::value;
+    f4 acc[CT];
+    slab16<NK>(src, lds, Wt, 32 * NK, 16 * w, lane, acc);
+    float c0 = 0.0f;
 #pragma unroll
-    for (int l = 0; l < 3; ++l) {
-      f4 acc[CT];
-      if (l == 0) slab16<NOUT / 32>(src[l], lds[l], Wt[l], NOUT, 16 * CT * w, lane, acc);
-      else slab16<WID / 32>(src[l], lds[l], Wt[l], WID, 16 * CT * w, lane, acc);
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct) {
-        const int j = 16 * CT * w + 16 * ct + (lane & 15);
-        float c0 = 0.0f, dae[4];
-        bf16_t hb[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int r = rq + e;
-          const float da = acc[ct][e] * gelu_grad(Al[l][(size_t)(r0 + r) * WID + j]);
-          c0 += da;
-          dae[e] = da;
-          if (l < 2) {
-            hb[e] = to_bf16(da);
-            dstb[l][r * LDH + j] = hb[e];
-          }
-        }
-        if (l < 2) store_t4(Dt[l], j, ldt, r0 + rq, hb);
-        c0 = col_sum16(c0);
-        if (lane < 16) bp[l][(size_t)rb * WID + j] = c0;
-        if (l == 2) {
-          // first layer's weight gradient: one feature at a time, summed
-          // over the block's rows (rows e of this lane, then across lanes)
-#pragma unroll
-          for (int c = 0; c < NFEAT; ++c) {
-            float cf = 0.0f;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) cf = fmaf(dae[e], xs[rq + e][c], cf);
-            cf = col_sum16(cf);
-            if (lane < 16) g.w1p[((size_t)rb * WID + j) * NFEAT + c] = cf;
-          }
-        }
-      }
-      if (l < 2) __syncthreads();
+    for (int e = 0; e < 4; ++e) {
+      da[e] = acc[0][e] * gelu_grad(av[e]);
+      c0 += da[e];
     }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// training step, part 2: the three weight-gradient products
-//   gW_l[M][N] = sum over batch rows of da_l^T h_{l-1}  (A = da_l^T, Bt = h_{l-1}^T)
-// in one launch, each split over KSPLIT batch rows into its own partial slab
-// (summed in split order by the finishing kernel).  64 x 64 block tiles, four
-// waves of 32 x 32; all operand fragments of a block are loaded first.
-// ---------------------------------------------------------------------------
-struct WgradProduct {
-  const bf16_t* A;   // [M][K], pitch ld
-  const bf16_t* Bt;  // [N][K], pitch ld
-  float* part;       // [splits][M][N]
-  int M;
-};
-
-struct WgradArgs {
-  WgradProduct p[3];
-  int ld, K, S;      // pitch (= max batch), batch rows, splits
-  int first[4];      // first block of each product (cumulative)
-};
-
-__global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs g) {
-  const int b = blockIdx.x;
-  const int pi = b < g.first[1] ? 0 : (b < g.first[2] ? 1 : 2);
-  const WgradProduct& P = g.p[pi];
-  constexpr int N = WID, TX = WID / 64;
-  const int ty = P.M / 64, loc = b - g.first[pi];
-  const int bx = loc % TX, by = (loc / TX) % ty, bz = loc / (TX * ty);
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, wr = w >> 1, wc = w & 1;
-  const int r16 = lane & 15, kq = (lane >> 4) * 8;
-  const int row0 = by * 64 + wr * 32, col0 = bx * 64 + wc * 32;
-  const int kb = bz * KSPLIT, ke = min(g.K, kb + KSPLIT);
-  const int nk = (ke - kb) >> 5;  // 2, 4, 6 or 8
-  const bf16_t* pa0 = P.A + (size_t)(row0 + r16) * g.ld + kq;
-  const bf16_t* pa1 = pa0 + (size_t)16 * g.ld;
-  const bf16_t* pb0 = P.Bt + (size_t)(col0 + r16) * g.ld + kq;
-  const bf16_t* pb1 = pb0 + (size_t)16 * g.ld;
-  f4 acc[2][2];
+    c0 = col_sum16(c0);
+    if (lane < 16) bp[(size_t)rb * WID + j] = c0;
+  };
+  auto hand_on = [&](bf16_t* dst, bf16_t* Dt) {
 #pragma unroll
-  for (int rt = 0; rt < 2; ++rt)
+    for (int e = 0; e < 4; ++e) dst[(rq + e) * LDH + j] = to_bf16(da[e]);
+    store_t4(blk(Dt, WID), j, rq, da);
+    __syncthreads();
+  };
+  back(std::integral_constant<int, NOUT / 32>{}, DY, LDY, g.W4t, a3, g.bp3);
+  hand_on(HB, g.D3t);
+  back(std::integral_constant<int, WID / 32>{}, HB, LDH, g.W3t, a2, g.bp2);
+  hand_on(HA, g.D2t);
+  back(std::integral_constant<int, WID / 32>{}, HA, LDH, g.W2t, a1, g.bp1);
+  // first layer's weight gradient, summed over the block's rows (rows e of this
+  // lane, then across lanes); four features at a time, each quarter of the wave
+  // stores one
+  float* wp = g.w1p + (size_t)rb * NFEAT * WID + j;
 #pragma unroll
-    for (int ct = 0; ct < 2; ++ct) acc[rt][ct] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-  bf16x8 fa[8][2], fb[8][2];
+  for (int c = 0; c < NFEAT; c += 4) {
+    float cf[4];
 #pragma unroll
-  for (int s = 0; s < 8; ++s) {
-    if (s < nk) {
-      const int k = kb + 32 * s;
-      fa[s][0] = load8(pa0 + k);
-      fa[s][1] = load8(pa1 + k);
-      fb[s][0] = load8(pb0 + k);
-      fb[s][1] = load8(pb1 + k);
+    for (int q = 0; q < 4; ++q) {
+      cf[q] = 0.0f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) cf[q] = fmaf(da[e], xs[rq + e][c + q], cf[q]);
+      cf[q] = col_sum16(cf[q]);
     }
+    const int q = lane >> 4;
+    wp[(size_t)(c + q) * WID] = q == 0 ? cf[0] : q == 1 ? cf[1] : q == 2 ? cf[2] : cf[3];
   }
-#pragma unroll
-  for (int s = 0; s < 8; ++s) {
-    if (s < nk) {
-      acc[0][0] = mma(fa[s][0], fb[s][0], acc[0][0]);
-      acc[0][1] = mma(fa[s][0], fb[s][1], acc[0][1]);
-      acc[1][0] = mma(fa[s][1], fb[s][0], acc[1][0]);
-      acc[1][1] = mma(fa[s][1], fb[s][1], acc[1][1]);
-    }
-  }
-  float* out = P.part + (size_t)bz * P.M * N;
-#pragma unroll
-  for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-    for (int ct = 0; ct < 2; ++ct)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int i = row0 + rt * 16 + (lane >> 4) * 4 + e, j = col0 + ct * 16 + r16;
-        out[(size_t)i * N + j] = acc[rt][ct][e];
-      }
 }
 
 // ---------------------------------------------------------------------------
@@ -496,20 +403,28 @@ struct TrainCtl {
   double lr;
 };
 
-struct FinishArgs {
-  const float *part2, *part3, *part4, *bp1, *bp2, *bp3, *bp4, *w1p;
+struct WgradProduct {
+  const bf16_t* A;   // [R][M][RB]
+  const bf16_t* Bt;  // [R][WID][RB]
+  int M, op;         // rows of the product, its place in the parameter vector
+  bf16_t *W, *Wt;    // BF16 copies [M][WID] and [WID][M]
+};
+
+struct GradArgs {
+  WgradProduct p[3];
+  int K, S, R;         // batch rows, splits of the weight products, RB-row blocks
+  const float *w1p, *bp1, *bp2, *bp3, *bp4;
   const double* lpart;
-  int S, R;            // splits of the weight products, RB-row blocks
   double inv_count;    // 1 / (nvalid * 64)
   double* loss;        // one FP64
-  float* G;            // gradient out [NPAR]
+  float* G;            // gradient out [NPAR] (without update)
   // Adam: step t = ctl->t0 + step + 1, bias corrections 1 - beta^t
   float *P, *Mo, *Ve;
   const TrainCtl* ctl;
   int step;
   double beta1, beta2;
   float eps;
-  WCopies c;
+  bf16_t* W1b;
 };
 
 __global__ void ctl_set_lr(TrainCtl* c, double lr) {
@@ -519,61 +434,206 @@ __global__ void ctl_advance(TrainCtl* c, int nsteps) {
   if (threadIdx.x == 0) c->t0 += (double)nsteps;
 }
 
-// sum_{r < n} base[r * stride] in order r = 0, 1, ...; the loads are issued
-// 16 at a time so that the chain waits for memory once per 16 terms
-__device__ __forceinline__ float ordered_sum(const float* __restrict__ base, size_t stride, int n) {
-  float g = 0.0f;
-  for (int r0 = 0; r0 < n; r0 += 16) {
-    float v[16];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) v[k] = (r0 + k < n) ? base[(size_t)(r0 + k) * stride] : 0.0f;
-#pragma unroll
-    for (int k = 0; k < 16; ++k)
-      if (r0 + k < n) g += v[k];
-  }
-  return g;
+// ---------------------------------------------------------------------------
+// training step, part 2: the three weight-gradient products
+//   gW_l[M][N] = sum over batch rows of da_l^T h_{l-1}  (A = da_l^T, Bt = h_{l-1}^T),
+// every other sum over the batch, and Adam, in one launch.  A block takes one of
+//   - a 32 x 32 tile of a product: wave s computes the splits s, s + 8, ... (KSPLIT
+//     batch rows each, all operand fragments loaded first), the block adds the
+//     splits in their order from LDS and updates the tile's weights and both
+//     BF16 copies, the transposed one through LDS;
+//   - 64 columns of the first layer's weight gradient or of a bias gradient: the
+//     waves load 128 blocks' partials side by side, the first wave adds them in
+//     order;
+//   - the loss.
+// At the training batch of 2048 rows that is one block per CU.
+// ---------------------------------------------------------------------------
+constexpr int GT = 512, GW = GT / 64, TILE = 32, TP = TILE + 4;  // threads, waves, tile, its LDS pitch
+constexpr int SUMR = 128;                                       // partials a block adds between barriers
+constexpr int TILES4 = (NOUT / TILE) * (WID / TILE), TILES3 = (WID / TILE) * (WID / TILE);
+constexpr int NTILES = TILES4 + 2 * TILES3, NW1B = WID * NFEAT / 64, NBIAS = (3 * WID + NOUT) / 64;
+constexpr int GRAD_BLOCKS = NTILES + NW1B + NBIAS + 1;
+
+struct AdamCoef {
+  float bc1, bc2;
+};
+__device__ __forceinline__ AdamCoef adam_coef(const GradArgs& g) {
+  const double t = g.ctl->t0 + (double)(g.step + 1);
+  return AdamCoef{(float)(1.0 - pow(g.beta1, t)), (float)(1.0 - pow(g.beta2, t))};
+}
+__device__ __forceinline__ float adam(const GradArgs& g, const AdamCoef& c, int p, float gr, float m0, float v0,
+                                      float w0) {
+  const float lr = (float)g.ctl->lr, b1 = (float)g.beta1, b2 = (float)g.beta2;
+  const float m = fmaf(1.0f - b1, gr, b1 * m0), v = fmaf(gr, (1.0f - b2) * gr, b2 * v0);
+  g.Mo[p] = m;
+  g.Ve[p] = v;
+  const float w = w0 - lr * (m / c.bc1) / (sqrtf(v / c.bc2) + g.eps);
+  g.P[p] = w;
+  return w;
 }
 
 template <bool UPDATE>
-__global__ __launch_bounds__(256) void finish_kernel(FinishArgs f) {
-  const int p = blockIdx.x * 256 + threadIdx.x;
-  if (p == 0) {
+__global__ __launch_bounds__(GT) void grad_kernel(GradArgs g) {
+  __shared__ __align__(16) float part[GW * TILE * TP];
+  __shared__ bf16_t tr[TILE][TILE + 2];
+  __shared__ AdamCoef coef;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  int b = blockIdx.x;
+  if (b < NTILES) {
+    const int pi = b < TILES4 ? 0 : (b < TILES4 + TILES3 ? 1 : 2);
+    const WgradProduct& P = g.p[pi];
+    const int loc = pi == 0 ? b : (b - TILES4) % TILES3;
+    const int row0 = loc / (WID / TILE) * TILE, col0 = loc % (WID / TILE) * TILE;
+    const int r16 = lane & 15, kq = (lane >> 4) * 8, M = P.M;
+    constexpr int EL = TILE * TILE / GT;  // elements per thread in the update
+    float sum[EL];
+    int pe[EL];
+    float m0[EL], v0[EL], w0[EL];
+#pragma unroll
+    for (int q = 0; q < EL; ++q) {
+      const int e = t + GT * q;
+      sum[q] = 0.0f;
+      pe[q] = P.op + (row0 + e / TILE) * WID + col0 + e % TILE;
+    }
+    for (int s0 = 0; s0 < g.S; s0 += GW) {
+      const int kb = (s0 + w) * KSPLIT, nk = (min(g.K, kb + KSPLIT) - kb) >> 5;  // <= 0 past the last split
+      f4 acc[2][2];
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+        for (int ct = 0; ct < 2; ++ct) acc[rt][ct] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+      bf16x8 fa[KSPLIT / 32][2], fb[KSPLIT / 32][2];
+#pragma unroll
+      for (int s = 0; s < KSPLIT / 32; ++s) {
+        if (s < nk) {
+          const int k = kb + 32 * s + kq;
+          const bf16_t* pa = P.A + ((size_t)(k / RB) * M + row0 + r16) * RB + k % RB;
+          const bf16_t* pb = P.Bt + ((size_t)(k / RB) * WID + col0 + r16) * RB + k % RB;
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            fa[s][q] = load8(pa + q * 16 * RB);
+            fb[s][q] = load8(pb + q * 16 * RB);
+          }
+        }
+      }
+      if (s0 == 0 && UPDATE) {
+#pragma unroll
+        for (int q = 0; q < EL; ++q) {
+          m0[q] = g.Mo[pe[q]];
+          v0[q] = g.Ve[pe[q]];
+          w0[q] = g.P[pe[q]];
+        }
+        if (w == GW - 1) {
+          const AdamCoef c = adam_coef(g);
+          if (lane == 0) coef = c;
+        }
+      }
+#pragma unroll
+      for (int s = 0; s < KSPLIT / 32; ++s) {
+        if (s < nk) {
+#pragma unroll
+          for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+            for (int ct = 0; ct < 2; ++ct) acc[rt][ct] = mma(fa[s][rt], fb[s][ct], acc[rt][ct]);
+        }
+      }
+      if (s0) __syncthreads();  // the sums below have read the previous splits
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+        for (int ct = 0; ct < 2; ++ct)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            part[(w * TILE + rt * 16 + (lane >> 4) * 4 + e) * TP + ct * 16 + r16] = acc[rt][ct][e];
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < EL; ++q) {
+        const int e = t + GT * q;
+#pragma unroll
+        for (int s = 0; s < GW; ++s)
+          if (s0 + s < g.S) sum[q] += part[(s * TILE + e / TILE) * TP + e % TILE];
+      }
+    }
+    if constexpr (!UPDATE) {
+#pragma unroll
+      for (int q = 0; q < EL; ++q) g.G[pe[q]] = sum[q];
+    } else {
+      const AdamCoef c = coef;
+#pragma unroll
+      for (int q = 0; q < EL; ++q) {
+        const int e = t + GT * q, i = e / TILE, j = e % TILE;
+        const bf16_t v = to_bf16(adam(g, c, pe[q], sum[q], m0[q], v0[q], w0[q]));
+        P.W[(row0 + i) * WID + col0 + j] = v;
+        tr[i][j] = v;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < EL; ++q) {
+        const int e = t + GT * q, j = e / TILE, i = e % TILE;
+        P.Wt[(size_t)(col0 + j) * M + row0 + i] = tr[i][j];
+      }
+    }
+    return;
+  }
+  b -= NTILES;
+  if (b < NW1B + NBIAS) {
+    // 64 columns: of w1p (feature-major, column c WID + j is parameter j NFEAT + c) or of a bias
+    const float* src;
+    int width, col, p;
+    if (b < NW1B) {
+      src = g.w1p;
+      width = WID * NFEAT;
+      col = 64 * b + lane;
+      p = OW1 + (col % WID) * NFEAT + col / WID;
+    } else {
+      const int k = b - NW1B, l = min(k / (WID / 64), 3);
+      src = l == 0 ? g.bp1 : l == 1 ? g.bp2 : l == 2 ? g.bp3 : g.bp4;
+      width = l < 3 ? WID : NOUT;
+      col = 64 * (k - l * (WID / 64)) + lane;
+      p = (l == 0 ? OB1 : l == 1 ? OB2 : l == 2 ? OB3 : OB4) + col;
+    }
+    static_assert(SUMR * 64 <= GW * TILE * TP, "partials fit the LDS of a tile block");
+    float sum = 0.0f;
+    for (int r0 = 0; r0 < g.R; r0 += SUMR) {
+      float v[SUMR / GW];
+#pragma unroll
+      for (int m = 0; m < SUMR / GW; ++m) {
+        const int r = r0 + w + GW * m;
+        v[m] = r < g.R ? src[(size_t)r * width + col] : 0.0f;
+      }
+      if (r0) __syncthreads();
+#pragma unroll
+      for (int m = 0; m < SUMR / GW; ++m) part[(w + GW * m) * 64 + lane] = v[m];
+      __syncthreads();
+      if (w == 0) {
+        const int n = min(SUMR, g.R - r0);  // R is a multiple of 4
+        for (int r = 0; r < n; r += 4) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) sum += part[(r + k) * 64 + lane];
+        }
+      }
+    }
+    if (w) return;
+    if constexpr (!UPDATE) {
+      g.G[p] = sum;
+    } else {
+      const float v = adam(g, adam_coef(g), p, sum, g.Mo[p], g.Ve[p], g.P[p]);
+      if (b < NW1B) g.W1b[p - OW1] = to_bf16(v);
+    }
+    return;
+  }
+  // the loss
+  double* lp = reinterpret_cast<double*>(part);
+  static_assert(MAX_BATCH / RB * sizeof(double) <= sizeof(part), "loss partials fit");
+  for (int r = t; r < g.R; r += GT) lp[r] = g.lpart[r];
+  __syncthreads();
+  if (t == 0) {
     double s = 0.0;
-    for (int r = 0; r < f.R; ++r) s += f.lpart[r];
-    f.loss[0] = s * f.inv_count;
-  }
-  if (p >= NPAR) return;
-  float g;
-  if (p < OB1) {
-    const int j = p / NFEAT, c = p % NFEAT;
-    g = ordered_sum(f.w1p + (size_t)j * NFEAT + c, (size_t)WID * NFEAT, f.R);
-  } else if (p < OW2) {
-    g = ordered_sum(f.bp1 + (p - OB1), WID, f.R);
-  } else if (p < OB2) {
-    g = ordered_sum(f.part2 + (p - OW2), (size_t)WID * WID, f.S);
-  } else if (p < OW3) {
-    g = ordered_sum(f.bp2 + (p - OB2), WID, f.R);
-  } else if (p < OB3) {
-    g = ordered_sum(f.part3 + (p - OW3), (size_t)WID * WID, f.S);
-  } else if (p < OW4) {
-    g = ordered_sum(f.bp3 + (p - OB3), WID, f.R);
-  } else if (p < OB4) {
-    g = ordered_sum(f.part4 + (p - OW4), (size_t)NOUT * WID, f.S);
-  } else {
-    g = ordered_sum(f.bp4 + (p - OB4), NOUT, f.R);
-  }
-  f.G[p] = g;
-  if constexpr (UPDATE) {
-    const double t = f.ctl->t0 + (double)(f.step + 1);
-    const float bc1 = (float)(1.0 - pow(f.beta1, t)), bc2 = (float)(1.0 - pow(f.beta2, t));
-    const float lr = (float)f.ctl->lr, b1 = (float)f.beta1, b2 = (float)f.beta2;
-    const float m = b1 * f.Mo[p] + (1.0f - b1) * g;
-    const float v = b2 * f.Ve[p] + (1.0f - b2) * g * g;
-    f.Mo[p] = m;
-    f.Ve[p] = v;
-    const float w = f.P[p] - lr * (m / bc1) / (sqrtf(v / bc2) + f.eps);
-    f.P[p] = w;
-    store_copies(p, w, f.c);
+    for (int r = 0; r < g.R; r += 4) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) s += lp[r + k];
+    }
+    g.loss[0] = s * g.inv_count;
   }
 }
 
@@ -749,11 +809,11 @@ struct surrogate_t {
   surrogate_params p;
   hipStream_t stream;
   int B;  // max_batch
-  float *P, *Mo, *Ve, *G, *A1, *A2, *A3;
+  float *P, *Mo, *Ve;
   Norm* nm;
   WCopies wc;
   bf16_t *H1t, *H2t, *H3t, *DYt, *D3t, *D2t;
-  float *part2, *part3, *part4, *bp1, *bp2, *bp3, *bp4, *w1p;
+  float *bp1, *bp2, *bp3, *bp4, *w1p;
   double *lpart, *losses, *stats;
   TrainCtl* ctl;
   int64_t t;   // Adam steps taken
@@ -776,13 +836,12 @@ size_t carve(int B, char* base, surrogate_t* s) {
     off += bytes;
     return q;
   };
-  const int S = (B + KSPLIT - 1) / KSPLIT, R = B / RB;
+  const int R = B / RB;
   surrogate_t d{};
   surrogate_t& h = s ? *s : d;
   h.P = (float*)take(4ull * NPAR);
   h.Mo = (float*)take(4ull * NPAR);
   h.Ve = (float*)take(4ull * NPAR);
-  h.G = (float*)take(4ull * NPAR);
   h.nm = (Norm*)take(sizeof(Norm));
   h.wc.W1b = (bf16_t*)take(2ull * WID * NFEAT);
   h.wc.W2b = (bf16_t*)take(2ull * WID * WID);
@@ -791,15 +850,9 @@ size_t carve(int B, char* base, surrogate_t* s) {
   h.wc.W3t = (bf16_t*)take(2ull * WID * WID);
   h.wc.W4b = (bf16_t*)take(2ull * NOUT * WID);
   h.wc.W4t = (bf16_t*)take(2ull * NOUT * WID);
-  h.A1 = (float*)take(4ull * B * WID);
-  h.A2 = (float*)take(4ull * B * WID);
-  h.A3 = (float*)take(4ull * B * WID);
   bf16_t** act[] = {&h.H1t, &h.H2t, &h.H3t, &h.D3t, &h.D2t};
   for (bf16_t** a : act) *a = (bf16_t*)take(2ull * B * WID);
   h.DYt = (bf16_t*)take(2ull * B * NOUT);
-  h.part2 = (float*)take(4ull * S * WID * WID);
-  h.part3 = (float*)take(4ull * S * WID * WID);
-  h.part4 = (float*)take(4ull * S * NOUT * WID);
   h.bp1 = (float*)take(4ull * R * WID);
   h.bp2 = (float*)take(4ull * R * WID);
   h.bp3 = (float*)take(4ull * R * WID);
@@ -848,7 +901,7 @@ void drop_graph(surrogate_t* h) {
 int train_step(surrogate_t* h, const float* X, const float* T, const int32_t* rows, int n, float* G,
                double* loss_dev, bool update, int step) {
   hipStream_t st = h->stream;
-  const int Bp = (n + 63) / 64 * 64, R = Bp / RB, S = (Bp + KSPLIT - 1) / KSPLIT, ldt = h->B;
+  const int Bp = (n + 63) / 64 * 64, R = Bp / RB, S = (Bp + KSPLIT - 1) / KSPLIT;
   const WCopies& c = h->wc;
   // rows: forward, loss, backward to the input layer
   RowArgs ra{};
@@ -858,43 +911,33 @@ int train_step(surrogate_t* h, const float* X, const float* T, const int32_t* ro
   ra.W1b = c.W1b; ra.W2b = c.W2b; ra.W3b = c.W3b; ra.W4b = c.W4b;
   ra.W2t = c.W2t; ra.W3t = c.W3t; ra.W4t = c.W4t;
   ra.b1 = h->P + OB1; ra.b2 = h->P + OB2; ra.b3 = h->P + OB3; ra.b4 = h->P + OB4;
-  ra.A1 = h->A1; ra.A2 = h->A2; ra.A3 = h->A3;
   ra.H1t = h->H1t; ra.H2t = h->H2t; ra.H3t = h->H3t;
   ra.DYt = h->DYt; ra.D3t = h->D3t; ra.D2t = h->D2t;
-  ra.ldt = ldt;
   ra.bp1 = h->bp1; ra.bp2 = h->bp2; ra.bp3 = h->bp3; ra.bp4 = h->bp4;
   ra.w1p = h->w1p; ra.lpart = h->lpart;
   hipLaunchKernelGGL(step_rows_kernel, dim3(R), dim3(64 * NWAVE), 0, st, ra);
   CL_HIP(hipGetLastError());
-  // weight gradients of layers 4, 3, 2
-  WgradArgs wa{};
-  wa.p[0] = WgradProduct{h->DYt, h->H3t, h->part4, NOUT};
-  wa.p[1] = WgradProduct{h->D3t, h->H2t, h->part3, WID};
-  wa.p[2] = WgradProduct{h->D2t, h->H1t, h->part2, WID};
-  wa.ld = ldt; wa.K = Bp; wa.S = S;
-  wa.first[0] = 0;
-  for (int q = 0; q < 3; ++q) wa.first[q + 1] = wa.first[q] + (WID / 64) * (wa.p[q].M / 64) * S;
-  hipLaunchKernelGGL(wgrad_kernel, dim3(wa.first[3]), dim3(256), 0, st, wa);
-  CL_HIP(hipGetLastError());
-  FinishArgs f{};
-  f.part2 = h->part2; f.part3 = h->part3; f.part4 = h->part4;
-  f.bp1 = h->bp1; f.bp2 = h->bp2; f.bp3 = h->bp3; f.bp4 = h->bp4; f.w1p = h->w1p;
-  f.lpart = h->lpart; f.S = S; f.R = R;
-  f.inv_count = 1.0 / ((double)n * NOUT);
-  f.loss = loss_dev;
-  f.G = G;
-  f.P = h->P; f.Mo = h->Mo; f.Ve = h->Ve;
-  f.c = c;
-  const int fb = (NPAR + 255) / 256;
+  GradArgs a{};
+  a.p[0] = WgradProduct{h->DYt, h->H3t, NOUT, OW4, c.W4b, c.W4t};
+  a.p[1] = WgradProduct{h->D3t, h->H2t, WID, OW3, c.W3b, c.W3t};
+  a.p[2] = WgradProduct{h->D2t, h->H1t, WID, OW2, c.W2b, c.W2t};
+  a.K = Bp; a.S = S; a.R = R;
+  a.w1p = h->w1p; a.bp1 = h->bp1; a.bp2 = h->bp2; a.bp3 = h->bp3; a.bp4 = h->bp4;
+  a.lpart = h->lpart;
+  a.inv_count = 1.0 / ((double)n * NOUT);
+  a.loss = loss_dev;
+  a.G = G;
+  a.P = h->P; a.Mo = h->Mo; a.Ve = h->Ve;
+  a.W1b = c.W1b;
   if (update) {
-    f.ctl = h->ctl;
-    f.step = step;
-    f.beta1 = h->p.beta1;
-    f.beta2 = h->p.beta2;
-    f.eps = (float)h->p.eps;
-    hipLaunchKernelGGL(finish_kernel<true>, dim3(fb), dim3(256), 0, st, f);
+    a.ctl = h->ctl;
+    a.step = step;
+    a.beta1 = h->p.beta1;
+    a.beta2 = h->p.beta2;
+    a.eps = (float)h->p.eps;
+    hipLaunchKernelGGL(grad_kernel<true>, dim3(GRAD_BLOCKS), dim3(GT), 0, st, a);
   } else {
-    hipLaunchKernelGGL(finish_kernel<false>, dim3(fb), dim3(256), 0, st, f);
+    hipLaunchKernelGGL(grad_kernel<false>, dim3(GRAD_BLOCKS), dim3(GT), 0, st, a);
   }
   CL_HIP(hipGetLastError());
   return LAT_OK;
@@ -1012,7 +1055,7 @@ extern "C" int surrogate_train_epoch(surrogate_t* h, const float* dev_x, const f
   auto record = [&]() -> int {
     for (int64_t s = 0; s < steps; ++s) {
       const int ns = (int)std::min<int64_t>(h->B, n - s * h->B);
-      int rc = train_step(h, dev_x, dev_t, dev_perm + s * h->B, ns, h->G, h->losses + s, true, (int)s);
+      int rc = train_step(h, dev_x, dev_t, dev_perm + s * h->B, ns, nullptr, h->losses + s, true, (int)s);
       if (rc) return rc;
     }
     hipLaunchKernelGGL(ctl_advance, dim3(1), dim3(64), 0, h->stream, h->ctl, (int)steps);
