@@ -101,6 +101,16 @@ __device__ __forceinline__ f4 mma(bf16x8 a, bf16x8 b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
+// BF16 weight copies lie as the products read them: a wave's fragment of 16
+// outputs and 32 inputs is 1 KB on end (lane l's eight values at 8 l), the
+// fragments of 16 outputs follow each other.  Place of output o, input i of K.
+// (In rows of K a fragment is sixteen 64-byte pieces, half a cache line each: a
+// block that reads a hidden layer's 128 KB waited 3.2 us for it.)
+constexpr int FRAG = 512;
+__device__ __forceinline__ int wpos(int o, int i, int K) {
+  return (o / 16 * (K / 32) + i / 32) * FRAG + ((i % 32) / 8 * 16 + o % 16) * 8 + i % 8;
+}
+
 // normalisation constants on the device
 struct Norm {
   float in_shift[NIN], in_scale[NIN], out_shift[NOUT], out_scale[NOUT], enc_freq[NIN];
@@ -154,6 +164,11 @@ __device__ __forceinline__ void block_features(const float* X, const Norm* nm, i
 // weight-gradient products need (h_l, da_l, BF16) and per-block partial
 // sums of the bias gradients, of the first layer's weight gradient and of the
 // loss.
+//
+// Bound by latency (one block a CU at a batch of 2048 rows, each layer waits for
+// the one before): each layer's weights are requested while the previous layer's
+// activations are formed.  2048 rows: 19 us, 16384 rows 63 us; with row-major
+// weights requested in place 29 and 103.
 // ---------------------------------------------------------------------------
 constexpr int RB = 16;          // batch rows per block of the fused step kernel
 constexpr int LDY = NOUT + 8;   // LDS pitch of dL/dy (BF16)
@@ -185,33 +200,31 @@ __device__ __forceinline__ float col_sum16(float v) {
   return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
-// one 16 x (16 CT) slab of C = A Bt^T: A is the block's 16 rows in LDS (pitch
-// lda), Bt rows col0 .. col0 + 16 CT - 1 in global memory (pitch ldb),
-// K = 32 NK.  All weight fragments are requested before the first product, so
-// the wave waits for memory once per layer instead of once per 32-deep step.
+// one 16 x 16 tile of C = A Bt^T, K = 32 NK: A is the block's 16 rows in LDS
+// (pitch lda), Bt the fragments of the wave's 16 columns, which it has requested
+// before (while the previous layer's activations were formed)
 constexpr int CT = 1;  // 16-column tiles per wave
 template <int NK>
-__device__ __forceinline__ void slab16(const bf16_t* As, int lda, const bf16_t* __restrict__ Bt, int ldb,
-                                       int col0, int lane, f4 (&acc)[CT]) {
-  const int r16 = lane & 15, kq = (lane >> 4) * 8;
+struct Weights {
+  bf16x8 b[NK];
+  __device__ __forceinline__ Weights() {}
+  __device__ __forceinline__ Weights(const bf16_t* __restrict__ W, int tile, int lane) { request(W, tile, lane); }
+  __device__ __forceinline__ void request(const bf16_t* __restrict__ W, int tile, int lane) {
+    const bf16_t* p = W + (size_t)tile * NK * FRAG + 8 * lane;
 #pragma unroll
-  for (int ct = 0; ct < CT; ++ct) acc[ct] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-  const bf16_t* pb = Bt + (size_t)(col0 + r16) * ldb + kq;
-  bf16x8 b[NK][CT];
+    for (int s = 0; s < NK; ++s) b[s] = load8(p + FRAG * s);
+  }
+  __device__ __forceinline__ f4 times(const bf16_t* As, int lda, int lane) const {
+    const int r16 = lane & 15, kq = (lane >> 4) * 8;
+    f4 acc = f4{0.0f, 0.0f, 0.0f, 0.0f};
+    bf16x8 a[NK];
 #pragma unroll
-  for (int s = 0; s < NK; ++s)
+    for (int s = 0; s < NK; ++s) a[s] = load8(As + r16 * lda + 32 * s + kq);
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) b[s][ct] = load8(pb + (size_t)ct * 16 * ldb + 32 * s);
-  bf16x8 a[NK];
-#pragma unroll
-  for (int s = 0; s < NK; ++s) a[s] = load8(As + r16 * lda + 32 * s + kq);
-  // keep the scheduler from sinking the loads back between the products
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int s = 0; s < NK; ++s)
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct) acc[ct] = mma(a[s], b[s][ct], acc[ct]);
-}
+    for (int s = 0; s < NK; ++s) acc = mma(a[s], b[s], acc);
+    return acc;
+  }
+};
 
 // four rows i0 .. i0+3 of unit j into a block's [units][RB] copy
 __device__ __forceinline__ void store_t4(bf16_t* Ht, int j, int i0, const float (&v)[4]) {
@@ -237,22 +250,33 @@ __global__ __launch_bounds__(64 * NWAVE) void step_rows_kernel(RowArgs g) {
   };
   auto blk = [&](bf16_t* p, int width) { return p + (size_t)rb * width * RB; };
 
+  constexpr int KH = WID / 32, KO = NOUT / 32;
+  // requested ahead of their use: the first two layers' weights and, behind the
+  // features' inputs (loads return in order), the targets
+  const Weights<KH> w2(g.W2b, w, lane);
+  bf16x8 w1[NFEAT / 8];
+#pragma unroll
+  for (int c = 0; c < NFEAT / 8; ++c) w1[c] = load8(g.W1b + NFEAT * j + 8 * c);
+  const float bj1 = g.b1[j];
   block_features<RB, 64 * NWAVE>(g.X, g.nm, t, row_of, xs);
+  float tv[4];
+  if (w < NOUT / 16) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int64_t src = row_of(rq + e);
+      tv[e] = src >= 0 ? g.T[src * NOUT + j] : 0.0f;
+    }
+  }
   __syncthreads();
   // layer 1 (K = NFEAT, plain FMA); padding rows (past nvalid) have zero features
   float a1[4], a2[4], a3[4];
   {
     float wf[NFEAT], hv[4];
 #pragma unroll
-    for (int c = 0; c < NFEAT; c += 8) {
-      const bf16x8 v = load8(g.W1b + NFEAT * j + c);
-#pragma unroll
-      for (int m = 0; m < 8; ++m) wf[c + m] = (float)v[m];
-    }
-    const float bj = g.b1[j];
+    for (int c = 0; c < NFEAT; ++c) wf[c] = (float)w1[c / 8][c % 8];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      float a = bj;
+      float a = bj1;
 #pragma unroll
       for (int c = 0; c < NFEAT; ++c) a = fmaf(xs[rq + e][c], wf[c], a);
       a1[e] = a;
@@ -264,40 +288,37 @@ __global__ __launch_bounds__(64 * NWAVE) void step_rows_kernel(RowArgs g) {
   __syncthreads();
 
   // hidden layers 2 and 3: a = h W^T + b, h' = BF16(GELU(a))
-  auto hidden = [&](const bf16_t* src, bf16_t* dst, const bf16_t* W, const float* bias, bf16_t* Ht, float (&av)[4]) {
-    f4 acc[CT];
-    slab16<WID / 32>(src, LDH, W, WID, 16 * w, lane, acc);
-    const float bj = bias[j];
+  auto hidden = [&](const f4& acc, bf16_t* dst, float bj, bf16_t* Ht, float (&av)[4]) {
     float hv[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      av[e] = acc[0][e] + bj;
+      av[e] = acc[e] + bj;
       hv[e] = gelu(av[e]);
       dst[(rq + e) * LDH + j] = to_bf16(hv[e]);
     }
     store_t4(blk(Ht, WID), j, rq, hv);
     __syncthreads();
   };
-  hidden(HA, HB, g.W2b, g.b2, g.H2t, a2);
-  hidden(HB, HA, g.W3b, g.b3, g.H3t, a3);
+  const float b2 = g.b2[j], b3 = g.b3[j];
+  f4 acc = w2.times(HA, LDH, lane);
+  const Weights<KH> w3(g.W3b, w, lane);
+  hidden(acc, HB, b2, g.H2t, a2);
+  acc = w3.times(HB, LDH, lane);
+  Weights<KH> w4;
+  if (w < NOUT / 16) w4.request(g.W4b, w, lane);
+  const Weights<KO> w4t(g.W4t, w, lane);
+  hidden(acc, HA, b3, g.H3t, a3);
 
   // output layer, loss and dL/dy = 2 (y - t) / (n NOUT) in normalised units;
   // waves 0-3 own outputs 16w .. 16w+15
   if (w < NOUT / 16) {
-    f4 acc[CT];
-    float tv[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int64_t src = row_of(rq + e);
-      tv[e] = src >= 0 ? g.T[src * NOUT + j] : 0.0f;
-    }
-    slab16<WID / 32>(HA, LDH, g.W4b, WID, 16 * w, lane, acc);
+    acc = w4.times(HA, LDH, lane);
     const float bj = g.b4[j], sh = g.nm->out_shift[j], sc = g.nm->out_scale[j];
     double lsum = 0.0;
     float cs = 0.0f, dv[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const float y = acc[0][e] + bj;
+      const float y = acc[e] + bj;
       float dy = 0.0f;
       if (r0 + rq + e < g.nvalid) {
         const float tn = (tv[e] - sh) * sc;
@@ -322,14 +343,12 @@ __global__ __launch_bounds__(64 * NWAVE) void step_rows_kernel(RowArgs g) {
 
   // backward through layers 4 -> 3 -> 2 (da_l = (da_{l+1} W_{l+1}) GELU'(a_l)) and 2 -> 1
   float da[4];
-  auto back = [&](auto nk, const bf16_t* src, int lds, const bf16_t* Wt, const float (&av)[4], float* bp) {
-    constexpr int NK = decltype(nk)::value;
-    f4 acc[CT];
-    slab16<NK>(src, lds, Wt, 32 * NK, 16 * w, lane, acc);
+  const Weights<KH> w3t(g.W3t, w, lane);
+  auto back = [&](const float (&av)[4], float* bp) {
     float c0 = 0.0f;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      da[e] = acc[0][e] * gelu_grad(av[e]);
+      da[e] = acc[e] * gelu_grad(av[e]);
       c0 += da[e];
     }
     c0 = col_sum16(c0);
@@ -341,11 +360,15 @@ __global__ __launch_bounds__(64 * NWAVE) void step_rows_kernel(RowArgs g) {
     store_t4(blk(Dt, WID), j, rq, da);
     __syncthreads();
   };
-  back(std::integral_constant<int, NOUT / 32>{}, DY, LDY, g.W4t, a3, g.bp3);
+  acc = w4t.times(DY, LDY, lane);
+  back(a3, g.bp3);
   hand_on(HB, g.D3t);
-  back(std::integral_constant<int, WID / 32>{}, HB, LDH, g.W3t, a2, g.bp2);
+  acc = w3t.times(HB, LDH, lane);
+  const Weights<KH> w2t(g.W2t, w, lane);
+  back(a2, g.bp2);
   hand_on(HA, g.D2t);
-  back(std::integral_constant<int, WID / 32>{}, HA, LDH, g.W2t, a1, g.bp1);
+  acc = w2t.times(HA, LDH, lane);
+  back(a1, g.bp1);
   // first layer's weight gradient, summed over the block's rows (rows e of this
   // lane, then across lanes); four features at a time, each quarter of the wave
   // stores one
@@ -378,16 +401,16 @@ __device__ __forceinline__ void store_copies(int p, float v, const WCopies& c) {
     c.W1b[p] = b;
   } else if (p >= OW2 && p < OB2) {
     const int e = p - OW2, o = e / WID, i = e % WID;
-    c.W2b[e] = b;
-    c.W2t[i * WID + o] = b;
+    c.W2b[wpos(o, i, WID)] = b;
+    c.W2t[wpos(i, o, WID)] = b;
   } else if (p >= OW3 && p < OB3) {
     const int e = p - OW3, o = e / WID, i = e % WID;
-    c.W3b[e] = b;
-    c.W3t[i * WID + o] = b;
+    c.W3b[wpos(o, i, WID)] = b;
+    c.W3t[wpos(i, o, WID)] = b;
   } else if (p >= OW4 && p < OB4) {
     const int e = p - OW4, o = e / WID, i = e % WID;
-    c.W4b[e] = b;
-    c.W4t[i * NOUT + o] = b;
+    c.W4b[wpos(o, i, WID)] = b;
+    c.W4t[wpos(i, o, NOUT)] = b;
   }
 }
 
@@ -407,7 +430,7 @@ struct WgradProduct {
   const bf16_t* A;   // [R][M][RB]
   const bf16_t* Bt;  // [R][WID][RB]
   int M, op;         // rows of the product, its place in the parameter vector
-  bf16_t *W, *Wt;    // BF16 copies [M][WID] and [WID][M]
+  bf16_t *W, *Wt;    // BF16 copies, M outputs of WID inputs and the transpose
 };
 
 struct GradArgs {
@@ -446,7 +469,9 @@ __global__ void ctl_advance(TrainCtl* c, int nsteps) {
 //     waves load 128 blocks' partials side by side, the first wave adds them in
 //     order;
 //   - the loss.
-// At the training batch of 2048 rows that is one block per CU.
+// At the training batch of 2048 rows that is one block per CU, 8.4 us; a product
+// kernel with the splits' partials through memory and a kernel of one thread per
+// parameter took 27.
 // ---------------------------------------------------------------------------
 constexpr int GT = 512, GW = GT / 64, TILE = 32, TP = TILE + 4;  // threads, waves, tile, its LDS pitch
 constexpr int SUMR = 128;                                       // partials a block adds between barriers
@@ -562,15 +587,16 @@ __global__ __launch_bounds__(GT) void grad_kernel(GradArgs g) {
 #pragma unroll
       for (int q = 0; q < EL; ++q) {
         const int e = t + GT * q, i = e / TILE, j = e % TILE;
-        const bf16_t v = to_bf16(adam(g, c, pe[q], sum[q], m0[q], v0[q], w0[q]));
-        P.W[(row0 + i) * WID + col0 + j] = v;
-        tr[i][j] = v;
+        tr[i][j] = to_bf16(adam(g, c, pe[q], sum[q], m0[q], v0[q], w0[q]));
       }
       __syncthreads();
+      // a tile is two fragments of either copy
+      static_assert(TILE == 32, "one 32-deep fragment");
 #pragma unroll
       for (int q = 0; q < EL; ++q) {
-        const int e = t + GT * q, j = e / TILE, i = e % TILE;
-        P.Wt[(size_t)(col0 + j) * M + row0 + i] = tr[i][j];
+        const int e = t + GT * q, f = e / FRAG, x = e % FRAG, o = 16 * f + x / 8 % 16, i = x / 128 * 8 + x % 8;
+        P.W[((row0 / 16 + f) * (WID / 32) + col0 / 32) * FRAG + x] = tr[o][i];
+        P.Wt[((col0 / 16 + f) * (M / 32) + row0 / 32) * FRAG + x] = tr[i][o];
       }
     }
     return;
@@ -642,10 +668,10 @@ __global__ __launch_bounds__(GT) void grad_kernel(GradArgs g) {
 //
 // Bound by vector instruction issue: a GELU is 22 instructions and two
 // transcendentals, 768 of them a row, the first layer 6144 multiply-adds a row
-// (47 of 63 us at 65536 rows; the matrix products alone would take 17).  The
-// kernel before (one thread of four forming all features of a row, one unit per
-// thread in the first layer, lanes holding one unit of four rows and storing
-// them as 16-bit words, integer rounding to BF16, two blocks a CU): 88 us.
+// (47 of 61 us at 65536 rows; the matrix products alone would take 17).  With
+// one thread of four forming all features of a row, one unit per thread in the
+// first layer, lanes holding one unit of four rows and storing them as 16-bit
+// words, integer rounding to BF16, row-major weights and two blocks a CU: 88 us.
 // ---------------------------------------------------------------------------
 template <int RT, int NW>
 __global__ __launch_bounds__(64 * NW, NW == 16 ? 4 : 3) void predict_kernel(const float* __restrict__ X, int64_t n,
@@ -711,12 +737,12 @@ __global__ __launch_bounds__(64 * NW, NW == 16 ? 4 : 3) void predict_kernel(cons
     for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-    const bf16_t* wb = W + (size_t)(16 * CT * w + r16) * WID + kq;
+    const bf16_t* wb = W + (size_t)CT * w * (WID / 32) * FRAG + 8 * lane;
 #pragma unroll CT == 1 ? 8 : 2
     for (int kk = 0; kk < WID; kk += 32) {
       bf16x8 a[RT], b[CT];
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct) b[ct] = load8(wb + (size_t)ct * 16 * WID + kk);
+      for (int ct = 0; ct < CT; ++ct) b[ct] = load8(wb + (ct * (WID / 32) + kk / 32) * FRAG);
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) a[rt] = load8(&H[(rt * 16 + r16) * LDH + kk + kq]);
 #pragma unroll
@@ -744,10 +770,10 @@ __global__ __launch_bounds__(64 * NW, NW == 16 ? 4 : 3) void predict_kernel(cons
   f4 acc[RT];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) acc[rt] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-  const bf16_t* wb = c.W4b + (size_t)(16 * w + r16) * WID + kq;
+  const bf16_t* wb = c.W4b + (size_t)w * (WID / 32) * FRAG + 8 * lane;
 #pragma unroll CT == 1 ? 8 : 2
   for (int kk = 0; kk < WID; kk += 32) {
-    const bf16x8 b = load8(wb + kk);
+    const bf16x8 b = load8(wb + kk / 32 * FRAG);
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) acc[rt] = mma(b, load8(&H[(rt * 16 + r16) * LDH + kk + kq]), acc[rt]);
   }
@@ -1113,15 +1139,16 @@ extern "C" int surrogate_predict(surrogate_t* h, const float* dev_x, int64_t n, 
     hipLaunchKernelGGL(kernel, dim3((unsigned)((n + rows - 1) / rows)), dim3(threads), 0, h->stream, dev_x, n, h->nm, c,
                        h->P + OB1, h->P + OB2, h->P + OB3, h->P + OB4, dev_y);
   };
-  // The rows a block takes: as few as give every CU at most one block of sixteen
-  // waves, whose wave has a single tile of units per layer (up to 4096 rows 14-16
-  // us with 16 rows a block, 27 with 64; up to 8192 20 us with 32 against 27; at
-  // 16384 37 against 30).  From there on four waves with four tiles each,
-  // which read a row's activations from LDS a quarter as often and leave room for
-  // four blocks on a CU (65536 rows: 63 us, sixteen waves 102, eight 76).
+  // Rows per block: 16 as long as every CU gets at most one block of sixteen
+  // waves, whose wave has a single tile of units per layer (one row 8.1 us, 4096
+  // rows 9.9; 32-row blocks 12.2, 64-row ones 22.9), then 32 (8192 rows 13.8 us,
+  // 14.8 with 16 and 23.6 with 64; 16384 rows 24.5, 27.1 and 26.0).  Beyond that
+  // four waves with four tiles each, which read a row's activations from LDS a
+  // quarter as often and leave room for four blocks on a CU (32768 rows 37.7 us,
+  // 32-row blocks 45.0; 65536 rows 61 us).
   constexpr int CUS = 256;
   if (n <= 16 * CUS) launch(predict_kernel<1, 16>, 16, 1024);
-  else if (n <= 32 * CUS) launch(predict_kernel<2, 16>, 32, 1024);
+  else if (n <= 64 * CUS) launch(predict_kernel<2, 16>, 32, 1024);
   else launch(predict_kernel<4, 4>, 64, 256);
   CL_HIP(hipGetLastError());
   return LAT_OK;

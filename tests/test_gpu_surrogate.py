@@ -87,7 +87,7 @@ def test_predict_matches_oracle_forward(n):
     assert np.linalg.norm(d) < 1e-4 * np.linalg.norm(yn), np.linalg.norm(d) / np.linalg.norm(yn)
 
 
-@pytest.mark.parametrize("n", [15, 17, 4096, 4097, 8192, 8193, 16400])
+@pytest.mark.parametrize("n", [15, 17, 4096, 4097, 8192, 8193, 16384, 16400])
 def test_predict_gives_a_row_the_same_bits_in_any_batch(n):
     """Blocks of 16, 32 and 64 rows and the last, partial one: a row's answer
     depends neither on the batch it comes in nor on its place there, and rows
