@@ -90,6 +90,49 @@ __device__ __forceinline__ double apow(double a, double p) {
   }
   return pow(a, p);
 }
+// Sum over the 64 lanes, the same in every lane: v + v[lane ^ 32], then ^ 16, 8,
+// 4, 2, 1.  The exchanges are lane swaps and DPP moves, vector instructions (a
+// shuffle is a trip through LDS, and the six of each sum are a chain on the
+// critical path of every pass); within a row a rotation by 4 reads lane ^ 4's
+// value, since by then lanes 8 apart agree.  (A pass of the FP32 64^3 two-field
+// lattice 7.8 us against 9.1 with shuffles, 32^3 7.4 against 8.5, U(1) 64^3 20.4
+// against 22.6.)
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (uint32_t)u, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+template <bool HALVES>
+__device__ __forceinline__ double swap_sum(double v) {
+  typedef uint32_t u2 __attribute__((__vector_size__(8)));
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t a = (uint32_t)u, b = (uint32_t)(u >> 32);
+  u2 lo, hi;
+  if constexpr (HALVES) {
+    lo = __builtin_bit_cast(u2, __builtin_amdgcn_permlane32_swap(a, a, false, false));
+    hi = __builtin_bit_cast(u2, __builtin_amdgcn_permlane32_swap(b, b, false, false));
+  } else {
+    lo = __builtin_bit_cast(u2, __builtin_amdgcn_permlane16_swap(a, a, false, false));
+    hi = __builtin_bit_cast(u2, __builtin_amdgcn_permlane16_swap(b, b, false, false));
+  }
+  return __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]) +
+         __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {  // the same lane for all
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, lane), hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), lane);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  v = swap_sum<true>(v);
+  v = swap_sum<false>(v);
+  v += dpp_move<0x128>(v);  // row_ror:8
+  v += dpp_move<0x124>(v);  // row_ror:4
+  v += dpp_move<0x4e>(v);   // quad_perm [2, 3, 0, 1]
+  return v + dpp_move<0xb1>(v);  // quad_perm [1, 0, 3, 2]
+}
 template <typename T>
 __device__ __forceinline__ Coef<T> ucoef(double v) {
   const Coef<T> c = coef<T>(v);

@@ -333,8 +333,7 @@ __global__ __launch_bounds__(64 * NWAVE) void step_rows_kernel(RowArgs g) {
     store_t4(blk(g.DYt, NOUT), j, rq, dv);
     cs = col_sum16(cs);
     if (lane < 16) g.bp4[(size_t)rb * NOUT + j] = cs;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) lsum += __shfl_xor(lsum, o);
+    lsum = wave_sum(lsum);
     if (lane == 0) lred[w] = lsum;
   }
   static_assert(NOUT / 16 == 4, "loss partials of four waves");

@@ -50,12 +50,6 @@ struct Acc {
   static constexpr int N = FULL ? 5 * NF + 3 : 4;
 };
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
 // dV/dphi_f with the couplings as hi + lo pairs (no coherent rounding of them)
 template <typename T, int NF>
 __device__ __forceinline__ T dpot(int f, const T (&p)[NF], const Coef<T>& m2_0, const Coef<T>& m2_1,

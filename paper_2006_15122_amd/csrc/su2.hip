@@ -114,12 +114,6 @@ struct Su2Args {
   DevState* st;
 };
 
-__device__ __forceinline__ double wsum64(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
 // per-block sums of 256 threads' accumulators (waves in order) into the block's record
 template <int NACC>
 __device__ void su2_block_partials(double (&acc)[NACC], double* partials) {
@@ -127,7 +121,7 @@ __device__ void su2_block_partials(double (&acc)[NACC], double* partials) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
 #pragma unroll
   for (int k = 0; k < NACC; ++k) {
-    const double s = wsum64(acc[k]);
+    const double s = wave_sum(acc[k]);
     if (lane == 0) red[wv][k] = s;
   }
   __syncthreads();
@@ -692,7 +686,7 @@ __global__ __launch_bounds__(TZ* TY, WPE) void su2_pass_kernel(Su2PassArgs<T> A)
   // the tile's sums: waves in order
 #pragma unroll
   for (int k = 0; k < NACC; ++k) {
-    const double s = wsum64(acc[k]);
+    const double s = wave_sum(acc[k]);
     if ((tid & 63) == 0) red[tid >> 6][k] = s;
   }
   __syncthreads();
@@ -725,10 +719,12 @@ __device__ bool su2_reduce_records(const double* rec, int nb, double (&S)[NACC])
   __syncthreads();
   if (tid >= 64) return false;
   double v = 0.0;
-  if (tid < NACC)
-    for (int j = tid; j < NL; j += NACC) v += part[j];
+  if (tid < NACC) {
 #pragma unroll
-  for (int k = 0; k < NACC; ++k) S[k] = __shfl(v, k, 64);
+    for (int l = 0; l < NL / NACC; ++l) v += part[l * NACC + tid];
+  }
+#pragma unroll
+  for (int k = 0; k < NACC; ++k) S[k] = lane_value(v, k);
   return tid == 0;
 }
 
@@ -894,7 +890,7 @@ __global__ __launch_bounds__(1024) void su2_gauss_finish_kernel(const double* pa
   for (int b = tid; b < nblocks; b += 1024)
     for (int k = 0; k < kSu2GaussAcc; ++k) tot[k] += partials[(size_t)b * kSu2GaussAcc + k];
   for (int k = 0; k < kSu2GaussAcc; ++k) {
-    const double v = wsum64(tot[k]);
+    const double v = wave_sum(tot[k]);
     if (lane == 0) red[wv][k] = v;
   }
   __syncthreads();

@@ -60,12 +60,6 @@ constexpr int kU1Acc = 11, kU1StepAcc = 5;
 // the workspace reserves 16 FP64 partials per 256-site block
 static_assert(kU1Acc <= 16, "U(1) partials exceed the reserved region");
 
-__device__ __forceinline__ double wsum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
 // Per-block sums of NT threads' accumulators (waves in order) into the
 // block's record.
 template <int NT, int NACC>
@@ -75,7 +69,7 @@ __device__ void u1_block_partials(double (&acc)[NACC], double* partials) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
 #pragma unroll
   for (int k = 0; k < NACC; ++k) {
-    const double s = wsum(acc[k]);
+    const double s = wave_sum(acc[k]);
     if (lane == 0) red[wv][k] = s;
   }
   __syncthreads();
@@ -118,7 +112,7 @@ __global__ __launch_bounds__(1024) void u1_gauss_finish_kernel(const double* par
   for (int b = tid; b < nblocks; b += 1024)
     for (int k = 0; k < 4; ++k) tot[k] += partials[(size_t)b * 4 + k];
   for (int k = 0; k < 4; ++k) {
-    const double s = wsum(tot[k]);
+    const double s = wave_sum(tot[k]);
     if (lane == 0) red[wv][k] = s;
   }
   __syncthreads();
@@ -628,8 +622,8 @@ __device__ void u1_finish_state(const U1PassArgs<T>& A, const PassDesc& pd, cons
 }
 
 
-// Sums of NB partial records in block order by one block of NT threads
-// (strided per thread, then waves in order); thread 0 returns them in S.
+// Sums of nb partial records in a fixed order by one block of NT threads;
+// thread 0 returns them in S.
 template <int NACC, int NT>
 __device__ bool u1_reduce_partials(const double* partials, int nb, double (&S)[NACC]) {
   // Thread t < NL reads doubles t, t + NL, t + 2 NL, ... of the nb records
@@ -652,10 +646,12 @@ __device__ bool u1_reduce_partials(const double* partials, int nb, double (&S)[N
   __syncthreads();
   if (tid >= 64) return false;
   double v = 0.0;
-  if (tid < NACC)
-    for (int j = tid; j < NL; j += NACC) v += red[j];
+  if (tid < NACC) {
 #pragma unroll
-  for (int k = 0; k < NACC; ++k) S[k] = __shfl(v, k, 64);
+    for (int l = 0; l < NL / NACC; ++l) v += red[l * NACC + tid];
+  }
+#pragma unroll
+  for (int k = 0; k < NACC; ++k) S[k] = lane_value(v, k);
   return tid == 0;
 }
 
