@@ -30,12 +30,15 @@ struct Tiling {
 // places empty, seven fill them, 178 -> 160 us a pass; full-row scalar tiles at
 // 320^3 213 -> 206, at 224^3 95 -> 79.)  Blocks of fewer than `least` planes are
 // not split further: there the two planes a block reads beyond its own cost
-// more than empty places (96^3 U(1) 45.6 us against 38).
+// more than empty places (96^3 U(1) 45.6 us against 38), unless every block
+// then still has a CU to itself (32^3 U(1) 21.3 -> 13.1 us a pass, FP64 two
+// fields 10.0 -> 7.1).
+constexpr int kCUs = 256;
 inline int x_blocks(int N, int xc, int tiles, int slots, double extra, int least) {
   const int n0 = N / xc;
   int best = n0;
   double cost = 1e30;
-  for (int n = n0; n == n0 || n * least <= N; ++n) {
+  for (int n = n0; n == n0 || n * least <= N || (n <= N && tiles * n <= kCUs); ++n) {
     const double c = (double)((tiles * n + slots - 1) / slots) * ((double)((N + n - 1) / n) + extra);
     if (c < 0.98 * cost) { cost = c; best = n; }
   }

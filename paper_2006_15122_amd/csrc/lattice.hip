@@ -97,15 +97,15 @@ static void layout(const lattice_params* p, size_t* off_part, size_t* off_part2,
   // per-block FP64 partials: scalar passes write at most 32 per tile of at
   // least 32 x 8 x 4 sites; the U(1) site kernels write up to 16 per block of
   // 256 sites
-  const size_t part_doubles = std::max((size_t)mb * 32, (size_t)(V / 256) * 16);
+  const size_t part_doubles = std::max((size_t)std::max<int64_t>(mb, kCUs) * 32, (size_t)(V / 256) * 16);
   size_t o = align_up(2 * sizeof(DevState), 256);
   *off_part = o;
   o = align_up(o + part_doubles * sizeof(double), 256);
   // every other pass of a chain writes its records here: at most mb blocks
-  // (tiles of at least 1024 sites) of 4 scalar or 11 U(1) sums; SU(2) x U(1)
-  // blocks take 256 sites or more and write 7
+  // (tiles of at least 1024 sites) or one per CU, of 4 scalar or 11 U(1) sums; SU(2) x U(1)
+  // blocks take 256 sites or more, or are one per CU, and write 7
   *off_part2 = o;
-  o = align_up(o + (is_su2(*p) ? (size_t)(V / 256) * 16 : (size_t)mb * 16) * sizeof(double), 256);
+  o = align_up(o + (size_t)std::max<int64_t>(is_su2(*p) ? V / 256 : mb, kCUs) * 16 * sizeof(double), 256);
   *off_spec = o;
   o = align_up(o + (size_t)(spec_blocks((int)N) + 2) * spec_bins((int)N) * 24, 256);
   *off_buf0 = o;
@@ -710,11 +710,10 @@ void default_tiling(lattice* h) {
   }
   // Below 128^3 (where no tuner runs) a pass is latency: many blocks that march
   // few planes, down to the 1024 sites a block needs for its record, up to 512
-  // blocks (scalar FP32 64^3: 9.1 us a pass with two planes a block, 21.5 with
-  // sixteen; 96^3: 12.8 with four, 14.6 with two; U(1) 64^3: 22.9 with two,
-  // 29.4 with four; 96^3: 37.9 with eight, 46.1 with four).  FP64 two-field
-  // lattices take full rows (32^3, 64^3, 96^3: 9.8, 9.8 and 18.9 us against
-  // 12.2, 13.1 and 27.4 for the best general tile).
+  // blocks (scalar FP32 64^3: 8.0 us a pass with two planes a block, 9.6 with
+  // four; 96^3: 11.6 with four, 12.8 with two; U(1) 64^3: 20.7 with two, 27.2
+  // with four; 96^3: 34.3 with eight, 42.5 with four).  FP64 two-field lattices
+  // take full rows (64^3: 9.2 us against 11.8 for the best general tile).
   const bool rows = !is_u1(h->p) && h->p.precision == LAT_FP64 && h->p.nf == 2;
   Tiling t;
   if (rows) t = Tiling{N, N == 96 ? 4 : 8, 1, 1};

@@ -52,15 +52,16 @@ static void* scratch_ptr() {
 // Scalar: one observation pass on its fixed tile, 5 nf + 3 FP64 sums per
 // tile.  U(1): the Gauss residual (4 per 256 sites),
 // then the pass on the lattice's tile (11 per tile).  SU(2) x U(1): the Gauss
-// residuals and the pass, at most 16 per 256 sites.
+// residuals and the pass, at most 16 per 256 sites (or 256 records).
 static size_t energy_partial_bytes(const lattice* h) {
   const size_t N = (size_t)h->p.N, V = N * N * N;
-  if (is_su2(h->p)) return V / 256 * 16 * sizeof(double);
+  if (is_su2(h->p)) return std::max(V / 256, (size_t)kCUs) * 16 * sizeof(double);
   if (is_u1(h->p)) {
     const Tiling& t = h->tile;
     const size_t tiles = (N / (size_t)t.tz) * (N / (size_t)(t.by * t.ry)) * (N / (size_t)t.xc);
-    // (a pass may take more blocks along x than N / xc, of 16 planes or more)
-    return std::max(V / 256 * 4, std::max(tiles, V / 4096) * 11) * sizeof(double);
+    // (a pass may take more blocks along x than N / xc, of 16 planes or more or
+    // as many as there are CUs)
+    return std::max(V / 256 * 4, std::max({tiles, V / 4096, (size_t)kCUs}) * 11) * sizeof(double);
   }
   return (size_t)scalar_obs_blocks(h->p.N) * (size_t)(5 * h->p.nf + 3) * sizeof(double);
 }

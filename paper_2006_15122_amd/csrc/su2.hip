@@ -957,11 +957,11 @@ static int su2_pass_t(lattice* h, const PassDesc& pd, PassChain* chain) {
   constexpr int NT = Su2Tile<TZ, TY>::NT;
   const int tiles = (N / TZ) * (N / TY);
   // every block pays about three planes' work before its first (planes x0-1,
-  // x0, x0+1 and what x0-1 hands on); at least 256 sites per block, the record
-  // regions' size
+  // x0, x0+1 and what x0-1 hands on); at least 256 sites per block or one per CU,
+  // the record regions' size
   A.nx = x_blocks(N, N, tiles, 256 * (4 * WPE / (NT / 64)), 3.0, (256 + NT - 1) / NT);
   const int nb = tiles * A.nx;
-  if ((int64_t)nb * 256 > (int64_t)N * N * N) { set_error("SU(2) pass: records exceed their region"); return LAT_EINVAL; }
+  if (nb > std::max<int64_t>((int64_t)N * N * N / 256, kCUs)) { set_error("SU(2) pass: records exceed their region"); return LAT_EINVAL; }
   A.swizzle = nb % 8 == 0 ? 1 : 0;
   DevState* slot[2] = {h->st, h->st2};
   if (chain) {
