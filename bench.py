@@ -24,7 +24,7 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0           # MI355X HBM3E, GB/s
 # (tz, by, ry) shapes the library's autotuner times for FP32 two-field lattices
 TUNER_SHAPES = ((64, 4, 2), (64, 8, 2), (32, 8, 2), (128, 8, 2), (256, 4, 2), (128, 4, 2),
-                (128, 16, 1), (256, 8, 1), (512, 4, 1))
+                (256, 4, 1), (256, 8, 1))
 BYTES_PER_SITE_VV2_NF2_FP32 = 32  # read phi, chi, pi_phi, pi_chi; write the same (FP32)
 
 
@@ -33,7 +33,7 @@ def _pass_kernel_name(tile) -> str:
     tz = N, four sites per lane) or the general tile."""
     tz, by, ry = tile[:3]
     if ry == 1:
-        return "scalar_rows_kernel<float, 4, 2, %d, %d>" % (tz // 4, by)
+        return "scalar_rows_kernel<float, 4, 2, %d, 0>" % by
     return "scalar_pass_kernel<float, 2, false, %d, %d, %d>" % (tz, by, ry)
 
 
@@ -42,7 +42,7 @@ def _kernel_hash() -> str:
     out, so that a change to the code, not to its comments, marks the stored
     traffic counters as stale."""
     h = hashlib.sha256()
-    for f in ("scalar.hip", "scalar_tile.hpp", "scalar_rows.hpp", "common.hpp"):
+    for f in ("scalar.hip", "scalar_tile.hpp", "scalar_rows.hpp", "common.hpp", "internal.hpp"):
         for line in open(os.path.join(ROOT, "paper_2006_15122_amd", "csrc", f)):
             code = line.split("//", 1)[0].rstrip()
             if code:
@@ -212,10 +212,10 @@ def time_spectrum(N: int = 256, reps: int = 50) -> dict:
     del lat
     torch.cuda.empty_cache()
     # algorithmic HBM bytes per spectrum of the three line passes (complex
-    # FP64): the z pass reads the FP32 field (4) and writes the complex volume
-    # (16), the y pass reads and writes it (32), the x pass reads it (16) and
-    # bins in LDS (FP64 sums)
-    per_site = 4 + 16 + 32 + 16
+    # FP64, half the modes: the field is real): the z pass reads the FP32 field
+    # (4) and writes the half volume (8), the y pass reads and writes it (16),
+    # the x pass reads it (8) and bins in LDS (FP64 sums)
+    per_site = 4 + 8 + 16 + 8
     return {"N": N, "ms_per_spectrum": ms, "spectra_per_s": 1e3 / ms, "bytes_per_site": per_site,
             "hbm_frac": N ** 3 * per_site / (ms / 1e3) / 1e9 / HBM_PEAK_GBS}
 
@@ -387,15 +387,14 @@ def main():
                                   "bytes_per_site_update": 64, "steps": st64}
         # SU(2) x U(1) doublet, 128^3, FP32, velocity Verlet: 35 FP32 per site
         # (Phi 4, pi 4, U(1) phases 3, pi_A 3, SU(2) links 12, pi_B 9) read and
-        # written once per pass = 280 B per site-update; each pass is a drift,
-        # a kick and a finish kernel
+        # written once per pass = 280 B per site-update
         c5 = synth.config_su2u1()
         st5 = max(args.steps // 20, 10)
         ms5, _, obs5, _, k5 = time_lattice(c5, st5, 5, st5 + 1)
         n5 = c5["N"] ** 3
         extras["su2u1_128_vv2"] = {"site_updates_per_s": n5 * st5 / (ms5 / 1e3),
                                    "hbm_frac": n5 * 280 / (ms5 / (st5 + 1) / 1e3) / 1e9 / HBM_PEAK_GBS,
-                                   "ms_per_pass": ms5 / (st5 + 1), "ms_per_kick_kernel": k5,
+                                   "ms_per_pass": ms5 / (st5 + 1), "ms_per_pass_ext_events": k5,
                                    "bytes_per_site_update": 280, "steps": st5, "gauss": obs5["gauss"],
                                    "gauss_B": obs5["gauss_B"]}
         extras["batch_96"] = time_batch(max(args.steps // 10, 20))
