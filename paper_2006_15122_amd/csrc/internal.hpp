@@ -30,9 +30,9 @@ struct Tiling {
 // places empty, seven fill them, 178 -> 160 us a pass; full-row scalar tiles at
 // 320^3 213 -> 206, at 224^3 95 -> 79.)  Blocks of fewer than `least` planes are
 // not split further: there the two planes a block reads beyond its own cost
-// more than empty places (96^3 U(1) 45.6 us against 38), unless every block
-// then still has a CU to itself (32^3 U(1) 21.3 -> 13.1 us a pass, FP64 two
-// fields 10.0 -> 7.1).
+// more than empty places (96^3 U(1): 14 blocks of seven planes 32.6 us, 12 of
+// eight 34.4, 16 of six 36.2, 21 of five 43), unless every block then still has
+// a CU to itself (32^3 U(1) 21.3 -> 13.1 us a pass, FP64 two fields 10.0 -> 7.1).
 constexpr int kCUs = 256;
 inline int x_blocks(int N, int xc, int tiles, int slots, double extra, int least) {
   const int n0 = N / xc;
@@ -43,6 +43,14 @@ inline int x_blocks(int N, int xc, int tiles, int slots, double extra, int least
     if (c < 0.98 * cost) { cost = c; best = n; }
   }
   return best;
+}
+// Tile of block b of nb: blocks go to the eight XCDs in turn, tiles in contiguous
+// ranges, so that neighbouring tiles share their halo through one L2 (block
+// counts that eight does not divide had none of it: U(1) 160^3 128 -> 112 us a
+// pass, SU(2) 160^3 420 -> 378, full rows 288^3 157 -> 151).
+__device__ inline int xcd_tile(int b, int nb) {
+  const int x = b & 7;
+  return x * (nb >> 3) + min(x, nb & 7) + (b >> 3);
 }
 // block k of n along x: its first plane; (k + 1)'s is one past its last
 __host__ __device__ inline int x_first(int N, int k, int n) { return (int)((long long)k * N / n); }

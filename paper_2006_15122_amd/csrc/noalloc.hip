@@ -59,9 +59,9 @@ static size_t energy_partial_bytes(const lattice* h) {
   if (is_u1(h->p)) {
     const Tiling& t = h->tile;
     const size_t tiles = (N / (size_t)t.tz) * (N / (size_t)(t.by * t.ry)) * (N / (size_t)t.xc);
-    // (a pass may take more blocks along x than N / xc, of 16 planes or more or
+    // (a pass may take more blocks along x than N / xc, of 6 planes or more or
     // as many as there are CUs)
-    return std::max(V / 256 * 4, std::max({tiles, V / 4096, (size_t)kCUs}) * 11) * sizeof(double);
+    return std::max(V / 256 * 4, std::max({tiles, V / 1024, (size_t)kCUs}) * 11) * sizeof(double);
   }
   return (size_t)scalar_obs_blocks(h->p.N) * (size_t)(5 * h->p.nf + 3) * sizeof(double);
 }

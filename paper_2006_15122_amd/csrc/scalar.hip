@@ -213,7 +213,6 @@ hipError_t launch_scalar_pass(int fp32, int nf, const void* const* src, void* co
   const int nx = ry == 1 ? x_blocks(N, xc, N / ty, 256 * std::max(1, 12 / (N / (fp32 ? 4 : 2) * by / 64)), 2.0, 8) : 0;
   const int nblocks = (N / tz) * (N / ty) * (nx ? nx : N / xc);
   if (nblocks_out) *nblocks_out = nblocks;
-  const int swz = (swizzle && (nblocks % 8 == 0)) ? 1 : 0;
   auto fill = [&](auto& A, auto* tag) {
     using TT = std::remove_pointer_t<decltype(tag)>;
     for (int i = 0; i < 4; ++i) {
@@ -223,7 +222,7 @@ hipError_t launch_scalar_pass(int fp32, int nf, const void* const* src, void* co
     A.N = N;
     A.XC = xc;
     A.nx = nx;
-    A.swizzle = swz;
+    A.swizzle = swizzle;
     A.dx = phys[0];
     A.alpha = phys[1];
     A.fmp2 = phys[2];

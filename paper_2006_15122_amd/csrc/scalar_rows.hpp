@@ -356,7 +356,7 @@ __device__ __forceinline__ void scalar_rows(const ScalarArgs<T>& A, const int BY
 template <typename T, int W, int NF, int BY, int MODE = kRowsStep>
 __global__ __launch_bounds__(kRowsMaxThreads) void scalar_rows_kernel(ScalarArgs<T> A) {
   int bid = blockIdx.x;
-  if (A.swizzle) bid = (bid & 7) * (gridDim.x >> 3) + (bid >> 3);
+  if (A.swizzle) bid = xcd_tile(bid, gridDim.x);
   auto get_ab = [&](double& a_in, double& b_in) {
     if (A.prev.partials) {
       constexpr int NP = Acc<NF, false>::N;

@@ -444,7 +444,7 @@ __device__ __forceinline__ void scalar_tile(const ScalarArgs<T>& A, int tile, in
 template <typename T, int NF, bool FULL, int TZ, int BY, int RY>
 __global__ __launch_bounds__(TZ* BY, RY <= 4 ? 4 : 1) void scalar_pass_kernel(ScalarArgs<T> A) {
   int bid = blockIdx.x;
-  if (A.swizzle) bid = (bid & 7) * (gridDim.x >> 3) + (bid >> 3);
+  if (A.swizzle) bid = xcd_tile(bid, gridDim.x);
   auto get_ab = [&](double& a_in, double& b_in) {
     if (A.prev.partials) {
       // finish of the previous pass (stepping passes only, Acc<NF, false>)

@@ -159,7 +159,7 @@ template <typename T>
 struct Su2PassArgs {
   const T* src;  // component c at src + c N^3
   T* dst;
-  int N, nx, swizzle;  // nx blocks along x
+  int N, nx;  // nx blocks along x
   double dx, alpha, fmp2, lam, m2, e, g, wf2, h;
   int expand;
   PassDesc pd;
@@ -228,8 +228,7 @@ __global__ __launch_bounds__(TZ* TY, WPE) void su2_pass_kernel(Su2PassArgs<T> A)
   const unsigned NN = (unsigned)N * N;
   const size_t V = (size_t)NN * N;
   const int tid = threadIdx.x;
-  int bid = blockIdx.x;
-  if (A.swizzle) bid = (bid & 7) * (gridDim.x >> 3) + (bid >> 3);
+  const int bid = xcd_tile(blockIdx.x, gridDim.x);
   const int nzt = N / TZ, nyt = N / TY;
   const int z0 = (bid % nzt) * TZ, y0 = ((bid / nzt) % nyt) * TY, xb = bid / (nzt * nyt),
             x0 = x_first(N, xb, A.nx), XC = x_first(N, xb + 1, A.nx) - x0;
@@ -962,7 +961,6 @@ static int su2_pass_t(lattice* h, const PassDesc& pd, PassChain* chain) {
   A.nx = x_blocks(N, N, tiles, 256 * (4 * WPE / (NT / 64)), 3.0, (256 + NT - 1) / NT);
   const int nb = tiles * A.nx;
   if (nb > std::max<int64_t>((int64_t)N * N * N / 256, kCUs)) { set_error("SU(2) pass: records exceed their region"); return LAT_EINVAL; }
-  A.swizzle = nb % 8 == 0 ? 1 : 0;
   DevState* slot[2] = {h->st, h->st2};
   if (chain) {
     A.st = slot[chain->rd];

@@ -152,7 +152,7 @@ template <typename T>
 struct U1PassArgs {
   const T* src;  // component c at src + c N^3
   T* dst;
-  int N, nx, swizzle;  // nx blocks along x
+  int N, nx;  // nx blocks along x
   double dx, alpha, fmp2, lam, m2, e, wf2, h;
   int expand;
   PassDesc pd;
@@ -199,8 +199,7 @@ __global__ __launch_bounds__(TZ* BY) void u1_pass_kernel(U1PassArgs<T> A) {
   const int N = A.N;
   const int NN = N * N;
   const int tid = threadIdx.x, tz = tid % TZ, ty = tid / TZ;
-  int bid = blockIdx.x;
-  if (A.swizzle) bid = (bid & 7) * (gridDim.x >> 3) + (bid >> 3);
+  const int bid = xcd_tile(blockIdx.x, gridDim.x);
   const int nzt = N / TZ, nyt = N / TY;
   const int z0 = (bid % nzt) * TZ;
   const int y0 = ((bid / nzt) % nyt) * TY;
@@ -711,9 +710,8 @@ static int u1_pass_t(lattice* h, const PassDesc& pd, PassChain* chain) {
   const int tiles = (N / TZ) * (N / TY);
   A.N = N;
   // two blocks share a CU; a block reads two planes and computes one beyond its own
-  A.nx = x_blocks(N, h->tile.xc, tiles, 512, 2.5, 16);
+  A.nx = x_blocks(N, h->tile.xc, tiles, 512, 2.5, 6);
   const int nb = tiles * A.nx;
-  A.swizzle = (nb % 8 == 0) ? 1 : 0;
   A.dx = h->dx;
   A.alpha = h->p.alpha;
   A.fmp2 = h->p.fstar_over_mp * h->p.fstar_over_mp;
