@@ -667,10 +667,17 @@ __global__ __launch_bounds__(TZ* TY, WPE) void su2_pass_kernel(Su2PassArgs<T> A)
 #pragma unroll
         for (int k = 0; k < kSu2Acc; ++k) acc[k] += (double)ts[k];
       } else {
-        if (lf) { kin += kin0; ka += ka0; kb += kb0; }
-        const T ts[kSu2StepAcc] = {kin, eg, lam * r2 * r2 + m2 * r2, ka, omA, kb, omB};
+        // each term into its FP64 sum: two of them added in FP32 first would
+        // round every site of a near-homogeneous state alike, and a and b with it
+        const T ts[kSu2StepAcc] = {kin, eg, lam * r2 * r2, ka, omA, kb, omB};
 #pragma unroll
         for (int k = 0; k < kSu2StepAcc; ++k) acc[k] += (double)ts[k];
+        acc[2] += (double)(m2 * r2);
+        if (lf) {
+          acc[0] += (double)kin0;
+          acc[3] += (double)ka0;
+          acc[5] += (double)kb0;
+        }
       }
     }
 #pragma unroll

@@ -235,3 +235,66 @@ def test_su2_pass_sites_on_a_rough_state(precision, N, integ, nsteps, tol):
     # the chain's records stay in their regions: the shell geometry behind them is untouched
     after = lat.spectrum(0)
     assert np.array_equal(before["k"], after["k"]) and np.array_equal(before["count"], after["count"])
+
+
+def _scale_factor_force(cfg, e):
+    """b' = K_a at the energies e (Sec. 5.4.1 and Sec. 6.3.1)."""
+    al, a = cfg["alpha"], e["a"]
+    gauge = e["EK_A"] + e["EG_A"] + e["EK_B"] + e["EG_B"]
+    return cfg["fstar_over_mp"] ** 2 / 3.0 * a ** (1.0 + 2.0 * al) * (
+        (al - 2.0) * e["EK"] + al * e["EG"] + (al + 1.0) * e["EV"] + (al - 1.0) * gauge)
+
+
+@pytest.mark.parametrize("integ", ["lf2", "vv2"])
+@pytest.mark.parametrize("seed", [1, 2, 3])
+def test_su2_step_sums_carry_the_bits_of_the_observation_sums(integ, seed):
+    """b moves by the force of the energies that an observation of the same
+    state reports: both add the same FP32 terms of a site to FP64 sums one by
+    one.  The state is the same at every site, so that a rounding of two terms
+    added in FP32 (up to 6e-8 of them) is the same everywhere and does not
+    average out.  The sums differ by the order of 32^3 FP64 additions of equal
+    sign (at most 4e-12 of b's change); each b carries 1e-16 of itself."""
+    rng = np.random.default_rng(seed)
+    N = 32
+    cfg = _cfg(N, "fp32", integrator=integ, alpha=0.0, m2=(1.0, 0.0), e=0.5, g=0.5, omega_over_f=1.0,
+               fstar_over_mp=1.0)
+    st = oracle.su2_vacuum_ic(cfg)
+    one = np.ones((N, N, N))
+    const = lambda shape: rng.uniform(0.3, 1.0, shape).astype(np.float32).astype(np.float64)[..., None, None, None] * one
+    st["phi"], st["pi"] = const(4), const(4)
+    st["piA"], st["piB"] = const(st["piA"].shape[:-3]), const(st["piB"].shape[:-3])
+    st["links"] = np.stack([np.ones((3, N, N, N)), np.zeros((3, N, N, N))], axis=1)
+    st["su2"] = np.stack([one * (k == 0) for k in range(4)])[None].repeat(3, axis=0)
+    h = cfg["dt"]
+    lat, ahead = _lattice(cfg), _lattice(cfg)
+    for x in (lat, ahead):
+        _set(x, st)
+
+    def b_of(x):
+        return x.get_state()["b"]
+
+    def close(b, before, terms, what):
+        want = sum(terms)
+        got = b - before
+        assert abs(got - want) < 1e-11 * sum(map(abs, terms)) + 1e-15 * abs(b), (what, got, want, got / want - 1.0)
+
+    b0, f0 = b_of(lat), _scale_factor_force(cfg, lat.energies())
+    if integ == "lf2":
+        lat.step(0)
+        ahead.step(0)
+        b1, f1 = b_of(lat), _scale_factor_force(cfg, lat.energies())
+        close(b1, b0, [-0.5 * h * f0], "start-up kick")
+        ahead.step(1)
+        close(b_of(ahead), b1, [h * f1], "kick")
+        f2 = _scale_factor_force(cfg, ahead.energies())
+        lat.step(2)
+        close(b_of(lat), b1, [h * f1, h * f2], "kick and drift with kick")
+    else:
+        ahead.step(1)
+        f1 = _scale_factor_force(cfg, ahead.energies())
+        close(b_of(ahead), b0, [0.5 * h * f0, 0.5 * h * f1], "one step")
+        # (the closing state's energies are lat's own: its merged kick rounds the
+        # momenta once where two single steps round them twice)
+        lat.step(2)
+        f2 = _scale_factor_force(cfg, lat.energies())
+        close(b_of(lat), b0, [0.5 * h * f0, h * f1, 0.5 * h * f2], "two steps")
