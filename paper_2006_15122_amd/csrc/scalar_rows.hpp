@@ -1,18 +1,20 @@
-// Full-row tile of the fused scalar pass (stepping passes).
+// Full-row tile of the fused scalar pass: stepping passes and observations.
 //
 // A block holds whole z-rows of the lattice: N = W NL sites per row, W
 // consecutive sites per lane moved as one 16-byte access (W = 4 in FP32
 // storage, 2 in FP64).  It owns BY consecutive y-rows and marches along x
-// over XC planes like the general tile, with each site's drift and kick
-// written term for term as there: from the same a and b, a pass gives every
-// site the general tile's new field and momentum bit for bit.  The energy
-// terms of a lane's W sites are summed in storage precision before they join
-// the FP64 totals, so the sums (and with them a and b after the pass) agree
-// with the general tile's to rounding, not bit for bit.  What changes is the
-// memory side: the periodic z-neighbours of a row are in the row itself (no
-// z halo loads at all), every global access is a whole 16-byte lane segment
-// of a row, and one address serves W sites.  The only halo left is the two
-// y-rows above and below the block, spread over all lanes.
+// over its share of planes like the general tile, with each site's drift and
+// kick written term for term as there: from the same a and b, a pass gives every
+// site the general tile's new field and momentum bit for bit.  Each site's
+// energy terms join the FP64 totals one by one, as there (the four sites of a
+// lane added in FP32 first round alike in a near-homogeneous state, 1e-8 of b's
+// change, and saved next to nothing: 160^3 32.3 us a pass then, 31.6 now, 192^3
+// 49.8 and 49.4, 320^3 204 and 203, 128^3 19.4 and 20.0), so the sums differ from
+// the general tile's by the order of FP64 additions.  What
+// changes is the memory side: the periodic z-neighbours of a row are in the row
+// itself (no z halo loads at all), every global access is a whole 16-byte lane
+// segment of a row, and one address serves W sites.  The only halo left is the
+// two y-rows above and below the block, spread over all lanes.
 //
 // N is a run-time number (any multiple of 32), so the block size is too: with
 // BY a multiple of 64 / W every block is whole waves.  Each row's place in LDS
@@ -38,14 +40,6 @@ struct RowVec {
 
 __device__ __forceinline__ float fma_t(float a, float b, float c) { return fmaf(a, b, c); }
 __device__ __forceinline__ double fma_t(double a, double b, double c) { return fma(a, b, c); }
-
-// the W sites' terms of one lane, summed pairwise
-template <typename T, int W>
-__device__ __forceinline__ T lane_sum(const T (&v)[W]) {
-  if constexpr (W == 4) return (v[0] + v[1]) + (v[2] + v[3]);
-  if constexpr (W == 2) return v[0] + v[1];
-  return v[0];
-}
 
 // Per-lane accumulators of a block of whole waves into partials[pidx] (wave
 // shuffles, then the waves in order).
@@ -270,9 +264,6 @@ __device__ __forceinline__ void scalar_rows(const ScalarArgs<T>& A, const int BY
           acc[5 * NF + 1] += (double)(quarter * lam * p2 * p2);
         }
       } else {
-        // the potential at the lane's W sites, summed pairwise in storage
-        // precision and added to the FP64 total once per plane
-        T v4[W];
 #pragma unroll
         for (int e = 0; e < W; ++e) {
           const T p2 = pc[0][e] * pc[0][e];
@@ -281,9 +272,8 @@ __device__ __forceinline__ void scalar_rows(const ScalarArgs<T>& A, const int BY
             const T c2 = pc[1][e] * pc[1][e];
             v = fma_t(c2, fma_t(hqq, p2, hm2_1), v);
           }
-          v4[e] = v;
+          acc[3] += (double)v;
         }
-        acc[3] += (double)lane_sum<T, W>(v4);
       }
 #pragma unroll
       for (int f = 0; f < NF; ++f) {
@@ -294,7 +284,6 @@ __device__ __forceinline__ void scalar_rows(const ScalarArgs<T>& A, const int BY
         const T zlo = reinterpret_cast<const T*>(pl)[zl];
         const T zhi = reinterpret_cast<const T*>(pl)[zh];
         VW pout;
-        T s0 = T(0), s1 = T(0), s2 = T(0);
 #pragma unroll
         for (int e = 0; e < W; ++e) {
           T cur[NF];
@@ -320,16 +309,15 @@ __device__ __forceinline__ void scalar_rows(const ScalarArgs<T>& A, const int BY
             acc[5 * f + 3] += (double)c;
             acc[5 * f + 4] += (double)(c * c);
           } else {
-            s0 = fma_t(pin, pin, s0);
-            s1 = fma_t(pe, pe, s1);
-            s2 += gx * gx + gy * gy + gz * gz;
+            acc[1] += (double)(pe * pe);
+            acc[2] += (double)(gx * gx + gy * gy + gz * gz);
           }
         }
         if constexpr (!FULL) {
-          // the W sites' terms summed in storage precision, then into the FP64 totals
-          if (lf) acc[0] += (double)s0;
-          acc[1] += (double)s1;
-          acc[2] += (double)s2;
+          if (lf) {
+#pragma unroll
+            for (int e = 0; e < W; ++e) acc[0] += (double)(qc[f][e] * qc[f][e]);
+          }
           // streaming stores of the new state (read again only by the next pass)
           store(pc[f], A.dst[f], o);
           store(pout, A.dst[2 + f], o);

@@ -176,3 +176,31 @@ def test_full_row_batch_tile_against_oracle(precision, width, tol):
     with pytest.raises(LatticeError):
         W.set_tiling(width, 256, 1, 8)
     W.close()
+
+
+def test_full_row_batch_sums_carry_the_bits_of_the_general_tile():
+    """A full-row batch block adds each FP32 site's terms to the FP64 sums one
+    by one, as the general tile does: a and b of each run agree to the order of
+    the FP64 additions (at most 1e-11 of their change).  The sites of a lane hold
+    four different values, the same in every lane, so that terms added in FP32
+    first would not average out."""
+    from paper_2006_15122_amd.lattice import Batch
+
+    cfgs = [dict(c, q=0.0, m2=(0.5, 0.0), lam=0.0, alpha=0.0, fstar_over_mp=1.0) for c in _runs(sizes=(32, 96, 128))]
+    rng = np.random.default_rng(7)
+    B = Batch(cfgs)
+    out = []
+    start = [np.tile(rng.uniform(0.3, 1.0, (2, 2, 1, 1, 4)).astype(np.float32), c["N"] // 4).astype(np.float64)
+             for c in cfgs]
+    for t in ((32, 8, 2, 8), (4, 256, 1, 8)):
+        B.set_tiling(*t)
+        for run, c, s in zip(B.runs, cfgs, start):
+            N = c["N"]
+            phi, pi = np.broadcast_to(s, (2, 2, N, N, N)).copy()
+            run.set_state(phi, pi, 1.0, 0.5)
+        B.step(2)
+        out.append([run.get_state() for run in B.runs])
+    for g, r in zip(*out):
+        for k, s in (("a", 1.0), ("b", 0.5)):
+            assert abs(r[k] - g[k]) < 1e-11 * abs(g[k] - s) + 1e-15 * abs(g[k]), (k, (r[k] - g[k]) / (g[k] - s))
+    B.close()

@@ -555,6 +555,36 @@ def test_full_row_tiles_of_any_length_against_oracle(precision, nf, N, shapes):
         assert np.max(np.abs(s["pi"] - pi)) < tol * np.max(np.abs(pi)), t
 
 
+@pytest.mark.parametrize("integ", ["lf2", "vv2"])
+@pytest.mark.parametrize("nf,N,by,xc", [(2, 64, 4, 4), (2, 96, 8, 8), (2, 160, 8, 16), (1, 64, 16, 8), (1, 96, 8, 4),
+                                        (1, 32, 8, 4)])
+def test_full_row_sums_carry_the_bits_of_the_general_tile(nf, N, by, xc, integ):
+    """A full-row tile adds each FP32 site's terms to the FP64 sums one by one,
+    as the general tile does: a and b agree to the order of the FP64 additions.
+    The four sites of a lane hold different values, the same in every lane, so
+    that terms added in FP32 first (rounded by up to 6e-8) would not average
+    out.  The potential is a mass term, whose rounding is the same in both
+    tiles.  64^3 to 160^3 additions of equal sign in another order differ by at
+    most 1e-11 of b's change (1e-13 in practice); each a and b carries 1e-16 of
+    itself."""
+    cfg = dict(synth.small(synth.config2(q=0.0), N), nf=nf, integrator=integ, m2=(0.5, 0.0), lam=0.0, alpha=0.0,
+               fstar_over_mp=1.0)
+    rng = np.random.default_rng(100 * N + by)
+    four = rng.uniform(0.3, 1.0, (2, nf, 4)).astype(np.float32).astype(np.float64)
+    phi, pi = np.broadcast_to(np.tile(four, N // 4)[:, :, None, None, :], (2, nf, N, N, N)).copy()
+    lat = _lattice(cfg)
+    out = []
+    for t in ((32, 8, 2, 8), (N, by, 1, xc)):
+        lat.set_tiling(*t)
+        lat.set_state(phi, pi, 1.0, 0.5)
+        lat.step(2)
+        out.append(lat.get_state())
+    g, r = out
+    for k, start in (("a", 1.0), ("b", 0.5)):
+        assert abs(r[k] - g[k]) < 1e-11 * abs(g[k] - start) + 1e-15 * abs(g[k]), (k, (r[k] - g[k]) / (g[k] - start))
+    lat.close()
+
+
 @pytest.mark.parametrize("N", [32, 96, 160])
 def test_spectrum_of_single_modes_on_the_half_volume(N):
     """The transform keeps half the modes along z and counts the others through
