@@ -275,7 +275,10 @@ int lattice_pass_timer(lattice_t* h, int32_t max_launches);
 int lattice_pass_timer_read(lattice_t* h, double* total_ms, int64_t* launches);
 
 /* Device pointer to component c of the current fields (storage precision),
-   and the storage element size in bytes; for zero-copy consumers. */
+   and the storage element size in bytes; for zero-copy consumers.  A compact
+   U(1) link is its phase: written through the pointer, it may be any number of
+   turns; observations and the kick that opens a step take it as it is, and a
+   drift stores it within one turn. */
 int lattice_field_device_ptr(lattice_t* h, int c, void** ptr, int32_t* elem_bytes);
 
 /* ------------------------------------------------------------------------

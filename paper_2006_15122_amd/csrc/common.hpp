@@ -154,6 +154,12 @@ __device__ __forceinline__ T mul_c(const Coef<T>& c, T x) {
   return fmaf(c.hi, x, c.lo * x);
 }
 
+// Instantiations of a gauge model's pass: with a drift, without one (the kick
+// that opens a step), and the observation, which neither drifts nor stores.
+// Only a drift moves the compact links, and wraps their phases; the other two
+// take a phase as it is stored, whatever its turn.
+enum PassKind { kPassStep = 0, kPassKick = 1, kPassObs = 2 };
+
 struct PassDesc {
   double wd, wk1, wk2;
   int mode;

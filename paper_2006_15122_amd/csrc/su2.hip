@@ -205,8 +205,9 @@ struct Su2Tile {
   static constexpr int NR = 2 * LZ + 2 * TY;  // ring sites
 };
 
-template <typename T, int TZ, int TY, int WPE, bool OBS>
+template <typename T, int TZ, int TY, int WPE, int MODE>
 __global__ __launch_bounds__(TZ* TY, WPE) void su2_pass_kernel(Su2PassArgs<T> A) {
+  constexpr bool OBS = MODE == kPassObs;
   using Tile = Su2Tile<TZ, TY>;
   constexpr int LY = Tile::LY, LZ = Tile::LZ, NR = Tile::NR, NT = Tile::NT;
   constexpr int NACC = OBS ? kSu2Acc : kSu2StepAcc;
@@ -319,7 +320,6 @@ __global__ __launch_bounds__(TZ* TY, WPE) void su2_pass_kernel(Su2PassArgs<T> A)
   const double hw = A.pd.wd * A.h;
   const double anew = A.expand ? a_in + hw * b_in : a_in;
   const double amid = 0.5 * (a_in + anew);
-  const bool dr = A.pd.wd != 0.0;
   // per-pass coefficients as hi + lo pairs (no coherent rounding of them)
   const double p1 = apow(amid, 1.0 - A.alpha), pl = apow(anew, 1.0 + A.alpha), pb = apow(anew, A.alpha - 1.0);
   const double dx3 = A.dx * A.dx * A.dx;
@@ -351,10 +351,10 @@ __global__ __launch_bounds__(TZ* TY, WPE) void su2_pass_kernel(Su2PassArgs<T> A)
   // U renormalised to unit length after the product (rounding only).  A pass
   // without drift leaves the links as they are.
   auto drift_site = [&](const Su2Raw<T>& w, int b, int y, int z) {
-    if (!dr) {
+    if constexpr (MODE != kPassStep) {
       LP[b][y][z] = Q4<T>{w.ph[0], w.ph[1], w.ph[2], w.ph[3]};
 #pragma unroll
-      for (int i = 0; i < 3; ++i) { Lt[b][i][y][z] = wrap_turns(w.th[i]); LU[b][i][y][z] = w.u[i]; }
+      for (int i = 0; i < 3; ++i) { Lt[b][i][y][z] = w.th[i]; LU[b][i][y][z] = w.u[i]; }
       return;
     }
     LP[b][y][z] = Q4<T>{fma_c(cd, w.pi[0], w.ph[0]), fma_c(cd, w.pi[1], w.ph[1]), fma_c(cd, w.pi[2], w.ph[2]),
@@ -392,13 +392,19 @@ __global__ __launch_bounds__(TZ* TY, WPE) void su2_pass_kernel(Su2PassArgs<T> A)
     const Cx2<T> a = cadd2(o[0], vf[0]), b = cadd2(o[1], vf[1]);
     return Q4<T>{a.re, a.im, b.re, b.im};
   };
+  // (sin, cos - 1) of a link's or plaquette's phase: a drift wraps the links to
+  // one turn; stored phases (a caller may write any) are any number
+  auto sincos_link = [](T x, T* sn, T* cm) {
+    if constexpr (MODE == kPassStep) sincos_m1_near(x, sn, cm);
+    else sincos_m1_any(x, sn, cm);
+  };
   // plaquettes of place (y, z) of plane buffer c (plane x+1 in buffer n)
   auto plB = [&](const Q4<T>& ua, const Q4<T>& ubf, const Q4<T>& ub, const Q4<T>& uaf) -> Q4<T> {
     return qmul(qmul(ua, ubf), qdag(qmul(ub, uaf)));
   };
   auto plA = [&](T ta, T tbf, T taf, T tb, T& om) -> T {
     T sn, cm;
-    sincos_m1_near((ta + tbf) - (taf + tb), &sn, &cm);
+    sincos_link((ta + tbf) - (taf + tb), &sn, &cm);
     om = -cm;  // 1 - cos Phi
     return sn;
   };
@@ -437,7 +443,7 @@ __global__ __launch_bounds__(TZ* TY, WPE) void su2_pass_kernel(Su2PassArgs<T> A)
     sx01 = plA(Lt[1][0][ly][lz], Lt[0][1][ly][lz], Lt[1][0][ly + 1][lz], Lt[1][1][ly][lz], om);
     sx02 = plA(Lt[1][0][ly][lz], Lt[0][2][ly][lz], Lt[1][0][ly][lz + 1], Lt[1][2][ly][lz], om);
     T sn, cm;
-    sincos_m1_near(Lt[1][0][ly][lz], &sn, &cm);
+    sincos_link(Lt[1][0][ly][lz], &sn, &cm);
     Cx2<T> p[2];
     phi_at(1, ly, lz, p);
     hx = back(u0, sn, cm, p);
@@ -466,7 +472,7 @@ __global__ __launch_bounds__(TZ* TY, WPE) void su2_pass_kernel(Su2PassArgs<T> A)
       for (int d = 0; d < 3; ++d) {
         const Q4<T>& u = d == 0 ? u0 : d == 1 ? u1 : u2;
         T sn, cm;
-        sincos_m1_near(d == 0 ? t0 : d == 1 ? t1 : t2, &sn, &cm);
+        sincos_link(d == 0 ? t0 : d == 1 ? t1 : t2, &sn, &cm);
         Cx2<T> fp[2], um1f[2], g[2];
         phi_at(d == 0 ? n : c, ly + (d == 1), lz + (d == 2), fp);
         // W Phi_+ - Phi = (V - 1) y + (U - 1) Phi_+ + (Phi_+ - Phi),  y = U Phi_+
@@ -548,7 +554,7 @@ __global__ __launch_bounds__(TZ* TY, WPE) void su2_pass_kernel(Su2PassArgs<T> A)
       Bv[0][6][0][rid] = plA(Lt[c][0][0][z], Lt[n][1][0][z], Lt[c][0][1][z], Lt[c][1][0][z], om);
       Bv[0][7][0][rid] = plA(Lt[c][1][0][z], Lt[c][2][1][z], Lt[c][1][0][z + 1], Lt[c][2][0][z], om);
       T sn, cm;
-      sincos_m1_near(Lt[c][1][0][z], &sn, &cm);
+      sincos_link(Lt[c][1][0][z], &sn, &cm);
       Cx2<T> p[2];
       phi_at(c, 0, z, p);
       Bh[0][0][rid] = back(u1, sn, cm, p);
@@ -566,7 +572,7 @@ __global__ __launch_bounds__(TZ* TY, WPE) void su2_pass_kernel(Su2PassArgs<T> A)
       Bv[1][6][q][0] = plA(Lt[c][0][y][0], Lt[n][2][y][0], Lt[c][0][y][1], Lt[c][2][y][0], om);
       Bv[1][7][q][0] = plA(Lt[c][1][y][0], Lt[c][2][y + 1][0], Lt[c][1][y][1], Lt[c][2][y][0], om);
       T sn, cm;
-      sincos_m1_near(Lt[c][2][y][0], &sn, &cm);
+      sincos_link(Lt[c][2][y][0], &sn, &cm);
       Cx2<T> p[2];
       phi_at(c, y, 0, p);
       Bh[1][q][0] = back(u2, sn, cm, p);
@@ -977,7 +983,7 @@ static int su2_pass_t(lattice* h, const PassDesc& pd, PassChain* chain) {
   }
   if (!pd.write) {
     if (pd.wd != 0.0 || chain) { set_error("SU(2) pass: an observation neither drifts nor chains"); return LAT_EINVAL; }
-    hipLaunchKernelGGL((su2_pass_kernel<T, TZ, TY, WPE, true>), dim3(nb), dim3(NT), 0, h->stream, A);
+    hipLaunchKernelGGL((su2_pass_kernel<T, TZ, TY, WPE, kPassObs>), dim3(nb), dim3(NT), 0, h->stream, A);
     CL_HIP(hipGetLastError());
     hipLaunchKernelGGL((su2_finish_kernel<T, true>), dim3(1), dim3(kSu2FinishThreads), 0, h->stream, A, nb, h->st);
     CL_HIP(hipGetLastError());
@@ -989,10 +995,12 @@ static int su2_pass_t(lattice* h, const PassDesc& pd, PassChain* chain) {
     ev1 = h->timer[2 * h->timer_used + 1];
     ++h->timer_used;
   }
+  auto* const kernel =
+      pd.wd != 0.0 ? su2_pass_kernel<T, TZ, TY, WPE, kPassStep> : su2_pass_kernel<T, TZ, TY, WPE, kPassKick>;
   if (ev0)
-    hipExtLaunchKernelGGL((su2_pass_kernel<T, TZ, TY, WPE, false>), dim3(nb), dim3(NT), 0, h->stream, ev0, ev1, 0, A);
+    hipExtLaunchKernelGGL(kernel, dim3(nb), dim3(NT), 0, h->stream, ev0, ev1, 0, A);
   else
-    hipLaunchKernelGGL((su2_pass_kernel<T, TZ, TY, WPE, false>), dim3(nb), dim3(NT), 0, h->stream, A);
+    hipLaunchKernelGGL(kernel, dim3(nb), dim3(NT), 0, h->stream, A);
   CL_HIP(hipGetLastError());
   if (chain) {
     if (A.prev.partials) chain->rd ^= 1;

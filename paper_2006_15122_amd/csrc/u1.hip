@@ -180,8 +180,9 @@ __device__ __forceinline__ T wrap_phase(T t) {
 // plaquette terms are the angles themselves (Phi = -e dx^2 F_ij; Phi^2/2 for
 // the magnetic energy), which turns the compact kernels into the quadratic
 // ones with the same coefficients.
-template <typename T, int TZ, int BY, int RY, bool NC, bool OBS>
+template <typename T, int TZ, int BY, int RY, bool NC, int MODE>
 __global__ __launch_bounds__(TZ* BY) void u1_pass_kernel(U1PassArgs<T> A) {
+  constexpr bool OBS = MODE == kPassObs;
   constexpr int TY = BY * RY, NT = TZ * BY, LY = TY + 2, LZ = TZ + 2;
   constexpr int NACC = OBS ? kU1Acc : kU1StepAcc;
   constexpr int NH = 2 * LZ + 2 * TY;  // ring of the (TY+2) x (TZ+2) plane tile
@@ -288,13 +289,19 @@ __global__ __launch_bounds__(TZ* BY) void u1_pass_kernel(U1PassArgs<T> A) {
   const T lam = (T)A.lam, m2 = (T)A.m2;
   const Coef<T> lam2c = ucoef<T>(2.0 * A.lam), m2c = ucoef<T>(A.m2);
 
-  // (sin, cos - 1) of a link's phase: compact links are wrapped to one turn,
-  // the non-compact field is any number
+  // (sin, cos - 1) of a link's phase: a drift wraps compact links to one turn;
+  // stored phases (a caller may write any) and the non-compact field are any number
   auto link = [&](T th) -> C2<T> {
     T sn, cm;
     if constexpr (NC) sincos_m1(mul_c(mth, th), &sn, &cm);
-    else sincos_m1_near(th, &sn, &cm);
+    else if constexpr (MODE == kPassStep) sincos_m1_near(th, &sn, &cm);
+    else sincos_m1_any(th, &sn, &cm);
     return C2<T>{cm, sn};
+  };
+  // a compact link's phase after the drift; a pass without one leaves it as it is
+  auto drift_phase = [&](T th, T pa) -> T {
+    if constexpr (MODE == kPassStep) return wrap_phase(th - T(2) * atan_t(mul_c(cu, pa)));
+    else return th;
   };
   // drift the raw values into LDS buffer b
   // (the only transcendentals of the pass: one arctangent and one sincos per link)
@@ -310,7 +317,7 @@ __global__ __launch_bounds__(TZ* BY) void u1_pass_kernel(U1PassArgs<T> A) {
         if constexpr (NC) {
           th = fma_c(cA, raw[7 + i][r], raw[4 + i][r]);  // A_i after the drift
         } else {
-          th = wrap_phase(dr ? raw[4 + i][r] - T(2) * atan_t(mul_c(cu, raw[7 + i][r])) : raw[4 + i][r]);
+          th = drift_phase(raw[4 + i][r], raw[7 + i][r]);
         }
         Lt[b][i][ly][lz] = th;
         Lu[b][i][ly][lz] = link(th);
@@ -326,7 +333,7 @@ __global__ __launch_bounds__(TZ* BY) void u1_pass_kernel(U1PassArgs<T> A) {
           th = fma_c(cA, rraw[7 + i], rraw[4 + i]);
           Lt[b][i][rly][rlz] = th;  // the plaquette angles need A on the ring
         } else {
-          th = wrap_phase(dr ? rraw[4 + i] - T(2) * atan_t(mul_c(cu, rraw[7 + i])) : rraw[4 + i]);
+          th = drift_phase(rraw[4 + i], rraw[7 + i]);
         }
         Lu[b][i][rly][rlz] = link(th);
       }
@@ -739,18 +746,21 @@ static int u1_pass_t(lattice* h, const PassDesc& pd, PassChain* chain) {
     ++h->timer_used;
   }
   if (!pd.write) {
-    if (chain) { set_error("U(1) pass: an observation does not chain"); return LAT_EINVAL; }
-    hipLaunchKernelGGL((u1_pass_kernel<T, TZ, BY, RY, NC, true>), dim3(nb), dim3(TZ * BY), 0, h->stream, A);
+    if (pd.wd != 0.0 || chain) { set_error("U(1) pass: an observation neither drifts nor chains"); return LAT_EINVAL; }
+    hipLaunchKernelGGL((u1_pass_kernel<T, TZ, BY, RY, NC, kPassObs>), dim3(nb), dim3(TZ * BY), 0, h->stream, A);
     CL_HIP(hipGetLastError());
     hipLaunchKernelGGL((u1_pass_finish<T, true>), dim3(1), dim3(kU1FinishThreads), 0, h->stream, A, nb, h->st);
     CL_HIP(hipGetLastError());
     return LAT_OK;
   }
+  // (the non-compact drift is linear: a pass without one needs no kernel of its own)
+  constexpr int KICK = NC ? kPassStep : kPassKick;
+  auto* const kernel = pd.wd != 0.0 ? u1_pass_kernel<T, TZ, BY, RY, NC, kPassStep>
+                                    : u1_pass_kernel<T, TZ, BY, RY, NC, KICK>;
   if (ev0)
-    hipExtLaunchKernelGGL((u1_pass_kernel<T, TZ, BY, RY, NC, false>), dim3(nb), dim3(TZ * BY), 0, h->stream, ev0, ev1,
-                          0, A);
+    hipExtLaunchKernelGGL(kernel, dim3(nb), dim3(TZ * BY), 0, h->stream, ev0, ev1, 0, A);
   else
-    hipLaunchKernelGGL((u1_pass_kernel<T, TZ, BY, RY, NC, false>), dim3(nb), dim3(TZ * BY), 0, h->stream, A);
+    hipLaunchKernelGGL(kernel, dim3(nb), dim3(TZ * BY), 0, h->stream, A);
   CL_HIP(hipGetLastError());
   if (chain) {
     if (A.prev.partials) chain->rd ^= 1;

@@ -298,3 +298,24 @@ def test_su2_step_sums_carry_the_bits_of_the_observation_sums(integ, seed):
         lat.step(2)
         f2 = _scale_factor_force(cfg, lat.energies())
         close(b_of(lat), b0, [0.5 * h * f0, h * f1, 0.5 * h * f2], "two steps")
+
+
+@pytest.mark.parametrize("precision,N", [("fp32", 32), ("fp64", 32)])
+def test_su2_pass_without_drift_takes_stored_phases_as_they_are(precision, N):
+    """U(1) phases of many turns, written through the component pointers: the
+    observation and the start-up kick take the sine of the stored phase, and
+    the kick leaves it as it is."""
+    from test_gpu_u1 import phases_over_many_turns, run_phases_over_many_turns
+
+    rng = np.random.default_rng(6)
+    cfg = _cfg(N, precision, integrator="lf2", e=0.5, g=0.5)
+    st = oracle.su2_vacuum_ic(cfg)
+    for key in ("phi", "pi", "piA", "piB"):
+        st[key] = 0.5 * rng.normal(size=st[key].shape)
+    th = phases_over_many_turns(N, rng)
+    lat = _lattice(cfg)
+    _set(lat, st)
+    for key in ("phi", "pi", "piA", "piB"):
+        st[key] = lat.get_state()[key]
+    st["links"] = np.ascontiguousarray(np.stack([np.cos(th), np.sin(th)], axis=1))
+    run_phases_over_many_turns(lat, 8, th, lambda: oracle.su2_sync_observe(oracle.su2_model(cfg), st))

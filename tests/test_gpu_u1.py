@@ -401,3 +401,69 @@ def test_u1_blocks_share_the_planes(model, precision, N, tile, tol):
     for key in ("phi", "pi", "links", "piA"):
         scale = np.max(np.abs(o[key]))
         assert np.max(np.abs(s[key] - o[key])) < tol * scale, (key, np.max(np.abs(s[key] - o[key])) / scale)
+
+
+def component(lat, c):
+    """Component c of the state as a tensor on the lattice's own memory."""
+    import ctypes
+
+    import torch
+    from paper_2006_15122_amd.lattice import _check, lib
+
+    p, eb, N = ctypes.c_void_p(), ctypes.c_int32(), lat.N
+    _check(lib().lattice_field_device_ptr(lat.h, ctypes.c_int(c), ctypes.byref(p), ctypes.byref(eb)))
+    off = p.value - lat.ws.data_ptr()
+    t = lat.ws[off:off + N ** 3 * eb.value].view(torch.float32 if eb.value == 4 else torch.float64)
+    return t.view(N, N, N)
+
+
+def phases_over_many_turns(N, rng):
+    """Three directions' phases, 0 or 106 (17 turns less 0.81) by the parity of
+    the next coordinate, plus up to 0.05: every plaquette then holds one of them.
+    Multiples of 2^-10, so that FP32 holds them and the sums of four exactly."""
+    n = np.arange(N) % 2
+    th = rng.integers(-51, 52, (3, N, N, N)) / 1024.0
+    th[0] += 106.0 * n[:, None]
+    th[1] += 106.0 * n
+    th[2] += 106.0 * n[:, None, None]
+    return th
+
+
+def run_phases_over_many_turns(lat, first, th, observe):
+    """Writes the phases to components first .. first + 2; the energies agree
+    with observe(), and a start-up kick leaves the phases bit for bit."""
+    import torch
+
+    dev = [component(lat, first + i) for i in range(3)]
+    put = [torch.from_numpy(th[i]).to(dev[i]) for i in range(3)]
+    for d, t in zip(dev, put):
+        d.copy_(t)
+    torch.cuda.synchronize()
+    g, o = lat.energies(), observe()
+    # FP32: a link's cosine and sine carry 1e-7, a plaquette of four 4e-7, which
+    # 1 - cos at an angle of 0.8 doubles; a turn of 2 pi rounded to FP32 is off by
+    # 1.7e-7, 17 of them by 3e-6
+    tol = 2e-6 if dev[0].element_size() == 4 else 1e-12
+    for k in ("EG", "EG_A", "EK", "EK_A"):
+        assert abs(g[k] - o[k]) <= tol * abs(o[k]), (k, g[k] / o[k] - 1.0)
+    lat.step(0)
+    for i, t in enumerate(put):
+        assert torch.equal(component(lat, first + i), t), i
+
+
+@pytest.mark.parametrize("precision,N", [("fp32", 32), ("fp32", 64), ("fp64", 32)])
+def test_u1_pass_without_drift_takes_stored_phases_as_they_are(precision, N):
+    """Phases of many turns, written through the component pointers: the
+    observation and the start-up kick take the sine of the stored phase, and
+    the kick leaves it as it is."""
+    rng = np.random.default_rng(5)
+    cfg = _cfg(N, precision, integrator="lf2")
+    st = synth.random_u1_state(N, seed=43, amp=0.6, link_angle=0.1, emom=0.5)
+    st["a"], st["b"] = 1.0, 0.5
+    th = phases_over_many_turns(N, rng)
+    lat = _lattice(cfg)
+    lat.set_state(st["phi"], st["pi"], 1.0, 0.5, links=st["links"], piA=st["piA"])
+    st["links"] = np.ascontiguousarray(np.stack([np.cos(th), np.sin(th)], axis=1))
+    for k in ("phi", "pi", "piA"):
+        st[k] = lat.get_state()[k]
+    run_phases_over_many_turns(lat, 4, th, lambda: oracle.u1_sync_observe(oracle.u1_model(cfg), st))
