@@ -253,7 +253,10 @@ __global__ __launch_bounds__(TZ* TY, WPE) void su2_pass_kernel(Su2PassArgs<T> A)
   // to the next and is opaque to the compiler: 70 bases kept across the loop
   // overflow the scalar registers, and formed from the component number they
   // become 64-bit vector arithmetic, three instructions a load.  FP32 steps a
-  // scalar base; FP64, whose constants fill the scalar registers, a vector one.
+  // scalar base; FP64, whose constants fill the scalar registers, a vector one:
+  // with 55 scalar registers spilled the compiler split live ranges where a
+  // branch joins, ahead of the restored lane mask, and the lanes outside the
+  // branch lost their LDS addresses (the build refuses such code).
   struct Walk {
     GlobalPtr<const char> p;
     size_t st;
