@@ -87,10 +87,16 @@ constexpr int kBatchRowN = 128;
 template <typename T>
 __host__ __device__ constexpr int batch_row_width() { return sizeof(T) == 4 ? 4 : 2; }
 // y-rows of a block at size N: the most that fit, a divisor of N
-__host__ __device__ inline int batch_rows(int N, int W) {
+__host__ __device__ constexpr int batch_rows(int N, int W) {
   int by = 1;
   while (2 * by * (N / W) <= kBatchRowLanes && N % (2 * by) == 0) by *= 2;
   return by;
+}
+// whether NF halo sites a lane hold the 2 NF N of a block at every size it takes
+constexpr bool batch_halo_fits(int W) {
+  for (int N = 32; N <= kBatchRowN; N += 32)
+    if (2 * N > N / W * batch_rows(N, W)) return false;
+  return true;
 }
 
 template <typename T, int NF>
@@ -107,7 +113,7 @@ __global__ __launch_bounds__(kBatchRowLanes) void batch_rows_kernel(
   A.st = slots[2 * r + rd];
   const int first = tile_offset[r], nrec = tile_offset[r + 1] - first;
   DevState* const out = slots[2 * r + (rd ^ 1)];
-  // (at most two halo sites per lane up to N = 128)
+  static_assert(batch_halo_fits(W), "a lane holds NF halo sites");
   scalar_rows<T, W, NF, NF, true, kRowsStep>(A, batch_rows(A.N, W), local, b, [&](double& a_in, double& b_in) {
     if (prev.partials) {
       constexpr int NP = Acc<NF, false>::N;

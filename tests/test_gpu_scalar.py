@@ -585,6 +585,69 @@ def test_full_row_sums_carry_the_bits_of_the_general_tile(nf, N, by, xc, integ):
     lat.close()
 
 
+def full_row_planes(N, width, by, xc):
+    """Planes of each block along x that a full-row pass marches: the fewest
+    blocks of at most xc planes, or more, of eight planes or one per CU, where
+    the GPU then ends sooner (twelve waves share a CU)."""
+    slots = 256 * max(1, 12 // (N // width * by // 64))
+    tiles, n, best, cost = N // by, N // xc, 0, math.inf
+    n0 = n
+    while n == n0 or 8 * n <= N or (n <= N and tiles * n <= 256):
+        c = -(-tiles * n // slots) * (-(-N // n) + 2.0)
+        if c < 0.98 * cost:
+            cost, best = c, n
+        n += 1
+    return sorted({(k + 1) * N // best - k * N // best for k in range(best)})
+
+
+@pytest.mark.parametrize("precision,N,by,xc,lanes,lds,planes", [
+    ("fp32", 192, 16, 192, 768, 55296, [9, 10]), ("fp64", 192, 8, 64, 768, 61440, [19, 20]),
+    ("fp32", 384, 8, 32, 768, 61440, [24]), ("fp64", 384, 4, 48, 768, 73728, [48]),
+    ("fp32", 768, 4, 96, 768, 73728, [96]), ("fp64", 32, 4, 32, 64, 6144, [1])])
+def test_full_row_blocks_at_their_bounds(precision, N, by, xc, lanes, lds, planes):
+    """The largest full-row blocks, 768 lanes and up to 72 KB of LDS, and one
+    wave: a start-up kick is bit for bit the general tile's at every site, two
+    leapfrog steps agree to a few roundings of the state (a and b differ by the
+    order of FP64 additions), and the observation's kinetic sum and means are
+    the device's own in FP64."""
+    import torch
+    from test_gpu_u1 import component
+
+    width = 4 if precision == "fp32" else 2
+    assert lanes == N // width * by and lds == 2 * 2 * (by + 2) * N * 16 // width
+    assert full_row_planes(N, width, by, xc) == planes
+    cfg = dict(synth.config2(q=100.0, N=N), precision=precision, integrator="lf2", ic="homogeneous")
+    out = []
+    for t in ((32, 8, 2, 8), (N, by, 1, xc)):
+        lat = _lattice(cfg)
+        lat.set_tiling(*t)
+        g = torch.Generator(device="cuda:0").manual_seed(N)
+        for c in range(4):
+            d = component(lat, c)
+            d.copy_(0.3 * torch.rand(d.shape, generator=g, device=d.device, dtype=d.dtype))
+        torch.cuda.synchronize()
+        e = lat.energies()
+        for f in range(2):
+            p = component(lat, 2 + f)
+            ek = float((p * p).double().mean()) / 2.0 / e["a"] ** 6
+            assert abs(e[f"EK{f}"] - ek) < 1e-11 * ek and abs(
+                e[f"mean{f}"] - float(component(lat, f).double().mean())) < 1e-11, (t, f)
+        lat.step(0)
+        torch.cuda.synchronize()
+        kick = [component(lat, c).clone() for c in range(4)]
+        lat.step(2)
+        torch.cuda.synchronize()
+        out.append((kick, [component(lat, c).clone() for c in range(4)]))
+        lat.close()
+        del lat, d, p
+        torch.cuda.empty_cache()
+    eps = 1.2e-7 if precision == "fp32" else 2.3e-16
+    for c in range(4):
+        assert torch.equal(out[0][0][c], out[1][0][c]), c
+        a, b = out[0][1][c], out[1][1][c]
+        assert float((a - b).abs().max()) <= 8 * eps * float(a.abs().max()), c
+
+
 @pytest.mark.parametrize("N", [32, 96, 160])
 def test_spectrum_of_single_modes_on_the_half_volume(N):
     """The transform keeps half the modes along z and counts the others through
