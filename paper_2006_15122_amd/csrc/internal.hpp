@@ -138,14 +138,14 @@ void u1_get_shape(int fp32, int i, int* tz, int* by, int* ry);
 int u1_pass(lattice* h, const PassDesc& pd, PassChain* chain = nullptr);
 int u1_chain_end(lattice* h, const PassChain& chain);
 int scalar_chain_end(lattice* h, const PassChain& chain);
-// blocks of a scalar observation pass (its fixed tile) at size N
-int64_t scalar_obs_blocks(int N);
+// records a scalar observation pass writes
+int64_t scalar_obs_blocks(int fp32, int nf, int N);
 int num_shapes(int fp32, int nf);
 bool get_shape(int fp32, int nf, int N, int i, int* tz, int* by, int* ry);
 hipError_t launch_scalar_pass(int fp32, int nf, const void* const* src, void* const* dst, int N, int tz, int by,
                               int ry, int xc, int swizzle, const double* phys, int expand, const PassDesc& pd,
-                              double* partials, DevState* st, hipStream_t s, int* nblocks_out, int full,
-                              hipEvent_t ev0, hipEvent_t ev1, const PrevPass& prev, DevState* fin);
+                              double* partials, int64_t max_records, DevState* st, hipStream_t s, int* nblocks_out,
+                              int full, hipEvent_t ev0, hipEvent_t ev1, const PrevPass& prev, DevState* fin);
 hipError_t launch_scalar_finish(int fp32, int nf, int N, const double* phys, int expand, const PassDesc& pd,
                                 double* partials, int nblocks, DevState* in, DevState* out, hipStream_t s);
 

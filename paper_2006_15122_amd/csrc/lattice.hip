@@ -94,15 +94,15 @@ static void layout(const lattice_params* p, size_t* off_part, size_t* off_part2,
   const size_t elem = p->precision == LAT_FP32 ? 4 : 8;
   const int nc = ncomponents(p);
   const int64_t mb = (N / 32) * (N / 8) * (N / 4);
-  // per-block FP64 partials: scalar passes write at most 32 per tile of at
-  // least 32 x 8 x 4 sites; the U(1) site kernels write up to 16 per block of
-  // 256 sites
+  // per-block FP64 partials: a scalar pass writes at most 13 per block, of
+  // which there are one per CU or per 32 x 8 x 4 sites; the U(1) site kernels
+  // write up to 16 per block of 256 sites
   const size_t part_doubles = std::max((size_t)std::max<int64_t>(mb, kCUs) * 32, (size_t)(V / 256) * 16);
   size_t o = align_up(2 * sizeof(DevState), 256);
   *off_part = o;
   o = align_up(o + part_doubles * sizeof(double), 256);
   // every other pass of a chain writes its records here: at most mb blocks
-  // (tiles of at least 1024 sites) or one per CU, of 4 scalar or 11 U(1) sums; SU(2) x U(1)
+  // (of 1024 sites or more) or one per CU, of 4 scalar or 5 U(1) sums; SU(2) x U(1)
   // blocks take 256 sites or more, or are one per CU, and write 7
   *off_part2 = o;
   o = align_up(o + (size_t)std::max<int64_t>(is_su2(*p) ? V / 256 : mb, kCUs) * 16 * sizeof(double), 256);
@@ -590,8 +590,9 @@ int scalar_pass(lattice* h, const PassDesc& pd, bool full, PassChain* chain) {
     fin = nullptr;
   }
   hipError_t e = launch_scalar_pass(h->p.precision == LAT_FP32, nf, src, dst, h->p.N, h->tile.tz, h->tile.by,
-                                    h->tile.ry, h->tile.xc, 1, phys, h->p.expansion, pd, part, st, h->stream, &nb,
-                                    full ? 1 : 0, ev0, ev1, prev, fin);
+                                    h->tile.ry, h->tile.xc, 1, phys, h->p.expansion, pd, part,
+                                    std::max<int64_t>(h->max_blocks, kCUs), st, h->stream, &nb, full ? 1 : 0, ev0, ev1,
+                                    prev, fin);
   if (e != hipSuccess) {
     set_error(std::string("scalar pass launch: ") + hipGetErrorString(e));
     return LAT_EHIP;

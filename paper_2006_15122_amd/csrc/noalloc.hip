@@ -49,8 +49,9 @@ static void* scratch_ptr() {
 }
 
 // Bytes of per-block partial records the observation passes of h write.
-// Scalar: one observation pass on its fixed tile, 5 nf + 3 FP64 sums per
-// tile.  U(1): the Gauss residual (4 per 256 sites),
+// Scalar: one observation pass, 5 nf + 3 FP64 sums per block, counted as one
+// block per 32 x 16 x 8 sites at least: the general tile's, which sets the
+// largest lattice the call takes.  U(1): the Gauss residual (4 per 256 sites),
 // then the pass on the lattice's tile (11 per tile).  SU(2) x U(1): the Gauss
 // residuals and the pass, at most 16 per 256 sites (or 256 records).
 static size_t energy_partial_bytes(const lattice* h) {
@@ -63,7 +64,8 @@ static size_t energy_partial_bytes(const lattice* h) {
     // as many as there are CUs)
     return std::max(V / 256 * 4, std::max({tiles, V / 1024, (size_t)kCUs}) * 11) * sizeof(double);
   }
-  return (size_t)scalar_obs_blocks(h->p.N) * (size_t)(5 * h->p.nf + 3) * sizeof(double);
+  const size_t records = (size_t)scalar_obs_blocks(h->p.precision == LAT_FP32, h->p.nf, h->p.N);
+  return std::max(records, V / 4096) * (size_t)(5 * h->p.nf + 3) * sizeof(double);
 }
 
 }  // namespace cl

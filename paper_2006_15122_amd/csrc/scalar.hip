@@ -110,13 +110,8 @@ static const Shape kShapesF64[] = {{64, 4, 2}, {32, 8, 2}, {32, 4, 4}, {0, 2, 1}
 
 // Observation passes: the 32 x 16 general tile with 8 planes, which divides
 // every supported N, where no full-row block fits; else full rows, as many
-// planes as leave 512 blocks (256^3 FP32: 90 us on the general tile, see
-// obs_tiling).
+// planes as leave 512 blocks.
 static const int kObsTz = 32, kObsBy = 8, kObsRy = 2, kObsXc = 8;
-
-int64_t scalar_obs_blocks(int N) {
-  return (int64_t)(N / kObsTz) * (N / (kObsBy * kObsRy)) * (N / kObsXc);
-}
 
 static Tiling obs_tiling(int fp32, int nf, int N) {
   const int ns = num_shapes(fp32, nf);
@@ -133,6 +128,24 @@ static Tiling obs_tiling(int fp32, int nf, int N) {
       return t;
     }
   return Tiling{kObsTz, kObsBy, kObsRy, kObsXc};
+}
+
+// Blocks of a pass on tile t.  Full rows share the planes among at least N / xc
+// of them (*nx along x): 168 VGPRs let twelve waves share a CU; a block reads
+// two planes beyond its own.
+static int64_t pass_blocks(int fp32, int N, const Tiling& t, int* nx) {
+  const int tiles = (N / t.tz) * (N / (t.by * t.ry));
+  *nx = 0;
+  if (t.ry == 1) {
+    const int waves = N / (fp32 ? 4 : 2) * t.by / 64;
+    *nx = x_blocks(N, t.xc, tiles, 256 * std::max(1, 12 / waves), 2.0, 8);
+  }
+  return (int64_t)tiles * (*nx ? *nx : N / t.xc);
+}
+
+int64_t scalar_obs_blocks(int fp32, int nf, int N) {
+  int nx;
+  return pass_blocks(fp32, N, obs_tiling(fp32, nf, N), &nx);
 }
 
 template <typename T, int NF>
@@ -194,24 +207,17 @@ bool get_shape(int fp32, int nf, int N, int i, int* tz, int* by, int* ry) {
 // Launch one pass.  buffers: src/dst arrays [4] in storage precision.
 hipError_t launch_scalar_pass(int fp32, int nf, const void* const* src, void* const* dst, int N, int tz,
                               int by, int ry, int xc, int swizzle, const double* phys, int expand,
-                              const PassDesc& pd, double* partials, DevState* st, hipStream_t s,
-                              int* nblocks_out, int full, hipEvent_t ev0, hipEvent_t ev1, const PrevPass& prev,
-                              DevState* fin) {
+                              const PassDesc& pd, double* partials, int64_t max_records, DevState* st,
+                              hipStream_t s, int* nblocks_out, int full, hipEvent_t ev0, hipEvent_t ev1,
+                              const PrevPass& prev, DevState* fin) {
   if (full && (prev.partials || !fin)) return hipErrorInvalidValue;  // observation passes finish themselves
   if ((pd.write != 0) == (full != 0)) return hipErrorInvalidValue;    // stepping passes store, observations do not
-  if (full) {
-    const Tiling t = obs_tiling(fp32, nf, N);
-    tz = t.tz;
-    by = t.by;
-    ry = t.ry;
-    xc = t.xc;
-  }
-  const Shape sh{tz, by, ry};
-  const int ty = by * ry;
-  // full rows: 168 VGPRs let twelve waves share a CU; a block reads two planes
-  // beyond its own
-  const int nx = ry == 1 ? x_blocks(N, xc, N / ty, 256 * std::max(1, 12 / (N / (fp32 ? 4 : 2) * by / 64)), 2.0, 8) : 0;
-  const int nblocks = (N / tz) * (N / ty) * (nx ? nx : N / xc);
+  const Tiling t = full ? obs_tiling(fp32, nf, N) : Tiling{tz, by, ry, xc};
+  const Shape sh{t.tz, t.by, t.ry};
+  int nx = 0;
+  const int64_t records = pass_blocks(fp32, N, t, &nx);
+  if (records > max_records) return hipErrorInvalidValue;  // they would leave their region
+  const int nblocks = (int)records;
   if (nblocks_out) *nblocks_out = nblocks;
   auto fill = [&](auto& A, auto* tag) {
     using TT = std::remove_pointer_t<decltype(tag)>;
@@ -220,7 +226,7 @@ hipError_t launch_scalar_pass(int fp32, int nf, const void* const* src, void* co
       A.dst[i] = static_cast<TT*>(dst[i]);
     }
     A.N = N;
-    A.XC = xc;
+    A.XC = t.xc;
     A.nx = nx;
     A.swizzle = swizzle;
     A.dx = phys[0];

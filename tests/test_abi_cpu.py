@@ -191,3 +191,31 @@ def test_model_codes_and_noncompact_layout():
     assert lattice.lib().lattice_workspace_size(ctypes.byref(p), ctypes.byref(n)) == -1
     p.model, p.nf = lattice.LAT_MODEL_U1_NC, 1
     assert lattice.lib().lattice_workspace_size(ctypes.byref(p), ctypes.byref(n)) == -1
+
+
+@pytest.mark.parametrize("precision,nf", [("fp32", 1), ("fp32", 2), ("fp64", 1), ("fp64", 2)])
+def test_scalar_observation_counts_the_records_it_writes(precision, nf):
+    """The count that sizes the records of a scalar observation pass is that of
+    the blocks it launches, on full rows where a block of them fits: whole rows
+    of by sites along y, 512 blocks or more of them sharing the planes."""
+    import ctypes
+
+    from test_gpu_scalar import full_row_planes
+
+    count = getattr(lattice.lib(), "_ZN2cl17scalar_obs_blocksEiii")
+    count.restype = ctypes.c_int64
+    w = 4 if precision == "fp32" else 2
+    sizes = (4, 8, 16) if w == 4 else (2, 4, 8)
+    for N in range(32, 1025, 32):
+        fit = [by for by in (8, 4, 2) if by in sizes and N // w * by % 64 == 0 and N // w * by <= 768
+               and 2 * nf * (by + 2) * N * 16 // w <= 98304]
+        if fit:
+            by = fit[0]
+            xc = next((x for x in (32, 16, 8, 4, 2) if N // by * (N // x) >= 512), 2)
+            planes = full_row_planes(N, w, by, xc)
+            want = range(N // by * N // max(planes), N // by * N // min(planes) + 1)
+            assert count(int(w == 4), nf, N) in want, (N, by, xc, planes)
+        else:
+            assert count(int(w == 4), nf, N) == (N // 32) * (N // 16) * (N // 8), N
+        # the records fit the region that every pass of a lattice has
+        assert count(int(w == 4), nf, N) <= max((N // 32) * (N // 8) * (N // 4), 256)
