@@ -709,22 +709,24 @@ void default_tiling(lattice* h) {
     h->tile = Tiling{0, 0, 0, 0};
     return;
   }
-  // Below 128^3 (where no tuner runs) a pass is latency: many blocks that march
-  // few planes, down to the 1024 sites a block needs for its record, up to 512
-  // blocks (scalar FP32 64^3: 8.0 us a pass with two planes a block, 9.6 with
-  // four; 96^3: 11.6 with four, 12.8 with two; U(1) 64^3: 20.7 with two, 27.2
-  // with four; 96^3: 34.3 with eight, 42.5 with four).  FP64 two-field lattices
-  // take full rows (64^3: 9.2 us against 11.8 for the best general tile).
-  const bool rows = !is_u1(h->p) && h->p.precision == LAT_FP64 && h->p.nf == 2;
-  Tiling t;
-  if (rows) t = Tiling{N, N == 96 ? 4 : 8, 1, 1};
-  else if (N % 64 == 0 && !(is_u1(h->p) && h->p.precision == LAT_FP64)) t = Tiling{64, 4, 2, 1};
-  else t = is_u1(h->p) ? Tiling{32, 8, 1, 1} : Tiling{32, 8, 2, 1};
+  // FP64 two-field lattices take full rows, eight to a block, whose pass shares
+  // the planes by itself (two and four rows a block: 32^3 7.9 us a pass with
+  // four, 7.1 with eight; 64^3 14.2, 10.2 and 8.7; 96^3 17.5 to 21.4 with four,
+  // 17.5 with eight; the best general tile 11.8 at 64^3).
+  h->tile = Tiling{N, 8, 1, 8};
+  if (!is_u1(h->p) && h->p.precision == LAT_FP64 && h->p.nf == 2 && tiling_ok(h, h->tile)) return;
+  // Else, below 128^3 (where no tuner runs) a pass is latency: many blocks that
+  // march few planes, down to 1024 sites a block, up to 512 blocks (scalar FP32
+  // 64^3: 8.0 us a pass with two planes a block, 9.6 with four; 96^3: 11.6 with
+  // four, 12.8 with two; U(1) 64^3: 20.7 with two, 27.2 with four; 96^3: 34.3
+  // with eight, 42.5 with four).
+  Tiling t = is_u1(h->p) ? Tiling{32, 8, 1, 1} : Tiling{32, 8, 2, 1};
+  if (N % 64 == 0 && !(is_u1(h->p) && h->p.precision == LAT_FP64)) t = Tiling{64, 4, 2, 1};
   const int64_t plane = (int64_t)t.tz * t.by * t.ry, tiles = (int64_t)N * N / plane;
   for (int c = 1; c <= N; ++c) {
     if (N % c) continue;
     t.xc = c;
-    if (plane * c >= 1024 && (rows || tiles * (N / c) <= 512) && tiling_ok(h, t)) break;
+    if (plane * c >= 1024 && tiles * (N / c) <= 512 && tiling_ok(h, t)) break;
   }
   h->tile = tiling_ok(h, t) ? t : is_u1(h->p) ? Tiling{32, 8, 1, 8} : Tiling{32, 8, 2, 8};
 }
