@@ -22,16 +22,16 @@ void set_error(const std::string& msg);
     }                                                                             \
   } while (0)
 
-// Device-resident homogeneous state and observables of one lattice.
-// Written only by the last-arriving block of a pass (one thread), read by all
-// blocks of the next pass.
+// Device-resident homogeneous state and observables of one lattice.  Two take
+// turns in a chain of passes: the first block of a pass writes one (one thread)
+// while every block reads the other; a finish kernel closes the chain.
 struct DevState {
   double a;          // scale factor at the current (sub-)step time
   double b;          // a' (half a step ahead inside a run of passes)
   double eta;        // program time of a
   double aux[5];     // reserved
   lattice_obs obs;   // observables of the last pass
-  unsigned int counter;   // arrival counter of the pass in flight
+  unsigned int reserved;
   int nonfinite;          // set when a volume average is NaN/Inf
 };
 

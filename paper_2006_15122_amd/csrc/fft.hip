@@ -515,7 +515,7 @@ __global__ __launch_bounds__(512) void fft_lines_inplace_kernel(Cx<R>* data, con
 // (+1: forward of Sec. 3.1, -1: inverse without the 1/N^3), then scaled.
 // Lines along z are contiguous; along y and x a batch is B neighbouring z
 // columns, so every row of the gather is B contiguous elements.
-template <typename R, bool ANY>
+template <typename R>
 __global__ __launch_bounds__(256) void fft_lines_kernel(Cx<R>* data, const Cx<double>* __restrict__ W, FFTPlan P,
                                                          int axis, int B, double sgn, double scale) {
   extern __shared__ unsigned char smem_raw[];
@@ -549,9 +549,7 @@ __global__ __launch_bounds__(256) void fft_lines_kernel(Cx<R>* data, const Cx<do
       case 3: fft_stage<R, 3>(in, out, W, N, B, Ns, sg); break;
       case 4: fft_stage<R, 4>(in, out, W, N, B, Ns, sg); break;
       case 5: fft_stage<R, 5>(in, out, W, N, B, Ns, sg); break;
-      default:
-        if constexpr (ANY) fft_stage_any<R>(in, out, W, N, B, Ns, Rr, sg);
-        break;
+      default: fft_stage_any<R>(in, out, W, N, B, Ns, Rr, sg); break;
     }
     __syncthreads();
     Cx<R>* tmp = in;
@@ -582,8 +580,8 @@ static void with_factors(const FFTPlan& P, Go go) {
 // Three line passes (z, y, x).  Lines per block B: the most that fit (one
 // buffer of at most 2048 elements plus the roots for the in-place kernel,
 // two buffers within 64 KiB for the generic one), at most kLinesZ along z,
-// fewer where that leaves under 2048 blocks, but at least 8 on the strided
-// axes so that each gathered row is 128 bytes.
+// fewer where that leaves under 2048 blocks, but on the strided axes 8, where
+// they fit, so that each gathered row is 128 bytes.
 template <typename R>
 static int fft3d(Cx<R>* data, const Cx<double>* W, int N, double sgn, double scale, hipStream_t s) {
   const FFTPlan P = make_plan(N);
@@ -610,7 +608,7 @@ static int fft3d(Cx<R>* data, const Cx<double>* W, int N, double sgn, double sca
     const double sc = axis == 0 ? scale : 1.0;
     if (any) {
       const size_t shm = (size_t)2 * B * N * sizeof(Cx<R>);
-      hipLaunchKernelGGL((fft_lines_kernel<R, true>), dim3(nblk), dim3(nt), shm, s, data, W, P, axis, B, sgn, sc);
+      hipLaunchKernelGGL((fft_lines_kernel<R>), dim3(nblk), dim3(nt), shm, s, data, W, P, axis, B, sgn, sc);
     } else {
       for (int f = 0; f < P.nfac; ++f)
         if ((B * N / P.fac[f] + nt - 1) / nt > inplace_pmax(P.fac[f], p2)) {
@@ -655,7 +653,8 @@ static int fft3d_bins(const TIN* f, Cx<R>* data, const Cx<double>* W, int N, int
   int Bmax = 32;
   while (Bmax > 1 && Bmax * N > 2048) Bmax >>= 1;
   while (Bmax > 1 && M % Bmax) Bmax >>= 1;
-  // lines per batch and threads per block of each pass, as in fft3d
+  // lines per batch and threads per block of each pass, as in fft3d (a row that
+  // the x pass gathers is half as long: its lines are columns at n2 and at -n2)
   int Bs[3], nts[3];
   for (int axis = 2; axis >= 0; --axis) {
     const int minB = axis == 2 ? 1 : std::min(Bmax, 8);

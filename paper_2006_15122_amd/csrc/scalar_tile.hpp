@@ -204,13 +204,6 @@ __device__ void finish_state(const ScalarArgs<T>& A, const PassDesc& pd, const D
   }
 }
 
-// In-place finish of the pass described by A (the batched path).
-template <typename T, int NF, bool FULL>
-__device__ void finish_from_sums(const ScalarArgs<T>& A, const double (&S)[Acc<NF, FULL>::N]) {
-  double an, bn;
-  finish_state<T, NF, FULL>(A, A.pd, A.st, S, A.st, an, bn);
-}
-
 // One block: combine the partials of all nblocks tiles in block order and
 // update the homogeneous state.
 // One block of kFinishThreads threads: four waves leave each thread the
