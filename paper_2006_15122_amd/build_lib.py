@@ -31,7 +31,8 @@ def masked_join_writes(asm: str) -> list:
 
     The block where a divergent branch joins is reached with the branch's mask,
     or with no lane at all where a wave skipped it, and has to widen the mask
-    (s_or_b64 exec) before anything else.  Under register pressure the compiler
+    (s_or_b64 exec; s_or_saveexec and s_andn2_saveexec ahead of an else) before
+    anything else.  Under register pressure the compiler
     has placed copies of live values, split in two there, ahead of that: the
     other lanes' values were lost.  An FP64 build of the SU(2) x U(1) pass
     computed its second plane from stale LDS addresses that way; nothing in the
@@ -51,7 +52,7 @@ def masked_join_writes(asm: str) -> list:
             prev = s
             if block is None:
                 continue
-            if s.startswith("s_or_b64 exec, exec,"):
+            if s.startswith(("s_or_b64 exec, exec,", "s_or_saveexec_b64", "s_andn2_saveexec_b64")):
                 if block:
                     found.append((kernel, label, block))
                 block = None

@@ -53,6 +53,14 @@ def test_a_mask_restored_first_passes(ahead):
     assert masked_join_writes(OUT_OF_LINE.format(join=".LBB0_1:", copies=ahead)) == []
 
 
+@pytest.mark.parametrize("turn", ["s_andn2_saveexec_b64 s[76:77], s[76:77]", "s_or_saveexec_b64 s[76:77], s[76:77]"])
+def test_a_copy_ahead_of_an_else_is_found(turn):
+    copy = "v_mov_b32_e32 v119, v188"
+    asm = JOIN.replace("s_or_b64 exec, exec, s[76:77]", turn)
+    assert masked_join_writes(asm.format(copies=f"\t{copy}\n")) == [("_Z4passv", ".LBB0_2", [copy])]
+    assert masked_join_writes(asm.format(copies="")) == []
+
+
 def test_a_body_that_ends_in_its_own_join_passes():
     # an if's body, entered with lanes: its writes are under the mask by right
     asm = JOIN.format(copies="\tv_mov_b32_e32 v119, v188\n")
