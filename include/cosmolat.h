@@ -255,7 +255,8 @@ const char* lattice_last_error(void);
    the built-in autotuner times them, once per model, size, precision,
    integrator and expansion in a process, so that later lattices of the same
    configuration share the tile and with it the order of their FP64 sums);
-   this call reports it.  SU(2) x U(1) passes are untiled (0, 0, 0, 0).  */
+   this call reports it.  SU(2) x U(1) passes have one tile, which is not set:
+   (0, 0, 0, 0).  */
 int lattice_get_tiling(lattice_t* h, int32_t* tz, int32_t* by, int32_t* ry, int32_t* xc);
 
 /* Force a tile shape (for the autotuner and tests).  Errors: LAT_EINVAL if

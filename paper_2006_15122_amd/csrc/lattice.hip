@@ -683,7 +683,7 @@ int scalar_energies(lattice* h) {
 // tiling
 // ---------------------------------------------------------------------------
 bool tiling_ok(const lattice* h, const Tiling& t) {
-  if (is_su2(h->p)) return false;  // its passes are untiled
+  if (is_su2(h->p)) return false;  // its passes have one tile
   bool compiled = false;
   const int fp32 = h->p.precision == LAT_FP32;
   const bool u1 = is_u1(h->p);

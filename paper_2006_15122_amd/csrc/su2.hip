@@ -147,13 +147,13 @@ __device__ void su2_block_partials(double (&acc)[NACC], double* partials) {
 // row y0-1 and the column z0-1 are computed by the waves without ring sites.
 //
 // Bound by its instruction stream: about 1600 VALU instructions a wave and
-// plane (45% of the issue slots at two waves per SIMD, which 251 VGPRs and
-// 79 KB of LDS per block allow).  In FP32 a pass takes 211 us at 128^3, 38 us
-// at 64^3 and 634 us at 192^3; a pointwise drift and a kick that read every
+// plane (46% of the issue slots at two waves per SIMD, which 247 VGPRs and
+// 79 KB of LDS per block allow).  In FP32 a pass takes 209 us at 128^3, 34 us
+// at 64^3 and 631 us at 192^3; a pointwise drift and a kick that read every
 // neighbour's links from memory took 484, 67 and 1560 us.  Ring threads in
 // waves of their own (six waves a block at 168 VGPRs) left one block on a CU
 // and spilled: 395 us.  FP64 takes half the tile so that a block's planes fit
-// (64^3: 126 us against 137, 96^3: 334 against 550).
+// (64^3: 122 us against 137, 96^3: 326 against 550).
 // ---------------------------------------------------------------------------
 template <typename T>
 struct Su2PassArgs {

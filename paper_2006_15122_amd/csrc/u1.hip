@@ -138,9 +138,9 @@ __global__ __launch_bounds__(1024) void u1_gauss_finish_kernel(const double* par
 // link), then by memory: ten fields in, ten out.  Addresses are a
 // scalar base per component and one 32-bit offset per lane, a stepping pass
 // sums only what the scale factor needs, and the blocks share the planes so
-// that all places on the GPU are taken: FP32 192^3 160 us a pass (3.5 TB/s;
+// that all places on the GPU are taken: FP32 192^3 157 us a pass (3.6 TB/s;
 // 196 with 64-bit lane addresses and equal blocks, 178 with equal blocks), 96^3
-// 38 us against 56, 64^3 23 against 34.
+// 33 us against 56, 64^3 20 against 34.
 // ---------------------------------------------------------------------------
 // One pass (as PassDesc of the scalar path, Sec. 3.3.2 merged kicks):
 //   a'  = a + wd h b,  a_mid = (a + a')/2
