@@ -319,3 +319,12 @@ def test_su2_pass_without_drift_takes_stored_phases_as_they_are(precision, N):
         st[key] = lat.get_state()[key]
     st["links"] = np.ascontiguousarray(np.stack([np.cos(th), np.sin(th)], axis=1))
     run_phases_over_many_turns(lat, 8, th, lambda: oracle.su2_sync_observe(oracle.su2_model(cfg), st))
+
+
+def test_su2_stored_phases_past_counting():
+    from test_gpu_u1 import run_phases_past_counting
+
+    cfg = _cfg(32, "fp32", integrator="lf2", e=0.5, g=0.5)
+    lat = _lattice(cfg)
+    _set(lat, oracle.su2_vacuum_ic(cfg))
+    run_phases_past_counting(lat, 8)

@@ -467,3 +467,26 @@ def test_u1_pass_without_drift_takes_stored_phases_as_they_are(precision, N):
     for k in ("phi", "pi", "piA"):
         st[k] = lat.get_state()[k]
     run_phases_over_many_turns(lat, 4, th, lambda: oracle.u1_sync_observe(oracle.u1_model(cfg), st))
+
+
+def run_phases_past_counting(lat, first):
+    """FP32 phases whose turns FP64 cannot count: their sines and cosines are
+    some angle's, so the energies and the start-up kick stay finite."""
+    import torch
+
+    rng = np.random.default_rng(9)
+    for i in range(3):
+        d = component(lat, first + i)
+        d.copy_(torch.from_numpy(rng.integers(-3, 4, (lat.N,) * 3) * 2.0 ** 100).to(d))
+    torch.cuda.synchronize()
+    assert all(np.isfinite(v).all() for v in lat.energies().values())
+    lat.step(0)
+    s = lat.get_state()
+    assert np.isfinite(s["pi"]).all() and np.isfinite(s["piA"]).all()
+
+
+def test_u1_stored_phases_past_counting():
+    st = synth.random_u1_state(32, seed=44, amp=0.6, link_angle=0.1, emom=0.5)
+    lat = _lattice(_cfg(32, "fp32", integrator="lf2"))
+    lat.set_state(st["phi"], st["pi"], 1.0, 0.5, links=st["links"], piA=st["piA"])
+    run_phases_past_counting(lat, 4)
